@@ -282,7 +282,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4))
     // Keypoint count: a host value, or (batches) a device value capped by it.
     int64_t n_all = n_host;
     if (n_dev) n_all = min(n_all, *n_dev);
-    const KeypointRange range = xcd_range(n_all);
+    const XcdRange range = xcd_range(n_all);
     const int64_t n = range.end;
     int64_t p = range.first;
     if (p >= n) return;

@@ -145,6 +145,7 @@ struct DenseMatchArgs {
     float ratio;
     int32_t *idx, *dist;
     uint8_t *accept;
+    int num_cus;
 };
 
 constexpr int kDenseMaxRadius = 8;

@@ -70,34 +70,7 @@ __device__ __forceinline__ uint32_t dot4(uint32_t a, uint32_t b, uint32_t acc)
     return __builtin_amdgcn_udot4(a, b, acc, false);
 }
 
-// The keypoints one workgroup of a grid-stride extraction takes.  The chip's
-// 8 XCDs (workgroups go to them round-robin by index) take contiguous eighths
-// of [0, n), so that one XCD's L2 holds the images (or, for keypoints in
-// raster order, the image rows) its own workgroups read, rather than every
-// XCD fetching every image; within its eighth an XCD's workgroups stride
-// over the keypoints.  Keypoint p of the range is first + m * stride.
-struct KeypointRange {
-    int64_t first, end, stride;
-};
-
-__device__ __forceinline__ KeypointRange xcd_range(int64_t n)
-{
-    constexpr int kXcds = 8;
-    const int g = gridDim.x, b = blockIdx.x;
-    KeypointRange r;
-    if (g < kXcds) {
-        r.first = b;
-        r.end = n;
-        r.stride = g;
-        return r;
-    }
-    const int xcd = b % kXcds;
-    const int64_t per = (n + kXcds - 1) / kXcds;
-    r.first = (int64_t)xcd * per + b / kXcds;
-    r.end = min(n, (int64_t)(xcd + 1) * per);
-    r.stride = (g - xcd + kXcds - 1) / kXcds;     // workgroups on this XCD
-    return r;
-}
+#include "xcd_range.h"
 
 // Rule steps 1-3 for one keypoint (uniform across the workgroup), with the
 // image it samples.

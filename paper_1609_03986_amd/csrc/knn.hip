@@ -25,6 +25,8 @@
 namespace latch {
 namespace {
 
+#include "fp4.h"
+
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
@@ -382,36 +384,12 @@ __device__ __forceinline__ void top2_pair(uint64_t &a1, uint64_t &a2, uint64_t c
 // fragments; QB = 2 is about 5% slower).
 // ---------------------------------------------------------------------------
 typedef float v16f __attribute__((ext_vector_type(16)));
-typedef int v8i __attribute__((ext_vector_type(8)));
 
 constexpr int kFp4Steps = 8;                          // K = 512 = 8 x 64
 constexpr int kFp4TileVec = kFp4Steps * 64;           // 16-byte fragments per tile (512)
 constexpr int kFp4ScaleTrain = 127;                   // E8M0 2^0
 constexpr int kFp4ScaleQuery = 127 + 14;              // E8M0 2^14
 constexpr float kFp4None = -33554432.0f;              // -2^25
-
-// Train word -> its four FP4 dwords (0 or c per bit, c = 0.5, 1, 2, 2).
-__device__ __forceinline__ uint4 fp4_train(uint32_t w)
-{
-    return make_uint4(w & 0x11111111u, w & 0x22222222u, w & 0x44444444u, (w >> 1) & 0x44444444u);
-}
-
-// Per nibble: `one` where m has its bit 0 set, `minus` elsewhere (m holds
-// bit 0 of each nibble only, so m * 15 is a nibble mask without carries).
-__device__ __forceinline__ uint32_t fp4_select(uint32_t m, uint32_t one, uint32_t minus)
-{
-    const uint32_t mask = m * 0xfu;
-    return (one & mask) | (minus & ~mask);
-}
-
-// Query word -> its four FP4 dwords (+-1 / c per bit: +-2, +-1, +-0.5, +-0.5).
-__device__ __forceinline__ uint4 fp4_query(uint32_t w)
-{
-    return make_uint4(fp4_select(w & 0x11111111u, 0x44444444u, 0xccccccccu),
-                      fp4_select((w >> 1) & 0x11111111u, 0x22222222u, 0xaaaaaaaau),
-                      fp4_select((w >> 2) & 0x11111111u, 0x11111111u, 0x99999999u),
-                      fp4_select((w >> 3) & 0x11111111u, 0x11111111u, 0x99999999u));
-}
 
 // Two keys into a running top two (k1 >= k2), as insert_pair_u32 does for
 // integer keys: t = med3(k1, x, y), k1 = max3(k1, x, y), k2 = max(k2, t), as
@@ -426,16 +404,6 @@ __device__ __forceinline__ void insert_pair(float &k1, float &k2, float x, float
         "v_max_f32 %1, %1, %2"
         : "+v"(k1), "+v"(k2), "=&v"(t)
         : "v"(x), "v"(y));
-}
-
-__device__ __forceinline__ v8i fp4_operand(uint4 f)
-{
-    v8i r = {};
-    r[0] = (int)f.x;
-    r[1] = (int)f.y;
-    r[2] = (int)f.z;
-    r[3] = (int)f.w;
-    return r;
 }
 
 // Staging role of a thread: tile row tid % 32, packed words 2 (tid / 32) and

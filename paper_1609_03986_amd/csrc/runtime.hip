@@ -998,6 +998,7 @@ int hamming_knn_window(latch_handle h, const uint32_t *query_dev, const uint32_t
     a.idx = idx_dev;
     a.dist = dist_dev;
     a.accept = accept_dev;
+    a.num_cus = h->num_cus;
     const hipError_t e =
         timed_launch(h, "knn_window", stream, [&] { return launch_dense_match(a, stream); });
     return e == hipSuccess ? LATCH_OK : hip_fail(h, e, "dense match launch");

@@ -89,6 +89,28 @@ def test_window_matching_matches_oracle(torch_cuda, lat, radius, k):
     assert np.array_equal(acc.cpu().numpy(), wa)
 
 
+@pytest.mark.parametrize("radius", [0, 1, 2, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("gw,gh", [(1, 1), (3, 40), (16, 16), (17, 33), (70, 5)])
+def test_window_matching_tile_edges(torch_cuda, lat, radius, gw, gh):
+    """Grids at the edges of the 16 x 16 tiles and 4 x 4 query blocks, every
+    region margin, with distances from 0 to 512 (all-zero and all-one
+    descriptors among tie-heavy ones): equal to the oracle."""
+    torch = torch_cuda
+    g = np.random.default_rng(70 + radius)
+    q = synth.random_descriptors(g, gw * gh, 0.05)
+    t = synth.random_descriptors(g, gw * gh, 0.5)
+    for a in (q, t):
+        a[g.random(len(a)) < 0.2] = 0
+        a[g.random(len(a)) < 0.2] = 0xffffffff
+    idx, dist, acc = lat.knn_window(torch.from_numpy(q.view(np.int32)).cuda(),
+                                    torch.from_numpy(t.view(np.int32)).cuda(), gw, gh, radius)
+    torch.cuda.synchronize()
+    wi, wd, wa = oracle.knn_window(q, t, gw, gh, radius, 2, 0.8)
+    assert np.array_equal(idx.cpu().numpy(), wi)
+    assert np.array_equal(dist.cpu().numpy(), wd)
+    assert np.array_equal(acc.cpu().numpy(), wa)
+
+
 def test_dense_flow_of_a_shifted_twin(torch_cuda, lat, triplets):
     """Dense descriptors of an image and its copy shifted by (3, 2) with noise,
     matched within radius 4: oracle parity on a sample, and most accepted
