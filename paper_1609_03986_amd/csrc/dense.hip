@@ -9,11 +9,28 @@
 //     G(q) = (I(q + c1) - I(q + c2)) (I(q + c1) + I(q + c2) - 2 I(q + a)),
 // with a, c1, c2 the centres minus (24, 24): bit = [box7x7(G)(p) > 0].  So a
 // workgroup that owns a tile of pixels evaluates G once per position and
-// triplet, sums it over 7 rows with a running sum held in registers (lane =
-// column, walking down the rows) and over 7 columns across lanes: about 10
-// operations per pixel and triplet instead of 3 x 49 products.  |G| <= 130,050
-// and the box sum < 2^23, so int32 is exact, and the result is bit-identical
+// triplet and sums it over 7 rows and 7 columns, instead of 3 x 49 products per
+// pixel and triplet.  |G| <= 130,050, a column's prefix sum over 38 rows and the
+// box sum stay below 2^23, so int32 is exact, and the result is bit-identical
 // to extracting at every pixel.
+//
+// A lane holds two neighbouring columns.  Their pixels are one dword of 16-bit
+// lanes (two copies of the window in LDS, one shifted by a pixel, make that so
+// for odd offsets too), so the two factors of -G take three packed instructions
+// per two pixels, and v_mad_i32_i16 adds their product to each column's prefix
+// sum; two prefix sums 7 rows apart differ by a 7-row sum.  The 7-column sums of
+// two columns share the sums of column pairs: six adds with the neighbour's value
+// through DPP and one without, for two outputs.  The sign of a sum is shifted
+// into the output word by one v_alignbit.  In all 16 instructions per two pixels
+// and triplet, plus 5 for the 6 rows of halo.
+//
+// What bounds it: vector issue, 88% of the time on the SIMDs of a 1920 x 1080
+// frame.  One column per lane with byte pixels took 14 instructions per pixel
+// (and 6 of 64 lanes of halo, now 6 of 128 columns): 618 -> 320 us there,
+// 258 -> 51 us for 64 x 48, where a workgroup now computes 4 of the 16 words and
+// the tile's 512 triplets spread over 4 workgroups.  The words of a pixel leave
+// as 16 bytes through LDS: HBM writes fell from 629 MB to the 130 MB of the
+// output.
 //
 // Dense matching: per query pixel, the two nearest train pixels by Hamming
 // distance within +/- R rows and columns (R <= 8), ties to the lower raster
@@ -29,39 +46,26 @@ namespace latch {
 namespace {
 
 #include "fp4.h"
+#include "packed16.h"
 #include "xcd_range.h"
 
 constexpr int kDThreads = 256;
-constexpr int kDTileW = 58;                         // output columns: lanes 0..57 (+6 halo lanes)
+constexpr int kDTileW = 122;                        // output columns: 2 l, 2 l + 1 of lanes 0..60
 constexpr int kDTileH = 32;                         // output rows per workgroup
+constexpr int kDWords = 4;                          // descriptor words per workgroup, one per wavefront
 constexpr int kDRegionRows = kDTileH + 6;           // rows of G per tile
 constexpr int kDTexRows = kDRegionRows + 41;        // image rows: 79
-constexpr int kDTexCols = 64 + 41;                  // image columns: 105
-constexpr int kDTexStride = 108;
-constexpr int kDTexLoads = (kDTexRows * kDTexCols + kDThreads - 1) / kDThreads;   // 33
-
-__device__ __forceinline__ int mul24(int a, int b)
-{
-    int r;
-    asm("v_mul_i32_i24 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-
-// a b + c with 24-bit signed a, b (b an inline constant here).
-__device__ __forceinline__ int mad24(int a, int b, int c)
-{
-    int r;
-    asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "i"(b), "v"(c));
-    return r;
-}
-
-// 1 if h > 0, else 0, in one instruction (median of h, 0 and 1).
-__device__ __forceinline__ uint32_t bit_of(int h)
-{
-    int r;
-    asm("v_med3_i32 %0, %1, 0, 1" : "=v"(r) : "v"(h));
-    return (uint32_t)r;
-}
+constexpr int kDTexQuads = 43;                      // image columns in fours: 172 (128 + 41 are read)
+constexpr int kDRowBytes = 2 * 170;                 // a row of 16-bit pixels: 85 dwords
+constexpr int kDCopyBytes = kDTexRows * kDRowBytes;
+constexpr int kDUnits = kDTexRows * kDTexQuads;
+constexpr int kDLoads = (kDUnits + kDThreads - 1) / kDThreads;
+constexpr int kDGroup = 3;                          // texture rows read together
+constexpr int kDOutRows = 16;                       // rows per pass of the output transpose
+constexpr int kDLdsBytes = 2 * kDCopyBytes + 8;     // 3 workgroups per CU
+static_assert(2 * kDCopyBytes <= 65536, "16-bit patch offsets");
+static_assert(3 * kDLdsBytes <= kLdsPerCu, "three workgroups per CU");
+static_assert(kDOutRows * 128 * 16 <= kDLdsBytes && kDTileH % kDOutRows == 0, "output transpose fits");
 
 // Lane l receives lane l + 1's value (DPP wave_shl:1; lane 63 receives 0
 // through bound_ctrl, so no old value has to be set up).
@@ -70,86 +74,175 @@ __device__ __forceinline__ int lane_next(int v)
     return __builtin_amdgcn_mov_dpp(v, 0x130, 0xF, 0xF, true);
 }
 
-// Sum of v over lanes l .. l + 6 (only lanes 0 .. 57 are used), in Horner
-// form t = v + (t of the next lane), six times: each step is one add whose
-// shifted operand comes through DPP (whole-wavefront shift), with no LDS
-// traffic.
-__device__ __forceinline__ int sum7_down(int v)
+// bits = bits << 1 | sign of h, in place.
+__device__ __forceinline__ void shift_in_sign(uint32_t &bits, int h)
 {
-    int t = v;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) t = v + lane_next(t);
-    return t;
+    asm("v_alignbit_b32 %0, %0, %1, 31" : "+v"(bits) : "v"(h));
 }
 
-__global__ __launch_bounds__(kDThreads) void dense_extract_kernel(
-    const uint8_t *__restrict__ img, int height, int width, int pitch, int x0, int y0, int gw, int gh,
-    int tiles_x, const uint2 *__restrict__ toff, uint32_t *__restrict__ desc)
+// The image window of a tile, in LDS as 16-bit pixels in two copies: copy 0
+// holds pixel (row, x) at element x of row `row`, copy 1 at element x - 1, so
+// that the pixels x, x + 1 of any column x are one dword of copy x & 1.
+// kInside: every column lies in the image and four pixels are one (unaligned)
+// load; otherwise columns clamp to the image one by one (the rule's
+// clamp-to-edge).  Rows clamp either way.
+template <bool kInside>
+__device__ __forceinline__ void stage_texture(const uint8_t *__restrict__ img, int height, int width,
+                                              int pitch, int xs, int ys, uint8_t *__restrict__ tex)
 {
-    __shared__ uint8_t tex[(kDTexLoads * kDThreads + kDTexCols - 1) / kDTexCols * kDTexStride];
-    const int tx = (int)(blockIdx.x % (unsigned)tiles_x), ty = (int)(blockIdx.x / (unsigned)tiles_x);
-    const int X0 = x0 + tx * kDTileW, Y0 = y0 + ty * kDTileH;
+    constexpr int kBatch = kInside ? 7 : 4;               // loads (of four pixels) in flight
+    for (int k0 = 0; k0 < kDLoads; k0 += kBatch) {
+        uint32_t v[kBatch];
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k) {
+            const int i = min((int)threadIdx.x + (k0 + k) * kDThreads, kDUnits - 1);
+            const int x = xs + 4 * (i % kDTexQuads);
+            const uint8_t *row = img + (size_t)min(max(ys + i / kDTexQuads, 0), height - 1) * pitch;
+            if constexpr (kInside) {
+                __builtin_memcpy(&v[k], row + x, 4);
+            } else {
+                uint32_t w = 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    w |= (uint32_t)row[min(max(x + j, 0), width - 1)] << (8 * j);
+                v[k] = w;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k) {
+            const int i = (int)threadIdx.x + (k0 + k) * kDThreads;
+            if (i >= kDUnits) break;
+            const int q = i % kDTexQuads;
+            uint8_t *to = tex + i / kDTexQuads * kDRowBytes + 8 * q;
+            const uint32_t p01 = __builtin_amdgcn_perm(0, v[k], 0x0c010c00), p12 = __builtin_amdgcn_perm(0, v[k], 0x0c020c01),
+                           p23 = __builtin_amdgcn_perm(0, v[k], 0x0c030c02);
+            // Columns 170 and 171 of the last quad would land in the next row.
+            *reinterpret_cast<uint32_t *>(to) = p01;
+            if (q < kDTexQuads - 1) *reinterpret_cast<uint32_t *>(to + 4) = p23;
+            uint8_t *to1 = to + kDCopyBytes;
+            if (q > 0) *reinterpret_cast<uint16_t *>(to1 - 2) = (uint16_t)p01;
+            *reinterpret_cast<uint32_t *>(to1) = p12;
+            if (q < kDTexQuads - 1) *reinterpret_cast<uint16_t *>(to1 + 4) = (uint16_t)(p23 >> 16);
+        }
+    }
+}
+
+// Block b covers words 4 y .. 4 y + 3 of tile t; the four blocks of a tile run
+// on one XCD (workgroups go to the 8 XCDs round-robin by index), whose L2 then
+// joins their quarters of each 64-byte descriptor.
+__global__ __launch_bounds__(kDThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void
+dense_extract_kernel(const uint8_t *__restrict__ img, int height, int width, int pitch, int x0, int y0,
+                     int gw, int gh, int tiles_x, int tiles, const uint2 *__restrict__ toff,
+                     uint32_t *__restrict__ desc)
+{
+    __shared__ __align__(16) uint8_t tex[kDLdsBytes];
+    const int local = (int)(blockIdx.x >> 3);
+    const int tile = (local / (kWords / kDWords)) * 8 + (int)(blockIdx.x & 7);
+    const int part = local % (kWords / kDWords);
+    if (tile >= tiles) return;
+    const int X0 = x0 + tile % tiles_x * kDTileW, Y0 = y0 + tile / tiles_x * kDTileH;
     const int t = threadIdx.x;
     const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
 
-    // Image rows Y0 - 24 .. Y0 + 54 and columns X0 - 24 .. X0 + 80, clamped
-    // to the image (the rule's clamp-to-edge); three batches of 11 loads in
-    // flight, so that the staging does not set the kernel's register count.
-    static_assert(kDTexLoads == 33, "three batches of 11");
-#pragma unroll
-    for (int batch = 0; batch < 3; ++batch) {
-        uint32_t v[11];
-#pragma unroll
-        for (int k = 0; k < 11; ++k) {
-            const int i = t + (11 * batch + k) * kDThreads;
-            const int yy = min(max(Y0 - 24 + i / kDTexCols, 0), height - 1);
-            const int xx = min(max(X0 - 24 + i % kDTexCols, 0), width - 1);
-            v[k] = img[(size_t)yy * pitch + xx];
-        }
-#pragma unroll
-        for (int k = 0; k < 11; ++k) {
-            const int i = t + (11 * batch + k) * kDThreads;
-            tex[(i / kDTexCols) * kDTexStride + i % kDTexCols] = (uint8_t)v[k];
-        }
-    }
+    // Image rows Y0 - 24 .. Y0 + 54 and columns X0 - 24 .. X0 + 147.
+    const int xs = X0 - 24, ys = Y0 - 24;
+    if (xs >= 0 && xs + 4 * kDTexQuads <= width)
+        stage_texture<true>(img, height, width, pitch, xs, ys, tex);
+    else
+        stage_texture<false>(img, height, width, pitch, xs, ys, tex);
     __syncthreads();
 
-    // Wavefront w computes output words w, w + 4, w + 8, w + 12.
-    for (int word = wave; word < kWords; word += 4) {
-        uint32_t bits[kDTileH];
+    const int word = kDWords * part + wave;
+    uint32_t bits[kDTileH][2];                      // of columns 2 l, 2 l + 1
 #pragma unroll
-        for (int o = 0; o < kDTileH; ++o) bits[o] = 0u;
-        for (int b = 0; b < 32; ++b) {
-            const uint2 off = toff[32 * word + b];           // uniform: scalar loads
-            const uint8_t *pa = tex + lane + (off.x & 0xffffu);
-            const uint8_t *p1 = tex + lane + (off.x >> 16);
-            const uint8_t *p2 = tex + lane + off.y;
-            int ring[7];
-            int s = 0;
+    for (int o = 0; o < kDTileH; ++o) bits[o][0] = bits[o][1] = 0u;
+    for (int b = 0; b < 32; ++b) {
+        const uint2 off = toff[32 * word + b];      // uniform: scalar loads
+        const uint8_t *pa = tex + 4 * lane + (off.x & 0xffffu);
+        const uint8_t *p1 = tex + 4 * lane + (off.x >> 16);
+        const uint8_t *p2 = tex + 4 * lane + off.y;
+        int pre0[7], pre1[7];                       // prefix sums of -G down the two columns
+        int s0 = 0, s1 = 0, v0[2], v1[2];
+        // Rows are read in groups, one group ahead of their use; the groups are
+        // kept apart (left alone, the compiler reads most rows first and
+        // spills).
+        short2v px[2][kDGroup][3];
+        auto read_rows = [&](int rr) {
 #pragma unroll
-            for (int rr = 0; rr < kDRegionRows; ++rr) {
-                const int a = pa[rr * kDTexStride], c1 = p1[rr * kDTexStride], c2 = p2[rr * kDTexStride];
-                const int g = mul24(c1 - c2, mad24(a, -2, c1 + c2));
-                ring[rr % 7] = g;
-                s += g;
-                if (rr >= 6) {
-                    const int h = sum7_down(s);                // box over rows rr-6..rr, columns l..l+6
-                    // Shift in from the right: triplet b ends at bit 31 - b.
-                    bits[rr - 6] = (bits[rr - 6] << 1) | bit_of(h);
-                    s -= ring[(rr - 6) % 7];
+            for (int k = 0; k < kDGroup; ++k) {
+                if (rr + k >= kDRegionRows) break;
+                short2v *to = px[rr / kDGroup & 1][k];
+                to[0] = *reinterpret_cast<const short2v *>(pa + (rr + k) * kDRowBytes);
+                to[1] = *reinterpret_cast<const short2v *>(p1 + (rr + k) * kDRowBytes);
+                to[2] = *reinterpret_cast<const short2v *>(p2 + (rr + k) * kDRowBytes);
+            }
+        };
+        read_rows(0);
+#pragma unroll
+        for (int rr = 0; rr < kDRegionRows; ++rr) {
+            if (rr % kDGroup == 0) {
+                __builtin_amdgcn_sched_barrier(0);
+                read_rows(rr + kDGroup);
+            }
+            const short2v *at = px[rr / kDGroup & 1][rr % kDGroup];
+            const short2v a = at[0], c1 = at[1], c2 = at[2];
+            const short2v d = c2 - c1;
+            const short2v s = pk_mad_i16(a, kPkMinus2, c1 + c2);
+            s0 = mad_i32_lo16(d, s, s0);
+            s1 = mad_i32_hi16(d, s, s1);
+            if (rr >= 6) {
+                // Rows rr - 6 .. rr of the two columns.
+                v0[rr & 1] = rr > 6 ? s0 - pre0[rr % 7] : s0;
+                v1[rr & 1] = rr > 6 ? s1 - pre1[rr % 7] : s1;
+            }
+            if (rr > 6 && (rr & 1)) {
+                // Seven columns from each, for two rows: with p = v0 + v1 and
+                // lanes l, l + 1, ..: p + p + p + v0 and v1 + p + p + p, in
+                // Horner form, the four chains in step (a DPP operand is not to
+                // be one of the last two results).
+                int h[2][2];
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    h[k][0] = v0[k];
+                    h[k][1] = v0[k] + v1[k];
                 }
+                const int p[2] = {h[0][1], h[1][1]};
+#pragma unroll
+                for (int step = 0; step < 3; ++step)
+#pragma unroll
+                    for (int c = 0; c < 2; ++c)
+#pragma unroll
+                        for (int k = 0; k < 2; ++k)
+                            h[k][c] = (c == 1 && step == 2 ? v1[k] : p[k]) + lane_next(h[k][c]);
+                // Shift the sign (box sum of G > 0) in from the right: triplet b
+                // ends at bit 31 - b.
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) shift_in_sign(bits[rr - 7 + k][c], h[k][c]);
             }
+            pre0[rr % 7] = s0;
+            pre1[rr % 7] = s1;
         }
+    }
+
+    // The four wavefronts' words of a pixel meet in LDS and leave as 16 bytes.
 #pragma unroll
-        for (int o = 0; o < kDTileH; ++o) bits[o] = __builtin_bitreverse32(bits[o]);
-        const int px = X0 + lane;
-        if (lane < kDTileW && px < x0 + gw) {
+    for (int o0 = 0; o0 < kDTileH; o0 += kDOutRows) {
+        __syncthreads();                            // texture or the previous rows are read
 #pragma unroll
-            for (int o = 0; o < kDTileH; ++o) {
-                const int py = Y0 + o;
-                if (py < y0 + gh)
-                    desc[((size_t)(py - y0) * gw + (px - x0)) * kWords + word] = bits[o];
-            }
+        for (int o = 0; o < kDOutRows; ++o)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+                reinterpret_cast<uint32_t *>(tex)[((2 * o + c) * 64 + lane) * kDWords + wave] =
+                    __builtin_bitreverse32(bits[o0 + o][c]);
+        __syncthreads();
+        for (int i = t; i < kDOutRows * kDTileW; i += kDThreads) {
+            const int o = i / kDTileW, c = i % kDTileW;
+            const int px = X0 - x0 + c, py = Y0 - y0 + o0 + o;
+            if (px < gw && py < gh)
+                reinterpret_cast<uint4 *>(desc)[((size_t)py * gw + px) * (kWords / 4) + part] =
+                    reinterpret_cast<const uint4 *>(tex)[(2 * o + (c & 1)) * 64 + (c >> 1)];
         }
     }
 }
@@ -631,15 +724,18 @@ __global__ __launch_bounds__(kDThreads) void window_popcount_kernel(
 
 uint32_t dense_patch_offset(int r, int c)
 {
-    return (uint32_t)((r - 3) * kDTexStride + (c - 3));
+    const int x = c - 3;
+    return (uint32_t)((x & 1) * kDCopyBytes + (r - 3) * kDRowBytes + 4 * (x >> 1));
 }
 
 hipError_t launch_dense_extract(const DenseArgs &a, hipStream_t stream)
 {
-    const int tiles_x = (a.gw + kDTileW - 1) / kDTileW;
-    const int64_t tiles = (int64_t)tiles_x * ((a.gh + kDTileH - 1) / kDTileH);
-    hipLaunchKernelGGL(dense_extract_kernel, dim3((unsigned)tiles), dim3(kDThreads), 0, stream, a.img,
-                       a.height, a.width, a.pitch, a.x0, a.y0, a.gw, a.gh, tiles_x, a.toff, a.desc);
+    const int tiles_x = (int)(((int64_t)a.gw + kDTileW - 1) / kDTileW);
+    const int64_t tiles = tiles_x * (((int64_t)a.gh + kDTileH - 1) / kDTileH);
+    const int64_t blocks = (tiles + 7) / 8 * 8 * (kWords / kDWords);
+    hipLaunchKernelGGL(dense_extract_kernel, dim3((unsigned)blocks), dim3(kDThreads), 0, stream, a.img,
+                       a.height, a.width, a.pitch, a.x0, a.y0, a.gw, a.gh, tiles_x, (int)tiles, a.toff,
+                       a.desc);
     return hipGetLastError();
 }
 

@@ -31,8 +31,7 @@ namespace latch {
 namespace {
 
 #include "keypoint.h"
-
-typedef short short2v __attribute__((ext_vector_type(2)));
+#include "packed16.h"
 
 constexpr int kWThreads = 256;
 
@@ -139,17 +138,6 @@ __device__ __forceinline__ void load_row_pair(uint32_t pa, uint32_t pc, uint32_t
         : "memory");
 }
 
-// c + a b per 16-bit half (v_pk_mad_i16; the compiler splits the multiply-add
-// of 16-bit vectors into a shift, an add and a subtract).  b is uniform.
-__device__ __forceinline__ short2v pk_mad_i16(short2v a, uint32_t b, short2v c)
-{
-    uint32_t r;
-    asm("v_pk_mad_i16 %0, %1, %2, %3"
-        : "=v"(r)
-        : "v"(__builtin_bit_cast(uint32_t, a)), "s"(b), "v"(__builtin_bit_cast(uint32_t, c)));
-    return __builtin_bit_cast(short2v, r);
-}
-
 // One patch row (4 pixel pairs) of sum w d s.
 __device__ __forceinline__ void weighted_row(const uint32_t *wrow, uint64_t a0, uint64_t a1, uint64_t c0,
                                              uint64_t c1, uint64_t e0, uint64_t e1, int &acc)
@@ -157,7 +145,6 @@ __device__ __forceinline__ void weighted_row(const uint32_t *wrow, uint64_t a0, 
     const uint32_t av[4] = {(uint32_t)a0, (uint32_t)(a0 >> 32), (uint32_t)a1, (uint32_t)(a1 >> 32)};
     const uint32_t cv[4] = {(uint32_t)c0, (uint32_t)(c0 >> 32), (uint32_t)c1, (uint32_t)(c1 >> 32)};
     const uint32_t ev[4] = {(uint32_t)e0, (uint32_t)(e0 >> 32), (uint32_t)e1, (uint32_t)(e1 >> 32)};
-    constexpr uint32_t kMinus2 = 0xfffefffeu;       // -2 in both 16-bit halves
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const short2v wv = __builtin_bit_cast(short2v, wrow[i]);
@@ -165,7 +152,7 @@ __device__ __forceinline__ void weighted_row(const uint32_t *wrow, uint64_t a0, 
         const short2v P1 = __builtin_bit_cast(short2v, cv[i]);
         const short2v P2 = __builtin_bit_cast(short2v, ev[i]);
         const short2v d = P1 - P2;
-        const short2v s = pk_mad_i16(A, kMinus2, P1 + P2);
+        const short2v s = pk_mad_i16(A, kPkMinus2, P1 + P2);
         acc = __builtin_amdgcn_sdot2(wv * d, s, acc, false);
     }
 }

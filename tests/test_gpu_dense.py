@@ -57,6 +57,27 @@ def test_dense_equals_sparse_path(torch_cuda, lat):
     assert torch.equal(d, s)
 
 
+@pytest.mark.parametrize("gw,gh", [(1, 1), (121, 31), (122, 32), (123, 33), (245, 65)])
+@pytest.mark.parametrize("x0,pad,shift", [(24, 0, 0), (25, 3, 1), (-3, 1, 0)])
+def test_dense_tile_edges(torch_cuda, lat, triplets, gw, gh, x0, pad, shift):
+    """Regions at the edges of the 122 x 32 tiles, in an image that just holds
+    a tile's 172 columns, with padded rows and an unaligned first pixel: every
+    descriptor equals single-keypoint extraction, a sample the oracle."""
+    torch = torch_cuda
+    g = np.random.default_rng(80 + gw)
+    H, W = gh + 7, x0 + 148 + max(0, (gw - 1) // 122 * 122)
+    whole = g.integers(0, 256, H * (W + pad) + shift, dtype=np.uint8)
+    img = torch.from_numpy(whole).cuda()[shift:].view(H, W + pad)[:, :W]
+    d = lat.extract_dense(img, x0, 2, gw, gh)
+    kps = oracle.dense_keypoints(x0, 2, gw, gh)
+    one = lat.extract(img, torch.from_numpy(kps).cuda())
+    torch.cuda.synchronize()
+    assert torch.equal(d, one)
+    sel = np.arange(0, gw * gh, 61)
+    want, _ = oracle.extract(np.ascontiguousarray(img.cpu().numpy()), kps[sel], triplets)
+    assert np.array_equal(u32(d)[sel], want)
+
+
 def test_dense_hd_sampled(torch_cuda, lat, triplets):
     """Every pixel of the 1920 x 1080 bench image in one launch; every 997th
     descriptor against the oracle."""
