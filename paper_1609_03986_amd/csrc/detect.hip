@@ -18,20 +18,30 @@
 //     boundary that the bin does not depend on the last bits of atan2), and
 //     the keypoint angle bin * 360 / 4096 degrees, exact in float.
 //
-// Three launches:
+// Two launches, or three for large images:
 //   1. detect_tile_kernel: a 64 x 16 tile per workgroup.  The image tile with
-//      a 4-pixel halo is staged in LDS, scores of the tile and a 1-pixel halo
-//      go to LDS, and each wavefront's ballot over one tile row is that row's
+//      a 4-pixel halo is staged in LDS; the pixels of the tile and a 1-pixel
+//      halo that pass a test on four of the circle's pixels are listed and
+//      scored, and each wavefront's ballot over one tile row is that row's
 //      64-bit survivor mask; the mask and its popcount (one byte per row and
-//      tile, rows of the count array padded to 16 bytes) go to the workspace.
-//   2. detect_scan_kernel: one workgroup sums each row's count bytes (two
-//      rows per thread) and scans them into each row's first output slot and
-//      the new total.
+//      tile, rows of the count array padded to 16 bytes) go to the workspace,
+//      with the tile's total or, in large images, without.
+//   2. detect_scan_kernel, in large images: one workgroup sums each row's count
+//      bytes (two rows per thread) and scans them into each row's first output
+//      slot and the new total.
 //   3. detect_emit_kernel: per tile, the image window of every disc staged in
-//      LDS; per tile row, the slot of each survivor from the row's first slot,
-//      the count bytes of the tiles to its left and the mask, its orientation
-//      with one disc row per lane (two keypoints per wavefront), then the
-//      keypoint written once, complete.
+//      LDS; the slot of each survivor from what precedes its row (the scan's
+//      slots, or the totals and counts) and the mask, its orientation with one
+//      disc row per lane (two keypoints per wavefront), then the keypoint
+//      written once, complete.
+//
+// What bounds it (1920 x 1080, 55,000 keypoints at threshold 20): every
+// workgroup of a launch is resident at once, so a launch takes its few
+// microseconds of start and staging latency plus its vector work, 407
+// instructions per wavefront in the tile kernel (5 of 12 us) and 690 in the emit
+// kernel (9 of 15 us).  Scoring every pixel one per lane took 17 us, the scan
+// 4 us and an emit kernel that ran a double atan2 in every wavefront 17 us: 37.7
+// -> 25.0 us per call.  39% of that image's pixels pass the four-pixel test.
 #include "internal.h"
 
 namespace latch {
@@ -47,38 +57,55 @@ constexpr int kScanThreads = 1024;
 constexpr int kDiscRows = 2 * kOrientRadius + 1;       // 31
 
 // Circle offsets, clockwise from the top (y downwards).
-__constant__ int2 kCircle[16] = {{0, -3}, {1, -3},  {2, -2},  {3, -1}, {3, 0},   {3, 1},
-                                 {2, 2},  {1, 3},   {0, 3},   {-1, 3}, {-2, 2},  {-3, 1},
-                                 {-3, 0}, {-3, -1}, {-2, -2}, {-1, -3}};
+struct Offset {
+    int x, y;
+};
+constexpr Offset kCircle[16] = {{0, -3}, {1, -3},  {2, -2},  {3, -1}, {3, 0},   {3, 1},
+                                {2, 2},  {1, 3},   {0, 3},   {-1, 3}, {-2, 2},  {-3, 1},
+                                {-3, 0}, {-3, -1}, {-2, -2}, {-1, -3}};
 
-// FAST-9 score of the pixel at p (an LDS image tile of row stride kImgW).
-__device__ __forceinline__ int fast_score(const uint8_t *p)
+typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
+typedef short short2v __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ ushort2v pk_min(ushort2v a, ushort2v b) { return __builtin_elementwise_min(a, b); }
+__device__ __forceinline__ ushort2v pk_max(ushort2v a, ushort2v b) { return __builtin_elementwise_max(a, b); }
+
+// FAST-9 scores of the two pixels at p and q (an LDS image tile of row stride
+// kImgW), one per 16-bit half.  On the circle values themselves: the best arc
+// of 9 for "brighter" has the largest minimum, that for "darker" the smallest
+// maximum, and the centre is subtracted at the end.  The arcs from k and from
+// k + 1 share the 8 pixels k + 1 .. k + 8, so the better of the two is
+// min(min of those 8, max of pixels k and k + 9): 8 such pairs.
+__device__ __forceinline__ short2v fast_scores(const uint8_t *p, const uint8_t *q)
 {
-    const int c = p[0];
-    int d[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) d[i] = (int)p[kCircle[i].y * kImgW + kCircle[i].x] - c;
-    // Smallest (brighter) and largest (darker) difference on each arc of 9,
-    // by doubling: arcs of 2, 4, 8, then 9.
-    int lo2[16], hi2[16], lo4[16], hi4[16];
+    ushort2v d[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-        lo2[i] = min(d[i], d[(i + 1) & 15]);
-        hi2[i] = max(d[i], d[(i + 1) & 15]);
+        const int off = kCircle[i].y * kImgW + kCircle[i].x;
+        d[i] = ushort2v{p[off], q[off]};
     }
+    ushort2v lo[8], hi[8];                                  // arcs of 2, then 4, from odd pixels
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        lo4[i] = min(lo2[i], lo2[(i + 2) & 15]);
-        hi4[i] = max(hi2[i], hi2[(i + 2) & 15]);
+    for (int i = 0; i < 8; ++i) {
+        lo[i] = pk_min(d[2 * i + 1], d[(2 * i + 2) & 15]);
+        hi[i] = pk_max(d[2 * i + 1], d[(2 * i + 2) & 15]);
     }
-    int best = -256;
+    ushort2v lo4[8], hi4[8];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int lo9 = min(min(lo4[i], lo4[(i + 4) & 15]), d[(i + 8) & 15]);
-        const int hi9 = max(max(hi4[i], hi4[(i + 4) & 15]), d[(i + 8) & 15]);
-        best = max(best, max(lo9, -hi9));
+    for (int i = 0; i < 8; ++i) {
+        lo4[i] = pk_min(lo[i], lo[(i + 1) & 7]);
+        hi4[i] = pk_max(hi[i], hi[(i + 1) & 7]);
     }
-    return best;
+    ushort2v best_lo = ushort2v{0, 0}, best_hi = ushort2v{255, 255};
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const ushort2v a = d[2 * i], b = d[(2 * i + 9) & 15];
+        best_lo = pk_max(best_lo, pk_min(pk_min(lo4[i], lo4[(i + 2) & 7]), pk_max(a, b)));
+        best_hi = pk_min(best_hi, pk_max(pk_max(hi4[i], hi4[(i + 2) & 7]), pk_min(a, b)));
+    }
+    const short2v c = {(short)p[0], (short)q[0]};
+    return __builtin_elementwise_max(__builtin_bit_cast(short2v, best_lo) - c,
+                                     c - __builtin_bit_cast(short2v, best_hi));
 }
 
 // Copies rows ry0 .. ry0 + kRows - 1 and columns cx0 .. cx0 + kCols - 1 of
@@ -135,49 +162,101 @@ constexpr int stage_lds_rows()
 template <bool kDword>
 __global__ __launch_bounds__(kThreads) void detect_tile_kernel(
     const uint8_t *__restrict__ img, int height, int width, int pitch, int threshold, int tiles_x,
-    uint64_t *__restrict__ masks, uint8_t *__restrict__ counts, int count_stride)
+    uint64_t *__restrict__ masks, uint8_t *__restrict__ counts, int count_stride,
+    uint16_t *__restrict__ tile_total, const int64_t *__restrict__ n_kps, int64_t *__restrict__ base)
 {
     __shared__ __align__(16) uint8_t timg[stage_lds_rows<kImgH, kImgW>() * kImgW];
-    __shared__ uint8_t tscore[kScoreH * kScoreW];
+    // Scores of the tile and a 1-pixel halo, at the pixels' places in timg.
+    __shared__ uint8_t tscore[kImgH * kImgW];
+    __shared__ uint16_t list[kScoreH * kScoreW + 1];       // places of the pixels to score
+    __shared__ int listed, kept;
     const int tx = (int)(blockIdx.x % (unsigned)tiles_x), ty = (int)(blockIdx.x / (unsigned)tiles_x);
     const int x0 = tx * kTileW, y0 = ty * kTileH;
     const int t = threadIdx.x;
 
+    if (t == 0) listed = kept = 0;
+    // The count on entry, for the emit kernel (one writer, before the count
+    // is replaced).
+    if (base && blockIdx.x == 0 && t == 0) *base = max(*n_kps, (int64_t)0);
     // Image tile with halo.  Clamped pixels only reach scores outside the
     // tested region, which are 0 regardless.
     stage_window<kDword, kImgH, kImgW, kImgW>(img, height, width, pitch, y0 - kHaloImg, x0 - kHaloImg,
                                               timg);
     __syncthreads();
 
-    // Scores of the tile and a 1-pixel halo.
-    for (int i = t; i < kScoreH * kScoreW; i += kThreads) {
+    // An arc of 9 holds two neighbouring compass points of the circle, so a
+    // corner has min(max(n, s), max(e, w)) - c or c - max(min(n, s), min(e, w))
+    // above the threshold.  The pixels that pass are listed and scored two per
+    // thread; the others score 0.
+    const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    constexpr int kPasses = (kScoreH * kScoreW + kThreads - 1) / kThreads;
+    uint64_t pass[kPasses];
+    int at[kPasses], total = 0;
+#pragma unroll
+    for (int k = 0; k < kPasses; ++k) {
+        const int i = t + k * kThreads;
         const int sy = i / kScoreW, sx = i % kScoreW;
         const int yy = y0 - 1 + sy, xx = x0 - 1 + sx;
-        int s = 0;
-        if (yy >= kDetectBorder && yy < height - kDetectBorder && xx >= kDetectBorder &&
-            xx < width - kDetectBorder) {
-            s = fast_score(&timg[(sy + kHaloImg - 1) * kImgW + sx + kHaloImg - 1]);
-            s = s > threshold ? s : 0;
+        at[k] = (sy + kHaloImg - 1) * kImgW + sx + kHaloImg - 1;
+        bool ok = false;
+        if (i < kScoreH * kScoreW) {
+            const uint8_t *p = timg + at[k];
+            const int n = p[-3 * kImgW], e = p[3], s = p[3 * kImgW], w = p[-3], c = p[0];
+            const int brighter = min(max(n, s), max(e, w)) - c, darker = c - max(min(n, s), min(e, w));
+            ok = (max(brighter, darker) > threshold) & (yy >= kDetectBorder) &
+                 (yy < height - kDetectBorder) & (xx >= kDetectBorder) & (xx < width - kDetectBorder);
+            tscore[at[k]] = 0;
         }
-        tscore[i] = (uint8_t)s;
+        pass[k] = __ballot(ok);
+        total += __popcll(pass[k]);
+    }
+    int first = 0;
+    if (lane == 0) first = atomicAdd(&listed, total);
+    first = __builtin_amdgcn_readfirstlane(first);
+#pragma unroll
+    for (int k = 0; k < kPasses; ++k) {
+        const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(pass[k] >> 32),
+                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)pass[k], 0));
+        if ((pass[k] >> lane) & 1) list[first + rank] = (uint16_t)at[k];
+        first += __popcll(pass[k]);
+    }
+    __syncthreads();
+    const int n = listed;
+    for (int i = 2 * t; i < n; i += 2 * kThreads) {
+        const int a = list[i], b = list[min(i + 1, n - 1)];
+        const short2v s = fast_scores(timg + a, timg + b);
+        tscore[a] = (uint8_t)(s[0] > threshold ? s[0] : 0);
+        tscore[b] = (uint8_t)(s[1] > threshold ? s[1] : 0);
     }
     __syncthreads();
 
-    // Suppression: wavefront w takes tile rows w, w + 4, ...; lane = column.
-    const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    for (int r = wave; r < kTileH; r += kThreads / 64) {
-        const int y = y0 + r;
-        if (y >= height) break;                         // uniform across the wavefront
-        const uint8_t *p = &tscore[(r + 1) * kScoreW + lane + 1];
-        const int s = p[0];
-        const bool keep = s > 0 && s > p[-kScoreW - 1] && s > p[-kScoreW] && s > p[-kScoreW + 1] &&
-                          s > p[-1] && s > p[1] && s > p[kScoreW - 1] && s > p[kScoreW] &&
-                          s > p[kScoreW + 1];
-        const uint64_t m = __ballot(keep);
-        if (lane == 0) {
+    // Suppression: wavefront w takes tile rows 4 w .. 4 w + 3; lane = column.
+    // A pixel stays if its score exceeds the largest of its 8 neighbours
+    // (and so 0).
+    constexpr int kRows = kTileH / (kThreads / 64);
+    const uint8_t *p = &tscore[(kRows * wave + kHaloImg) * kImgW + lane + kHaloImg];
+    int mid[kRows + 2], side[kRows + 2], survivors = 0;
+#pragma unroll
+    for (int r = 0; r < kRows + 2; ++r) {
+        const uint8_t *q = p + (r - 1) * kImgW;
+        mid[r] = q[0];
+        side[r] = max((int)q[-1], (int)q[1]);
+    }
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+        const int y = y0 + kRows * wave + r;
+        const int above = max(mid[r], side[r]), below = max(mid[r + 2], side[r + 2]);
+        const uint64_t m = __ballot(mid[r + 1] > max(max(above, below), side[r + 1]));
+        if (lane == 0 && y < height) {
             masks[(size_t)tx * height + y] = m;
             counts[(size_t)y * count_stride + tx] = (uint8_t)__popcll(m);
+            survivors += __popcll(m);
         }
+    }
+    if (tile_total) {
+        if (lane == 0) atomicAdd(&kept, survivors);
+        __syncthreads();
+        if (t == 0) tile_total[blockIdx.x] = (uint16_t)kept;
     }
 }
 
@@ -321,37 +400,86 @@ __device__ __forceinline__ int row16_sum(int v)
     return v;
 }
 
-// A value equal on every lane, in scalar registers.
-__device__ __forceinline__ int64_t uniform64(int64_t v)
+// Sum over each half-wavefront, on every lane of it.
+__device__ __forceinline__ int half_sum(int v)
 {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
+    v = row16_sum(v);
+    const auto w = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return (int)w[0] + (int)w[1];
+}
+
+// Mask of the n lowest bytes of a dword (none for n <= 0, all for n >= 4).
+__device__ __forceinline__ uint32_t low_bytes(int n)
+{
+    return n >= 4 ? 0xffffffffu : n <= 0 ? 0u : (1u << (8 * n)) - 1u;
+}
+
+// acc + the two 16-bit halves of v.
+__device__ __forceinline__ uint32_t sum_u16(uint32_t v, uint32_t acc)
+{
+    return acc + (v & 0xffffu) + (v >> 16);
+}
+
+__device__ __forceinline__ int64_t readlane64(int64_t v, int lane)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), lane);
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
 // Angle bin of moments (m10, m01), in double as the definition states.
-__device__ __forceinline__ int orientation_bin(int m10, int m01)
+__device__ __forceinline__ int orientation_bin_f64(int m10, int m01)
 {
     const double a = atan2((double)m01, (double)m10);
     return (int)((int64_t)rint(a * (4096.0 / (2.0 * 3.14159265358979323846))) & 4095);
 }
 
-// One workgroup per tile: the tile's image window goes to LDS, then
-// wavefront w takes the survivors of tile rows w, w + 4, ...  Moments are
-// summed two keypoints per pass (one per half-wavefront, a disc row per
-// lane); each keypoint's moments and slot are parked in the registers of
-// lane n (its index in the wavefront's queue), and when 63 or more are
-// queued, or at the end, every queued lane computes its angle and writes its
-// keypoint.
-template <bool kDword>
+// The same bin from a float atan2 (the moments are below 2^24, exact): its
+// error of at most 6 ulp, 9.4e-4 bins at pi, and the roundings of the product,
+// 2.4e-4 bins, only matter within 1/256 bin of a boundary, where the double
+// decides (about one keypoint in 128).
+__device__ __forceinline__ int orientation_bin(int m10, int m01)
+{
+    const float x = atan2f((float)m01, (float)m10) * (float)(4096.0 / (2.0 * 3.14159265358979323846));
+    const float r = rintf(x);
+    int bin = (int)r & 4095;
+    if (fabsf(x - r) > 0.5f - 1.0f / 256.0f) bin = orientation_bin_f64(m10, m01);
+    return bin;
+}
+
+// One workgroup per tile: the tile's image window goes to LDS, then wavefront
+// w takes the survivors of tile rows 4 w .. 4 w + 3, listed in LDS (64 at most:
+// no two survivors are neighbours).  Moments are summed two keypoints per pass
+// (one per half-wavefront, a disc row per lane) and parked in LDS; then lane n
+// computes the n-th keypoint's angle and writes it.
+constexpr int kEmitRows = kTileH / (kThreads / 64);
+constexpr int kEmitMost = kEmitRows / 2 * (kTileW / 2);
+
+//
+// kFused (at most kFusedTilesX tiles across and kFusedTiles in all): no scan
+// kernel ran; the workgroup adds up the survivors of the bands of tiles above it
+// from the per-tile totals (2 bytes each, read by every workgroup), then those of
+// the rows above in its own band, and the last one writes the new count.
+// 1920 x 1080 (2,040 tiles): 26.9 us with the scan, 25.0 without; 1277 x 719:
+// 17.9 and 15.7.  The totals read grow with the square of the tile count, and at
+// 3840 x 2160 (8,100 tiles) the two are equal (79.9, 80.7), so larger images
+// take the scan.
+constexpr int kFusedTilesX = 64, kFusedTiles = 1 << 12;
+
+template <bool kDword, bool kFused>
 __global__ __launch_bounds__(kThreads) void detect_emit_kernel(
     const uint8_t *__restrict__ img, int height, int width, int pitch, int tiles_x,
     const uint64_t *__restrict__ masks, const uint8_t *__restrict__ counts, int count_stride,
-    const int64_t *__restrict__ row_first, float4 *__restrict__ kps, int64_t max_kps,
-    int32_t *__restrict__ image_id, int32_t image_index)
+    const int64_t *__restrict__ row_first, const uint16_t *__restrict__ tile_total,
+    const int64_t *__restrict__ base, int64_t *__restrict__ n_kps, float4 *__restrict__ kps,
+    int64_t max_kps, int32_t *__restrict__ image_id, int32_t image_index)
 {
     // Rows past kOriRows take the rounding of the load count (never read).
     __shared__ __align__(16) uint8_t win[stage_lds_rows<kOriRows, kOriCols>() * kOriStride];
+    __shared__ uint8_t place[kThreads / 64][kEmitMost + 1];      // tile row - 4 w, column
+    __shared__ int2 moments[kThreads / 64][kEmitMost + 1];
+    __shared__ int row_total[kTileH], above_part[kThreads / 64];
+    static_assert(kEmitRows * kTileW <= 256 && kEmitMost <= 64, "one byte per place, one lane per keypoint");
     const int tx = (int)(blockIdx.x % (unsigned)tiles_x), ty = (int)(blockIdx.x / (unsigned)tiles_x);
     const int x0 = tx * kTileW, y0 = ty * kTileH;
     const int t = threadIdx.x;
@@ -364,76 +492,110 @@ __global__ __launch_bounds__(kThreads) void detect_emit_kernel(
                                                          x0 - 16, win);
     uint32_t bm[8];
     disc_masks(dy, bm);
-    __syncthreads();
 
-    // The queue: lane n holds the n-th queued keypoint.
-    int q_m10 = 0, q_m01 = 0, q_x = 0, q_y = 0;
-    int64_t q_slot = 0;
-    int queued = 0;                                       // uniform
-    auto flush = [&]() {
-        if (lane < queued && q_slot < max_kps) {
-            const int bin = orientation_bin(q_m10, q_m01);
-            kps[q_slot] = make_float4((float)q_x, (float)q_y, (float)bin * (360.0f / 4096.0f), 1.0f);
-            if (image_id) image_id[q_slot] = image_index;
-        }
-        queued = 0;
-    };
-
-    for (int rt = wave; rt < kTileH; rt += kThreads / 64) {
-        const int y = y0 + rt;
-        if (y >= height) break;                           // uniform across the wavefront
-        uint64_t m = masks[(size_t)tx * height + y];
-        const int64_t rf = row_first[y];
-        // Survivors of the tiles to the left in this row: their count bytes,
-        // one tile per lane (one coalesced load for up to 64 tiles).
-        int left = 0;
-        for (int i = lane; i < tx; i += 64) left += counts[(size_t)y * count_stride + i];
-        if (m == 0) continue;
+    // Survivors of the wavefront's rows: masks (uniform), and in the 16 lanes
+    // of row r those of the tiles to the left, four count bytes per lane.
+    const int yw = y0 + kEmitRows * wave;
+    uint64_t m[kEmitRows];
+    int before[kEmitRows + 1];
+    before[0] = 0;
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) left += __shfl_xor(left, o);
-        const int64_t first = uniform64(rf + left);
-        if (first >= max_kps) continue;
-        int rank = 0;                                     // survivors already queued from this row
-        while (m) {
-            const int j0 = __builtin_ctzll(m);
-            const uint64_t m1 = m & (m - 1);
-            const int j1 = m1 ? __builtin_ctzll(m1) : -1;
-            m = m1 ? (m1 & (m1 - 1)) : 0;
-            const int j = half ? j1 : j0;
-            uint32_t S = 0, W = 0;
-            if (j >= 0 && hl < kDiscRows) disc_row(win, j, rt, dy, bm, S, W);
-            const int s10 = row16_sum((int)W - kOrientRadius * (int)S);
-            const int s01 = row16_sum(dy * (int)S);
-            // Half-wavefront sums from rows of 16 lanes.
-            const int a10 = __builtin_amdgcn_readlane(s10, 0) + __builtin_amdgcn_readlane(s10, 16);
-            const int a01 = __builtin_amdgcn_readlane(s01, 0) + __builtin_amdgcn_readlane(s01, 16);
-            if (lane == queued) {
-                q_m10 = a10;
-                q_m01 = a01;
-                q_x = x0 + j0;
-                q_y = y;
-                q_slot = first + rank;
+    for (int r = 0; r < kEmitRows; ++r) {
+        m[r] = yw + r < height ? masks[(size_t)tx * height + yw + r] : 0ull;
+        before[r + 1] = before[r] + __popcll(m[r]);
+    }
+    const int n = __builtin_amdgcn_readfirstlane(before[kEmitRows]);
+    const int rl = lane >> 4;
+    const int yl = min(yw + rl, height - 1);
+    int left = 0, row = 0;
+    for (int c = 4 * (lane & 15); c < (kFused ? tiles_x : tx); c += 64) {
+        const uint32_t v = *reinterpret_cast<const uint32_t *>(counts + (size_t)yl * count_stride + c);
+        left = (int)__builtin_amdgcn_sad_u8(v & low_bytes(tx - c), 0u, (uint32_t)left);
+        if (kFused) row = (int)__builtin_amdgcn_sad_u8(v & low_bytes(tiles_x - c), 0u, (uint32_t)row);
+    }
+    left = row16_sum(left);
+    int64_t slot;                                            // of the row's first survivor in this tile
+    if (kFused) {
+        row = row16_sum(row);
+        if ((lane & 15) == 0) row_total[kEmitRows * wave + rl] = yw + rl < height ? row : 0;
+        uint32_t part = 0;
+        const int tiles_above = ty * tiles_x;
+        for (int i = 8 * t; i < tiles_above; i += 8 * kThreads) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(tile_total + i);
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const int nb = 2 * (tiles_above - i) - 4 * d;
+                part = sum_u16(w[d] & low_bytes(nb), part);
             }
-            if (j1 >= 0) {
-                const int b10 = __builtin_amdgcn_readlane(s10, 32) + __builtin_amdgcn_readlane(s10, 48);
-                const int b01 = __builtin_amdgcn_readlane(s01, 32) + __builtin_amdgcn_readlane(s01, 48);
-                if (lane == queued + 1) {
-                    q_m10 = b10;
-                    q_m01 = b01;
-                    q_x = x0 + j1;
-                    q_y = y;
-                    q_slot = first + rank + 1;
-                }
-                queued += 2;
-                rank += 2;
-            } else {
-                queued += 1;
-                rank += 1;
+        }
+        int sum = half_sum((int)part);
+        sum = __builtin_amdgcn_readlane(sum, 0) + __builtin_amdgcn_readlane(sum, 32);
+        if (lane == 0) above_part[wave] = sum;
+    } else {
+        slot = row_first[yl] + left;
+    }
+
+    uint8_t *at = place[wave];
+    int2 *mom = moments[wave];
+#pragma unroll
+    for (int r = 0; r < kEmitRows; ++r) {
+        const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m[r] >> 32),
+                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)m[r], 0));
+        if ((m[r] >> lane) & 1) at[before[r] + rank] = (uint8_t)(r * kTileW + lane);
+    }
+    __syncthreads();
+    if (kFused) {
+        int64_t all = *base;
+#pragma unroll
+        for (int i = 0; i < kThreads / 64; ++i) all += above_part[i];
+        slot = all + left;
+#pragma unroll
+        for (int i = 0; i < kTileH; ++i) {
+            const int v = row_total[i];
+            all += v;
+            slot += i < kEmitRows * wave + rl ? v : 0;
+        }
+        if (blockIdx.x == gridDim.x - 1 && t == 0) *n_kps = all;
+    }
+    // First slot of each row's survivors in this tile (uniform; read with
+    // every lane active).
+    int64_t first[kEmitRows];
+#pragma unroll
+    for (int r = 0; r < kEmitRows; ++r) first[r] = readlane64(slot, 16 * r);
+
+    for (int k = 0; k < n; k += 2) {
+        const int e = at[min(k + half, n - 1)];
+        uint32_t S = 0, W = 0;
+        if (hl < kDiscRows) disc_row(win, e % kTileW, kEmitRows * wave + e / kTileW, dy, bm, S, W);
+        int2 v;
+        v.x = half_sum((int)W - kOrientRadius * (int)S);
+        v.y = half_sum(dy * (int)S);
+        if (hl == 0 && k + half < n) mom[k + half] = v;
+    }
+    // The wavefront's own moments: its LDS accesses are in order.
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (lane < n) {
+        const int e = at[lane];
+        const int r = e / kTileW;
+        const int2 v = mom[lane];
+        int bf = 0;
+        int64_t s = 0;
+#pragma unroll
+        for (int i = 0; i < kEmitRows; ++i)
+            if (r == i) {
+                bf = before[i];
+                s = first[i];
             }
-            if (queued >= 63) flush();
+        s += lane - bf;
+        if (s < max_kps) {
+            kps[s] = make_float4((float)(x0 + e % kTileW), (float)(yw + r),
+                                 (float)orientation_bin(v.x, v.y) * (360.0f / 4096.0f), 1.0f);
+            if (image_id) image_id[s] = image_index;
         }
     }
-    flush();
 }
 
 }  // namespace
@@ -444,18 +606,27 @@ hipError_t launch_detect(const DetectArgs &a, hipStream_t stream)
     const int64_t tiles = (int64_t)tiles_x * ((a.height + kTileH - 1) / kTileH);
     const bool dword = (reinterpret_cast<uintptr_t>(a.img) & 3) == 0 && (a.pitch & 3) == 0 &&
                        (a.width & 3) == 0;
+    // The per-tile totals take the place of the rows' first slots (2 bytes per
+    // tile, at most 64 tiles per band of 16 rows, against 8 bytes per row).
+    const bool fused = tiles_x <= kFusedTilesX && tiles <= kFusedTiles;
+    static_assert(2 * kFusedTilesX <= 8 * kTileH, "totals fit the rows' first slots");
+    uint16_t *totals = fused ? reinterpret_cast<uint16_t *>(a.row_first) : nullptr;
     hipLaunchKernelGGL(dword ? detect_tile_kernel<true> : detect_tile_kernel<false>,
                        dim3((unsigned)tiles), dim3(kThreads), 0, stream, a.img, a.height, a.width,
-                       a.pitch, a.threshold, tiles_x, a.masks, a.counts, a.count_stride);
+                       a.pitch, a.threshold, tiles_x, a.masks, a.counts, a.count_stride, totals, a.n_kps,
+                       fused ? a.base : nullptr);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(detect_scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, a.counts,
-                       a.count_stride, a.height, tiles_x, a.row_first, a.base, a.n_kps);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(dword ? detect_emit_kernel<true> : detect_emit_kernel<false>,
-                       dim3((unsigned)tiles), dim3(kThreads), 0, stream, a.img, a.height, a.width,
-                       a.pitch, tiles_x, a.masks, a.counts, a.count_stride, a.row_first, a.kps,
-                       a.max_kps, a.image_id, a.image_index);
+    if (!fused) {
+        hipLaunchKernelGGL(detect_scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, a.counts,
+                           a.count_stride, a.height, tiles_x, a.row_first, a.base, a.n_kps);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    const auto emit = fused ? (dword ? detect_emit_kernel<true, true> : detect_emit_kernel<false, true>)
+                            : (dword ? detect_emit_kernel<true, false> : detect_emit_kernel<false, false>);
+    hipLaunchKernelGGL(emit, dim3((unsigned)tiles), dim3(kThreads), 0, stream, a.img, a.height, a.width,
+                       a.pitch, tiles_x, a.masks, a.counts, a.count_stride, a.row_first, totals, a.base,
+                       a.n_kps, a.kps, a.max_kps, a.image_id, a.image_index);
     return hipGetLastError();
 }
 

@@ -72,6 +72,33 @@ def test_wide_and_tall_images(torch_cuda, lat, shape):
     assert np.array_equal(kps[:n], want)
 
 
+@pytest.mark.parametrize("shape", [(1000, 4093), (1031, 4093), (1100, 4096)])
+def test_sizes_around_the_scan_limit(torch_cuda, lat, shape):
+    """Images of just under and over 4,096 tiles (slots from the per-tile
+    totals, or from the row scan), by bytes and by dwords."""
+    g = np.random.default_rng(shape[0])
+    img = g.integers(0, 256, shape, dtype=np.uint8)
+    want, wn = oracle.detect(img, 100)
+    kps, n = run(torch_cuda, lat, img, 100, wn + 5)
+    assert n == wn and wn > 10000
+    assert np.array_equal(kps[:n], want)
+
+
+@pytest.mark.parametrize("t", [0, 1, 254, 255])
+@pytest.mark.parametrize("levels", [2, 3, 256])
+def test_extreme_scores(torch_cuda, lat, t, levels):
+    """Scores from 1 to 255 at the ends of the threshold's range: random
+    images of 2, 3 and 256 levels between 0 and 255, and isolated dots."""
+    g = np.random.default_rng(17 * t + levels)
+    img = (g.integers(0, levels, (97, 145)) * 255 // (levels - 1)).astype(np.uint8)
+    img[40:60, 30:110] = 255 * (levels % 2)
+    img[50, 40:100:7] = 255 - 255 * (levels % 2)
+    want, wn = oracle.detect(img, t)
+    kps, n = run(torch_cuda, lat, img, t, wn + 5)
+    assert n == wn
+    assert np.array_equal(kps[:n], want)
+
+
 def test_truncation_keeps_raster_prefix_and_full_count(torch_cuda, lat):
     g = np.random.default_rng(3)
     img = synth.smoothed_noise(g, 300, 400)
