@@ -1,17 +1,17 @@
 // LATCH descriptor extraction for gfx950.
 //
-// A workgroup of two wavefronts computes one descriptor at a time
+// A workgroup of four wavefronts computes one descriptor at a time
 // (grid-stride over keypoints):
 //   1. resampling rule steps 1-3 on the keypoint (uniform across the group);
 //   2. gather of the 48 x 48 upright window (steps 4-5), one byte load per
 //      window position.  Rounding half away from zero is odd, so positions
 //      (u, v) and (-u, -v) sample at offsets (ox, oy) and (-ox, -oy), and the
 //      unrounded offsets of (u + 1, v) are those of (u, v) plus a per-keypoint
-//      constant: a thread takes 5 chains (u, v), (u + 1, v), (-u, -v),
-//      (-u - 1, -v) with two roundings per coordinate each (over
-//      [-24, 24]^2; the extra row and column are gathered and not read).
-//      The chains are taken in an order that keeps each load's samples on
-//      nearby image bytes: for the keypoint's angle class (32 bins), sorted
+//      constant: a thread takes 2 chains (3 in two of the wavefronts) (u, v),
+//      (u + 1, v), (-u, -v), (-u - 1, -v) with two roundings per coordinate
+//      each (over [-24, 24]^2; the extra row and column are gathered and not
+//      read).  The chains are taken in an order that keeps each load's samples
+//      on nearby image bytes: for the keypoint's angle class (32 bins), sorted
 //      by the band of image rows their first member samples at the class's
 //      middle angle, then by column (a host-built table).  The loads are
 //      issued one keypoint ahead so that their latency overlaps the previous
@@ -19,13 +19,12 @@
 //   3. the samples are written to a plain window in LDS, and a copy pass
 //      builds eight byte-shifted copies of it in which every 7-byte patch
 //      row is one 8-byte-aligned quadword with a zero last byte;
-//   4. Eq. 1 (Sec. 3.1) for 512 triplets: each wavefront takes 4 rounds of 64
+//   4. Eq. 1 (Sec. 3.1) for 512 triplets: each wavefront takes 2 rounds of 64
 //      lanes, one triplet per lane per round, in exact integer arithmetic;
-//   5. a 64-bit ballot per round packs the bits.  Triplets sit in (round,
-//      lane) slots chosen on the host so that the 32-lane halves of a
-//      ds_read_b64 hit few bank conflicts; four table lookups and ballots
-//      put the bits back in triplet order, and 8 lanes per wavefront store
-//      its 8 words.
+//   5. triplets sit in (wavefront, round, lane) slots chosen on the host so
+//      that the 32-lane halves of a ds_read_b64 hit few bank conflicts; each
+//      bit goes to its triplet's place in LDS as a byte, and after the next
+//      descriptor's first barrier 8 lanes at a time pack and store the words.
 //
 // Patch distances.  With A, C the 7 x 7 patches of the anchor and one
 // companion, ||A - C||^2 = sum A^2 + sum C^2 - 2 sum A C.  sum A^2 is shared by
@@ -35,106 +34,167 @@
 // result equals the exact integer one.
 //
 // The paper's CUDA kernel (Sec. 3.2) spreads one descriptor over 32 warps of
-// a 1024-thread block with float32 patches in shared memory; here two 64-lane
-// wavefronts share a 19.4 KB byte window (eight per CU, four wavefronts per
+// a 1024-thread block with float32 patches in shared memory; here four 64-lane
+// wavefronts share a 19.9 KB byte window (eight per CU, eight wavefronts per
 // SIMD) and synchronise twice per descriptor.
+//
+// What bounds it: no one unit.  Per keypoint the vector ALUs issue about 850
+// instructions, the LDS is busy some 950 cycles (patch reads 82 of 96 possible
+// bank cycles per row and group, copies, window) and the texture units 1,070 at
+// scale 1 to 1,290 over scales 1 to 3.6 (a byte load costs about 12 cycles plus
+// 1.2 per 16-byte chunk of each 16 lanes), of 1,250 to 1,400 in all.  50,000
+// keypoints of a 1920 x 1080 image: with two wavefronts per window (four per
+// SIMD), 1,060 instructions and 95 bank cycles 135 us at mixed scales and 127 us
+// upright; now 121 and 111 us.  16 images of 3000 x 2000 with 20,000 keypoints
+// each: 894 -> 848 us, 840 -> 750 us upright.  The registers just fit: 64 per
+// wavefront, and a spill of 20 bytes took back all of the gain (its accesses go
+// through the texture units).
 #include "internal.h"
 
 namespace latch {
 namespace {
 
-constexpr int kThreads = kExtractWaves * 64;             // 128: two wavefronts per window
-constexpr int kRoundsPerWave = 8 / kExtractWaves;         // 4
+constexpr int kThreads = kExtractWaves * 64;              // 256: four wavefronts per window
+constexpr int kRoundsPerWave = 8 / kExtractWaves;         // 2
+constexpr int kWaveTriplets = 64 * kRoundsPerWave;
 
-// Gather slots per thread: chains 128 m + tid of the gather order, four
-// samples each.
-constexpr int kGatherSlots = kGatherChains;               // 5
+// Gather slots per thread: chains 256 m + tid of the gather order, four
+// samples each; the last slot in wavefronts 0 and 1 only.
+constexpr int kGatherTailWaves = 2;
 constexpr int kRawCentre = kRawBase + kHalf * kRawStride + kHalf;
-static_assert(kGatherHeadChains == 4 && kGatherSlots == 5, "one uint2 and one uint16 of entries");
+static_assert(2 * kThreads + 64 * kGatherTailWaves == kGatherClassEntries, "chains per class");
 static_assert(kRawStride >= kWin + 1, "raw rows hold u = -24 .. 24");
 
 // Copy pass: units (row y, quadword q), 240 per window, unit e = 5 y + q.
 constexpr int kCopyUnits = kWin * kCopyQwords;
-static_assert(kCopyUnits > kThreads && kCopyUnits <= 2 * kThreads, "two copy units per thread");
+static_assert(kCopyUnits <= kThreads, "at most one copy unit per thread");
 static_assert(kWinLdsBytes * 8 <= kLdsPerCu, "eight windows per CU");
 
 #include "keypoint.h"
 
-// Raw-window byte of the first member (u, v) of the chain in half `h` of
-// packed entry pair `d`; (u + 1, v) is the next byte, (-u, -v) sits at
-// 2 kRawCentre minus it and (-u - 1, -v) one byte before that.
-__device__ __forceinline__ uint32_t raw_of(uint32_t d, int h)
-{
-    const int u = __builtin_amdgcn_sbfe((int)d, 16 * h, 8);
-    const int v = __builtin_amdgcn_sbfe((int)d, 16 * h + 8, 8);
-    return (uint32_t)(kRawCentre + mad_i24(v, kRawStride, u));
-}
+// The image offsets of one chain of keypoint k: its members (u, v), (u + 1, v),
+// (-u, -v), (-u - 1, -v) go to at[0 .. 3], and raw is the raw-window byte of
+// (u, v) less that of the centre (the mirrors' sit at minus it).  The chain's
+// entry is half `h` of t.
+//
+// Rule steps 4-5.  The unrounded offsets of (u, v) are sq (C u - S v) and
+// sq (S u + C v), formed from 24-bit products (|C u - S v| < 2^20 and sq <= 2^10,
+// so every product is exact and full rate; kSmall: sq < 2^9, where sq C and sq S
+// are 24-bit factors themselves and save a product per coordinate); those of
+// (u + 1, v) add sq C and sq S (|sq C| <= 2^24, a scalar product), and rounding
+// half away from zero is odd, so the mirrors sample at the negated offsets.  Two
+// roundings per coordinate serve the chain's four samples.
+// kTies: an offset may lie halfway between two integers (three instructions per
+// rounding instead of one).  kInterior: every sample lies inside the image, so
+// no coordinate is clamped.
+struct Chain {
+    int raw;
+    uint32_t a, b, c, d;
+};
 
-// Rule steps 4-5 for this thread's 5 chains of keypoint k: its entries of
-// the keypoint's angle class (an 8-byte and a 2-byte load; kept in e, two per
-// dword, for write_raw) and the byte loads of chain m's members (u, v),
-// (u + 1, v), (-u, -v), (-u - 1, -v) into g[4 m .. 4 m + 3].  The unrounded
-// offsets of (u, v) are sq (C u - S v) and sq (S u + C v), formed from
-// 24-bit products (|C u - S v| < 2^20 and sq <= 2^10, so every product is
-// exact and full rate); those of (u + 1, v) add sq C and sq S (|sq C| <= 2^24,
-// a scalar product), and rounding half away from zero is odd, so the mirrors
-// sample at the negated offsets.  Two roundings per coordinate serve the
-// chain's four samples.
-__device__ __forceinline__ void issue_gather(const Keypoint &k, const uint16_t *__restrict__ order,
-                                             int tid, uint32_t (&e)[(kGatherSlots + 1) / 2],
-                                             uint32_t (&g)[4 * kGatherSlots])
+template <bool kInterior, bool kTies, bool kSmall>
+__device__ __forceinline__ Chain chain_offsets(const Keypoint &k, uint32_t t, int h, int half)
 {
-    const uint16_t *cls = order + (size_t)k.cls * kGatherClassEntries;
-    const uint2 t0 = reinterpret_cast<const uint2 *>(cls)[tid];
-    e[0] = t0.x, e[1] = t0.y;
-    e[2] = cls[kGatherHeadChains * kThreads + tid];
-    GlobalByte *img = (GlobalByte *)k.img;
+    Chain r;
     const int xm = k.width - 1, ym = k.height - 1;
     const int sqc = k.sq * k.c, sqs = k.sq * k.s;
-#pragma unroll
-    for (int m = 0; m < kGatherSlots; ++m) {
-        const int u = __builtin_amdgcn_sbfe((int)e[m >> 1], 16 * (m & 1), 8);
-        const int v = __builtin_amdgcn_sbfe((int)e[m >> 1], 16 * (m & 1) + 8, 8);
-        const int nx = mul_i24_s(k.sq, mad_i24_s(k.c, u, mul_i24_s(-k.s, v)));
-        const int ny = mul_i24_s(k.sq, mad_i24_s(k.s, u, mul_i24_s(k.c, v)));
-        const int ox0 = round_q22(nx), oy0 = round_q22(ny);
-        const int ox1 = round_q22(nx + sqc), oy1 = round_q22(ny + sqs);
-        uint32_t a[4];
-        if (k.interior) {
-            // Every sample is inside the image, so |offset| * pitch < 2^31 and the
-            // 24-bit multiply-adds are exact.
-            const int d0 = mad_i24_s(k.pitch, oy0, ox0);
-            const int d1 = mad_i24_s(k.pitch, oy1, ox1);
-            a[0] = (uint32_t)(k.centre + d0);
-            a[1] = (uint32_t)(k.centre + d1);
-            a[2] = (uint32_t)(k.centre - d0);
-            a[3] = (uint32_t)(k.centre - d1);
-        } else {
-            a[0] = (uint32_t)mad_i24(clamp_med3(k.cy + oy0, 0, ym), k.pitch, clamp_med3(k.cx + ox0, 0, xm));
-            a[1] = (uint32_t)mad_i24(clamp_med3(k.cy + oy1, 0, ym), k.pitch, clamp_med3(k.cx + ox1, 0, xm));
-            a[2] = (uint32_t)mad_i24(clamp_med3(k.cy - oy0, 0, ym), k.pitch, clamp_med3(k.cx - ox0, 0, xm));
-            a[3] = (uint32_t)mad_i24(clamp_med3(k.cy - oy1, 0, ym), k.pitch, clamp_med3(k.cx - ox1, 0, xm));
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) g[4 * m + i] = img[a[i]];
+    const int u = __builtin_amdgcn_sbfe((int)t, 16 * h, 8);
+    const int v = __builtin_amdgcn_sbfe((int)t, 16 * h + 8, 8);
+    r.raw = mad_i24(v, kRawStride, u);
+    int mx, my;                                    // offsets + 2^21
+    if constexpr (kSmall) {
+        mx = mad_i24_s(sqc, u, mad_i24_s(-sqs, v, half));
+        my = mad_i24_s(sqs, u, mad_i24_s(sqc, v, half));
+    } else {
+        mx = mad_i24_s(k.sq, mad_i24_s(k.c, u, mul_i24_s(-k.s, v)), half);
+        my = mad_i24_s(k.sq, mad_i24_s(k.s, u, mul_i24_s(k.c, v)), half);
+    }
+    const int ox0 = round_half<kTies>(mx), oy0 = round_half<kTies>(my);
+    const int ox1 = round_half<kTies>(mx + sqc), oy1 = round_half<kTies>(my + sqs);
+    if constexpr (kInterior) {
+        // Every sample is inside the image, so |offset| * pitch < 2^31 and the
+        // 24-bit multiply-adds are exact.
+        const int d0 = mad_i24_s(k.pitch, oy0, ox0);
+        const int d1 = mad_i24_s(k.pitch, oy1, ox1);
+        r.a = (uint32_t)(k.centre + d0);
+        r.b = (uint32_t)(k.centre + d1);
+        r.c = (uint32_t)(k.centre - d0);
+        r.d = (uint32_t)(k.centre - d1);
+    } else {
+        r.a = (uint32_t)mad_i24(clamp_med3(k.cy + oy0, 0, ym), k.pitch, clamp_med3(k.cx + ox0, 0, xm));
+        r.b = (uint32_t)mad_i24(clamp_med3(k.cy + oy1, 0, ym), k.pitch, clamp_med3(k.cx + ox1, 0, xm));
+        r.c = (uint32_t)mad_i24(clamp_med3(k.cy - oy0, 0, ym), k.pitch, clamp_med3(k.cx - ox0, 0, xm));
+        r.d = (uint32_t)mad_i24(clamp_med3(k.cy - oy1, 0, ym), k.pitch, clamp_med3(k.cx - ox1, 0, xm));
+    }
+    return r;
+}
+
+// The offsets of one or two chains of an entry pair, by the keypoint's case
+// (uniform branches).
+template <bool kTwo>
+__device__ __forceinline__ void chains_offsets(const Keypoint &k, uint32_t t, Chain &x, Chain &y)
+{
+    const int half = opaque(kRoundHalf);
+    if (!k.interior) {
+        x = chain_offsets<false, true, false>(k, t, 0, half);
+        if (kTwo) y = chain_offsets<false, true, false>(k, t, 1, half);
+    } else if (k.ties) {
+        x = chain_offsets<true, true, false>(k, t, 0, half);
+        if (kTwo) y = chain_offsets<true, true, false>(k, t, 1, half);
+    } else if (k.sq < 512) {
+        x = chain_offsets<true, false, true>(k, t, 0, half);
+        if (kTwo) y = chain_offsets<true, false, true>(k, t, 1, half);
+    } else {
+        x = chain_offsets<true, false, false>(k, t, 0, half);
+        if (kTwo) y = chain_offsets<true, false, false>(k, t, 1, half);
+    }
+}
+
+// A chain's samples and the place of the first in the raw window.
+struct Samples {
+    int raw;
+    uint32_t a, b, c, d;
+};
+
+__device__ __forceinline__ void load_chain(GlobalByte *img, const Chain &c, Samples &s)
+{
+    s.raw = c.raw;
+    s.a = img[c.a];
+    s.b = img[c.b];
+    s.c = img[c.c];
+    s.d = img[c.d];
+}
+
+// Loads this thread's entries of the keypoint's angle class (a 4-byte and, in
+// the wavefronts with a third chain, a 2-byte load) and issues its gather.
+__device__ __forceinline__ void issue_gather(const Keypoint &k, const uint16_t *__restrict__ order,
+                                             int tid, bool tail, Samples &s0, Samples &s1, Samples &s2)
+{
+    // (A uniform base and 32-bit offsets: no address registers over the loop.)
+    const GlobalWord *cls = uniform_words((uint32_t *)(order + (size_t)k.cls * kGatherClassEntries));
+    const uint32_t t0 = cls[(uint32_t)opaque(tid)];
+    const uint32_t t1 = tail ? ((const GlobalHalf *)cls)[(uint32_t)opaque(tid + 2 * kThreads)] : 0u;
+    GlobalByte *img = (GlobalByte *)k.img;
+    Chain x, y;
+    chains_offsets<true>(k, t0, x, y);
+    load_chain(img, x, s0);
+    load_chain(img, y, s1);
+    if (tail) {
+        chains_offsets<false>(k, t1, x, y);
+        load_chain(img, x, s2);
     }
 }
 
 // The gathered samples into the raw window.  Chains overlap at the end of a
 // row and the padding slots repeat the centre's chain: such bytes are written
 // more than once, always with the same sample.
-__device__ __forceinline__ void write_raw(uint8_t *lds, const uint32_t (&e)[(kGatherSlots + 1) / 2],
-                                          const uint32_t (&g)[4 * kGatherSlots])
+__device__ __forceinline__ void write_chain(uint8_t *lds, const Samples &s)
 {
-#pragma unroll
-    for (int m = 0; m < kGatherSlots; ++m) {
-        const uint32_t r = raw_of(e[m >> 1], m & 1);
-        const uint32_t rm = 2 * kRawCentre - 1 - r;          // (-u - 1, -v)
-        lds[r] = (uint8_t)g[4 * m];
-        lds[r + 1] = (uint8_t)g[4 * m + 1];
-        lds[rm + 1] = (uint8_t)g[4 * m + 2];
-        lds[rm] = (uint8_t)g[4 * m + 3];
-    }
+    uint8_t *p = lds + kRawCentre + s.raw, *q = lds + kRawCentre - s.raw;
+    p[0] = (uint8_t)s.a;
+    p[1] = (uint8_t)s.b;
+    q[0] = (uint8_t)s.c;
+    q[-1] = (uint8_t)s.d;
 }
 
 // Copy unit e = 5 y + q: from raw bytes (y, 8 q .. 8 q + 15) build the
@@ -171,88 +231,68 @@ __device__ __forceinline__ void copy_unit(uint8_t *lds, int e)
     }
 }
 
-// Patch rows of one triplet: anchor, companion 1, companion 2, 7 rows each.
-struct Rows {
-    uint2 a[7], c[7], e[7];
+// One row of the three patches of a triplet: anchor, companion 1, companion 2.
+// Rows are read one row before their use (eight wavefronts per SIMD hide the
+// rest of the latency; two rows ahead are no faster, three spill registers).
+constexpr int kPatchRows = 2 * kPatchR + 1;
+constexpr int kRowsAhead = 1;
+
+struct PatchRow {
+    uint64_t a, c, e;
 };
 
-// The 21 patch rows of a triplet, each one ds_read_b64, then a wait for all
-// of them.  Written out because the compiler would pair rows k and k + 1 of
-// a patch into a ds_read2_b64, which gfx950 serves 16 lanes and one address
-// at a time (at best half the rate of two ds_read_b64, and bank-conflicted
-// unless the 16-lane quarters, rather than the 32-lane halves, of a wavefront
-// are spread over the banks).  Every address is a host-checked patch offset
-// plus a row offset inside the copies.
-__device__ __forceinline__ void load_rows(const uint8_t *lds, uint32_t oa, uint32_t o1, uint32_t o2,
-                                          Rows &r)
+// One ds_read_b64.  (Atomic, so that the compiler does not pair rows k and
+// k + 1 of a patch into a ds_read2_b64, which gfx950 serves 16 lanes and one
+// address at a time: at best half the rate of two ds_read_b64, and
+// bank-conflicted unless the 16-lane quarters, rather than the 32-lane halves,
+// of a wavefront are spread over the banks.)
+__device__ __forceinline__ uint64_t read_quad(const uint8_t *p)
 {
-    static_assert(kCopyRowBytes == 40, "row offsets below");
-    const uint32_t base = (uint32_t)(uintptr_t)lds;
-    uint64_t a0, a1, a2, a3, a4, a5, a6, c0, c1, c2, c3, c4, c5, c6, e0, e1, e2, e3, e4, e5, e6;
-    asm volatile(
-        "ds_read_b64 %0, %21\n"
-        "ds_read_b64 %7, %22\n"
-        "ds_read_b64 %14, %23\n"
-        "ds_read_b64 %1, %21 offset:40\n"
-        "ds_read_b64 %8, %22 offset:40\n"
-        "ds_read_b64 %15, %23 offset:40\n"
-        "ds_read_b64 %2, %21 offset:80\n"
-        "ds_read_b64 %9, %22 offset:80\n"
-        "ds_read_b64 %16, %23 offset:80\n"
-        "ds_read_b64 %3, %21 offset:120\n"
-        "ds_read_b64 %10, %22 offset:120\n"
-        "ds_read_b64 %17, %23 offset:120\n"
-        "ds_read_b64 %4, %21 offset:160\n"
-        "ds_read_b64 %11, %22 offset:160\n"
-        "ds_read_b64 %18, %23 offset:160\n"
-        "ds_read_b64 %5, %21 offset:200\n"
-        "ds_read_b64 %12, %22 offset:200\n"
-        "ds_read_b64 %19, %23 offset:200\n"
-        "ds_read_b64 %6, %21 offset:240\n"
-        "ds_read_b64 %13, %22 offset:240\n"
-        "ds_read_b64 %20, %23 offset:240\n"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&v"(a0), "=&v"(a1), "=&v"(a2), "=&v"(a3), "=&v"(a4), "=&v"(a5), "=&v"(a6),
-          "=&v"(c0), "=&v"(c1), "=&v"(c2), "=&v"(c3), "=&v"(c4), "=&v"(c5), "=&v"(c6),
-          "=&v"(e0), "=&v"(e1), "=&v"(e2), "=&v"(e3), "=&v"(e4), "=&v"(e5), "=&v"(e6)
-        : "v"(base + oa), "v"(base + o1), "v"(base + o2)
-        : "memory");
-    const uint64_t a[7] = {a0, a1, a2, a3, a4, a5, a6};
-    const uint64_t c[7] = {c0, c1, c2, c3, c4, c5, c6};
-    const uint64_t e[7] = {e0, e1, e2, e3, e4, e5, e6};
-#pragma unroll
-    for (int k = 0; k < 2 * kPatchR + 1; ++k) {
-        r.a[k] = make_uint2((uint32_t)a[k], (uint32_t)(a[k] >> 32));
-        r.c[k] = make_uint2((uint32_t)c[k], (uint32_t)(c[k] >> 32));
-        r.e[k] = make_uint2((uint32_t)e[k], (uint32_t)(e[k] >> 32));
-    }
+    return __atomic_load_n(reinterpret_cast<const uint64_t *>(p), __ATOMIC_RELAXED);
 }
 
-// Eq. 1 on one triplet: [||A - C1||^2 > ||A - C2||^2], via
-// ||A - Ck||^2 - sum A^2 = sum Ck^2 - 2 sum A Ck.  The zero last byte of
-// every row quadword keeps the sums to the 7 x 7 patch.
-__device__ __forceinline__ bool triplet_bit(const Rows &r)
-{
+// Sums of Eq. 1 on one triplet, via ||A - Ck||^2 - sum A^2 = sum Ck^2 - 2 sum A Ck.
+// The zero last byte of every row quadword keeps them to the 7 x 7 patch.
+struct TripletSums {
     uint32_t ac1 = 0, ac2 = 0, q1 = 0, q2 = 0;
+
+    __device__ __forceinline__ void add(const PatchRow &r)
+    {
 #pragma unroll
-    for (int k = 0; k < 2 * kPatchR + 1; ++k) {
-        ac1 = dot4(r.a[k].x, r.c[k].x, ac1);
-        ac1 = dot4(r.a[k].y, r.c[k].y, ac1);
-        ac2 = dot4(r.a[k].x, r.e[k].x, ac2);
-        ac2 = dot4(r.a[k].y, r.e[k].y, ac2);
-        q1 = dot4(r.c[k].x, r.c[k].x, q1);
-        q1 = dot4(r.c[k].y, r.c[k].y, q1);
-        q2 = dot4(r.e[k].x, r.e[k].x, q2);
-        q2 = dot4(r.e[k].y, r.e[k].y, q2);
+        for (int d = 0; d < 2; ++d) {
+            const uint32_t a = (uint32_t)(r.a >> (32 * d)), c = (uint32_t)(r.c >> (32 * d)),
+                           e = (uint32_t)(r.e >> (32 * d));
+            ac1 = dot4(a, c, ac1);
+            ac2 = dot4(a, e, ac2);
+            q1 = dot4(c, c, q1);
+            q2 = dot4(e, e, q2);
+        }
     }
-    return (int)(q1 - 2u * ac1) > (int)(q2 - 2u * ac2);
+
+    // [||A - C1||^2 > ||A - C2||^2]: the sign of the difference the other way round.
+    __device__ __forceinline__ uint32_t bit() const { return (((ac1 - ac2) << 1) + (q2 - q1)) >> 31; }
+};
+
+// Words 4 w .. 4 w + 3 of the descriptor whose bits are in LDS, a byte each, by
+// wavefront w: lane l packs bits 4 l .. 4 l + 3 of its 128, and groups of 8 lanes
+// add their nibbles to a word.
+__device__ __forceinline__ void store_words(const uint8_t *lds, int wave, int lane, uint32_t *row)
+{
+    const uint32_t four =
+        reinterpret_cast<const uint32_t *>(lds + kBitBase + kWaveTriplets * wave)[lane & 31];
+    int word = (int)(dot4(four, 0x08040201u, 0u) << (4 * (lane & 7)));
+    word += __builtin_amdgcn_update_dpp(0, word, 0xB1, 0xF, 0xF, false);    // quad_perm [1,0,3,2]
+    word += __builtin_amdgcn_update_dpp(0, word, 0x4E, 0xF, 0xF, false);    // quad_perm [2,3,0,1]
+    word += __builtin_amdgcn_update_dpp(0, word, 0x141, 0xF, 0xF, false);   // row_half_mirror
+    if ((lane & 39) == 0)
+        uniform_words(row + 2 * kRoundsPerWave * wave)[(uint32_t)lane >> 3] = (uint32_t)word;
 }
 
 template <bool kTable>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void extract_kernel(
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void extract_kernel(
     ImageSource src, const float4 *__restrict__ kps, int64_t n_host, const int64_t *__restrict__ n_dev,
     const int2 *__restrict__ rot, const uint2 *__restrict__ trip_off,
-    const uint32_t *__restrict__ unperm, const uint16_t *__restrict__ gather_order,
+    const uint32_t *__restrict__ bit_of, const uint16_t *__restrict__ gather_order,
     uint32_t *__restrict__ desc, uint32_t *__restrict__ flags)
 {
     __shared__ __attribute__((aligned(16))) uint8_t lds[kWinLdsBytes];
@@ -261,23 +301,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4))
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // Wavefront w evaluates triplets 256 w .. 256 w + 255 in 4 rounds; slot
-    // 64 r + lane holds the triplet the bank-aware assignment put there, and
-    // `slots` names, for output bits 256 w + 64 k + lane, k = 0..3, the slots
-    // that computed them.
+    // Wavefront w evaluates the triplets in slots 128 w + 64 r + lane, r = 0, 1,
+    // where the bank-aware assignment put them; `places` names their output
+    // bits (constant over keypoints).
     // Offsets: anchor | companion 1 << 16 per round, and the companion-2
-    // offsets of rounds 2 q and 2 q + 1 packed in off_2[q] (all < 2^16).
-    uint32_t off_a1[kRoundsPerWave], off_2[kRoundsPerWave / 2];
+    // offsets of both rounds packed in off_2 (all < 2^16).
+    uint32_t off_a1[kRoundsPerWave], off_2 = 0;
 #pragma unroll
     for (int r = 0; r < kRoundsPerWave; ++r) {
-        const uint2 o = trip_off[64 * (kRoundsPerWave * wave + r) + lane];
+        const uint2 o = trip_off[kWaveTriplets * wave + 64 * r + lane];
         off_a1[r] = o.x;
-        if (r & 1)
-            off_2[r >> 1] |= o.y << 16;
-        else
-            off_2[r >> 1] = o.y;
+        off_2 |= o.y << (16 * r);
     }
-    uint32_t *ballots = reinterpret_cast<uint32_t *>(lds + kBallotBase) + 8 * wave;
+    uint8_t *out_bits = lds + kBitBase;
+    const bool tail = wave < kGatherTailWaves;
 
     // Keypoint count: a host value, or (batches) a device value capped by it.
     int64_t n_all = n_host;
@@ -286,16 +323,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4))
     const int64_t n = range.end;
     int64_t p = range.first;
     if (p >= n) return;
-    // This lane's output bits 256 w + 64 k + lane come from slots
-    // (slots >> 8 k) & 0xff of its wavefront (constant over keypoints).
-    const uint32_t slots = unperm[64 * wave + lane];
+    const uint32_t places = bit_of[64 * wave + lane];
     const int64_t stride = range.stride;
-    uint32_t e[(kGatherSlots + 1) / 2], g[4 * kGatherSlots];
+    Samples s0, s1, s2;                       // s2 in the wavefronts with a third chain
     KeypointBatch batch = prepare_batch<kTable, kHalf>(kps, n, p, stride, lane, rot, src);
     bool bad_image = false;
     Keypoint cur = batch_get<kTable>(batch, 0, src, &bad_image);
-    if (cur.ok) issue_gather(cur, gather_order, tid, e, g);
+    if (cur.ok) issue_gather(cur, gather_order, tid, tail, s0, s1, s2);
 
+    int64_t pending = -1;                     // row whose bits are complete in LDS
     for (int i = 0; p < n; ++i, p += stride) {
         const bool compute = cur.ok;
         // Descriptor row of this position's keypoint (the position itself
@@ -307,10 +343,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4))
         } else {
             // The raw window was last read by the previous descriptor's copy
             // pass, which ended before that descriptor's second barrier.
-            write_raw(lds, e, g);
-            __syncthreads();   // raw window complete; the previous triplet reads are done
-            copy_unit(lds, tid);
-            if (tid < kCopyUnits - kThreads) copy_unit(lds, tid + kThreads);
+            write_chain(lds, s0);
+            write_chain(lds, s1);
+            if (tail) write_chain(lds, s2);
+            __syncthreads();   // raw window complete; the previous triplets are done
+            if (pending >= 0) store_words(lds, wave, lane, desc + pending * kWords);
+            if (tid < kCopyUnits) copy_unit(lds, tid);
             __syncthreads();   // copies complete
         }
 
@@ -318,34 +356,37 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4))
         const int j = (i + 1) & 63;
         if (j == 0) batch = prepare_batch<kTable, kHalf>(kps, n, p + stride, stride, lane, rot, src);
         cur = batch_get<kTable>(batch, j, src, &bad_image);
-        if (cur.ok) issue_gather(cur, gather_order, tid, e, g);
+        if (cur.ok) issue_gather(cur, gather_order, tid, tail, s0, s1, s2);
         if (!compute) continue;
 
-        // Eq. 1 for this wavefront's 256 triplets, in slot order.
-        uint32_t slot_word = 0;
+        // Eq. 1 for this wavefront's 128 triplets, each bit as a byte in the
+        // place of its triplet.
+        constexpr int kAllRows = kRoundsPerWave * kPatchRows;
+        PatchRow rows[kRowsAhead + 1];
+        auto read = [&](int n) {
+            const int r = n / kPatchRows, at = n % kPatchRows * kCopyRowBytes;
+            PatchRow &to = rows[n % (kRowsAhead + 1)];
+            to.a = read_quad(lds + (off_a1[r] & 0xffffu) + at);
+            to.c = read_quad(lds + (off_a1[r] >> 16) + at);
+            to.e = read_quad(lds + ((off_2 >> (16 * r)) & 0xffffu) + at);
+        };
 #pragma unroll
-        for (int r = 0; r < kRoundsPerWave; ++r) {
-            Rows rows;
-            load_rows(lds, off_a1[r] & 0xffffu, off_a1[r] >> 16, (off_2[r >> 1] >> (16 * (r & 1))) & 0xffffu,
-                      rows);
-            const uint64_t bits = __ballot(triplet_bit(rows));
-            if (lane == 2 * r) slot_word = (uint32_t)bits;
-            if (lane == 2 * r + 1) slot_word = (uint32_t)(bits >> 32);
-        }
-        // Back to triplet order through this wavefront's 8 ballot words in
-        // LDS (written and read by the same wavefront, so in order).
-        if (lane < 2 * kRoundsPerWave) ballots[lane] = slot_word;
-        uint32_t out_word = 0;
+        for (int n = 0; n < kRowsAhead; ++n) read(n);
+        TripletSums sums;
 #pragma unroll
-        for (int k = 0; k < kRoundsPerWave; ++k) {
-            const uint32_t s = (slots >> (8 * k)) & 0xffu;
-            const uint64_t bits = __ballot((ballots[s >> 5] >> (s & 31u)) & 1u);
-            if (lane == 2 * k) out_word = (uint32_t)bits;
-            if (lane == 2 * k + 1) out_word = (uint32_t)(bits >> 32);
+        for (int n = 0; n < kAllRows; ++n) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (n + kRowsAhead < kAllRows) read(n + kRowsAhead);
+            sums.add(rows[n % (kRowsAhead + 1)]);
+            if (n % kPatchRows == kPatchRows - 1) {
+                out_bits[(places >> (16 * (n / kPatchRows))) & 0xffffu] = (uint8_t)sums.bit();
+                sums = TripletSums();
+            }
         }
-        if (lane < 2 * kRoundsPerWave)
-            uniform_words(desc + (q * kWords + 2 * kRoundsPerWave * wave))[(uint32_t)lane] = out_word;
+        pending = q;
     }
+    __syncthreads();                          // the last triplets are done
+    if (pending >= 0) store_words(lds, wave, lane, desc + pending * kWords);
 }
 
 }  // namespace
@@ -359,11 +400,11 @@ hipError_t launch_extract(const ExtractArgs &a, hipStream_t stream)
     ImageSource src{a.img, a.height, a.width, a.pitch, a.table, a.image_id, a.n_images, a.order};
     if (a.table)
         hipLaunchKernelGGL(extract_kernel<true>, dim3((unsigned)blocks), dim3(kThreads), 0, stream,
-                           src, a.kps, a.n, a.n_dev, a.rot, a.trip_off, a.unperm, a.gather, a.desc,
+                           src, a.kps, a.n, a.n_dev, a.rot, a.trip_off, a.bit_of, a.gather, a.desc,
                            a.flags);
     else
         hipLaunchKernelGGL(extract_kernel<false>, dim3((unsigned)blocks), dim3(kThreads), 0, stream,
-                           src, a.kps, a.n, a.n_dev, a.rot, a.trip_off, a.unperm, a.gather, a.desc,
+                           src, a.kps, a.n, a.n_dev, a.rot, a.trip_off, a.bit_of, a.gather, a.desc,
                            a.flags);
     return hipGetLastError();
 }

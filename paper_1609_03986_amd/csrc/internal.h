@@ -18,12 +18,13 @@ constexpr int kBins = 4096;
 // covering [-24, 24]^2 (613 chains; the first members of a row's chains
 // overlap by one position at its end), sorted by the band of a quarter image
 // row at unit scale of the first member, then by its image column
-// (host-built); for each of the 128 extraction threads its 5 chains (chains
-// 128 m + thread; the last slots repeat the centre's chain) as 16-bit entries
-// u & 0xff | (v & 0xff) << 8.  A class's table holds, for thread t, chains
-// 0..3 at entries 4 t .. 4 t + 3 and chain 4 at entry 512 + t, so that a
-// thread reads its chains with one 8-byte and one 2-byte load and every load
-// of a wavefront is contiguous.
+// (host-built), as 16-bit entries u & 0xff | (v & 0xff) << 8: sorted chain k
+// belongs to extraction thread k mod 256, slot k / 256 (the last slots repeat the
+// centre's chain).  A class's table holds, for thread t, slots 0 and 1 at
+// entries 2 t and 2 t + 1 and, for the first 128 threads, slot 2 at entry
+// 512 + t, so that a thread reads its chains with one 4-byte and one 2-byte load
+// and every load of a wavefront is contiguous: 640 entries, 5 per thread of
+// half a workgroup, 4 of them in the head.
 constexpr int kGatherClasses = kBins / 32;
 constexpr int kGatherChains = 5;
 constexpr int kGatherHeadChains = 4;
@@ -51,9 +52,9 @@ constexpr int kEdgeBase = kCopies * kCopyBytes;                    // 15360
 constexpr int kEdgeBytes = kCopyBytes + 8;                         // 1928
 constexpr int kRawBase = (kEdgeBase + kEdgeBytes + 15) / 16 * 16;  // 17296
 constexpr int kRawStride = 52;
-constexpr int kBallotBase = kRawBase + (kWin + 1) * kRawStride;    // 19844: 8 ballot words per wavefront
-constexpr int kWinLdsBytes = kBallotBase + 2 * 8 * 4;              // 19908 per workgroup
-constexpr int kExtractWaves = 2;                           // wavefronts per workgroup
+constexpr int kBitBase = kRawBase + (kWin + 1) * kRawStride;       // 19844: a byte per output bit
+constexpr int kWinLdsBytes = kBitBase + kTriplets;                 // 20356 per workgroup
+constexpr int kExtractWaves = 4;                           // wavefronts per workgroup
 constexpr int kLdsPerCu = 160 * 1024;                      // gfx950
 
 // Matching.
@@ -91,9 +92,9 @@ struct ExtractArgs {
     const float4 *kps;
     int64_t n;                     // keypoints (upper bound when n_dev is set)
     const int64_t *n_dev;          // optional device-side keypoint count
-    const int2 *rot;          // [4096] {cos_q14, sin_q14}
+    const int2 *rot;          // [4096] {cos_q14 & 0xffff | sin_q14 << 16, tie masks (keypoint.h)}
     const uint2 *trip_off;    // [512] by slot: {offA | off1 << 16, off2} LDS byte offsets
-    const uint32_t *unperm;   // [128] per (wavefront, lane): slots of its four output bits
+    const uint32_t *bit_of;   // [256] per (wavefront, lane): output bits of its two slots
     const uint16_t *gather;   // [kGatherClasses][kGatherClassEntries] gather order
     uint32_t *desc;
     uint32_t *flags;

@@ -6,6 +6,7 @@
 
 typedef const __attribute__((address_space(1))) uint8_t GlobalByte;
 typedef __attribute__((address_space(1))) uint32_t GlobalWord;
+typedef __attribute__((address_space(1))) uint16_t GlobalHalf;
 
 // A wavefront-uniform global pointer, kept in scalar registers.
 __device__ __forceinline__ GlobalWord *uniform_words(uint32_t *ptr)
@@ -16,12 +17,37 @@ __device__ __forceinline__ GlobalWord *uniform_words(uint32_t *ptr)
     return (GlobalWord *)(lo | (hi << 32));
 }
 
+// 24-bit products of rule step 4 carry n + 2^21, the unrounded offset with the
+// rounding's half added (kRoundHalf as the addend of the last multiply-add).
+// Where n is no odd multiple of 2^21, rounding half away from zero is then an
+// arithmetic shift by 22.  An odd multiple needs sq (C u - S v) to have exactly
+// 21 trailing zero bits; the rotation table holds, per angle bin, for which
+// numbers of trailing zeros of sq some window position does (tie_masks, on the
+// host).  No scale with fewer than 3 (windows of 48; 2 for 64) has such an
+// angle; at scale 1 (8) 9% of the bins do.
+constexpr int kRoundHalf = 1 << 21;
+
 // n / 2^22 rounded half away from zero, for |n| < 2^31 - 2^21.
 // n >= 0: floor((n + 2^21) / 2^22).  n < 0: floor((n + 2^21 - 1) / 2^22),
 // which equals ceil((n - 2^21) / 2^22) = -floor((-n + 2^21) / 2^22).
 __device__ __forceinline__ int round_q22(int n)
 {
     return (n + (1 << 21) + (n >> 31)) >> 22;
+}
+
+// v, as a value the compiler does not know, made where it is used: what
+// follows from it is not kept in registers over a loop.
+__device__ __forceinline__ int opaque(int v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// Offset of m = n + 2^21, with kTies as round_q22 has it for any n.
+template <bool kTies>
+__device__ __forceinline__ int round_half(int m)
+{
+    return kTies ? round_q22(m - kRoundHalf) : m >> 22;
 }
 
 __device__ __forceinline__ int clamp_med3(int x, int lo, int hi)
@@ -78,6 +104,7 @@ struct Keypoint {
     bool ok;        // inside the rule's domain (and a real keypoint)
     bool interior;  // every sample lies inside the image: no clamping needed
     int cx, cy;
+    bool ties;      // some window position's offset lies halfway between two integers
     int c, s, sq;   // C[b], S[b] (Q14) and the Q8 scale
     int cls;        // angle class b >> 5 (0..127), which orders the window gather
     const uint8_t *img;
@@ -104,7 +131,7 @@ struct ImageSource {
 struct KeypointBatch {
     int cx, cy;
     int cs;          // C[b] & 0xffff | S[b] << 16
-    int sq_flags;    // sq | ok << 16 | interior << 17 | bad image << 18 | (b >> 5) << 19
+    int sq_flags;    // sq | ok << 16 | interior << 17 | bad image << 18 | (b >> 5) << 19 | ties << 26
     int id;          // image table: the keypoint's image (0 when out of range)
     int key;         // keypoint index (the position itself without an order)
 };
@@ -117,7 +144,8 @@ __device__ __forceinline__ KeypointBatch prepare_batch(const float4 *__restrict_
                                                        const ImageSource &src)
 {
     KeypointBatch kb;
-    int64_t idx = first + stride * lane;
+    // (first < 2^31 and the workgroups' strides keep the product small.)
+    int64_t idx = first + (int64_t)((int)stride * opaque(lane));
     const bool real = idx < n;
     if (kTable && src.order && real) idx = src.order[idx];
     const uint8_t *img = src.img;
@@ -154,15 +182,17 @@ __device__ __forceinline__ KeypointBatch prepare_batch(const float4 *__restrict_
         sq = (int)sqd;
     }
     const int2 cs = rot[bin];
+    const int c = (int)(short)(cs.x & 0xffff), s = cs.x >> 16;
     // |offset| <= (kHalfSide sq (|C| + |S|) + 2^21) / 2^22 < reach.
-    const int reach = ((kHalfSide * sq * (abs(cs.x) + abs(cs.y))) >> 22) + 1;
+    const int reach = ((kHalfSide * sq * (abs(c) + abs(s))) >> 22) + 1;
+    const int tie_bit = (kHalfSide <= kHalf ? 0 : 16) + __builtin_ctz(sq | 1024);
     const bool interior = ok && cx - reach >= 0 && cx + reach <= width - 1 && cy - reach >= 0 &&
                           cy + reach <= height - 1;
     kb.cx = cx;
     kb.cy = cy;
-    kb.cs = (cs.x & 0xffff) | (cs.y << 16);
+    kb.cs = cs.x;
     kb.sq_flags = sq | ((int)ok << 16) | ((int)interior << 17) | ((int)(real && !image_ok) << 18) |
-                  ((bin >> 5) << 19);
+                  ((bin >> 5) << 19) | (int)(((uint32_t)cs.y >> tie_bit & 1u) << 26);
     kb.id = image_id;
     kb.key = (int)idx;
     return kb;
@@ -184,7 +214,8 @@ __device__ __forceinline__ Keypoint batch_get(const KeypointBatch &kb, int j, co
     k.ok = (f >> 16) & 1;
     k.interior = (f >> 17) & 1;
     *bad_image = (f >> 18) & 1;
-    k.cls = f >> 19;
+    k.cls = (f >> 19) & (kGatherClasses - 1);
+    k.ties = (f >> 26) & 1;
     if (kTable) {
         // The keypoint's image entry, a uniform (scalar) load; the entry was
         // validated per lane in prepare_batch, and ok is false otherwise.

@@ -19,9 +19,9 @@ using namespace latch;
 struct latch_ctx {
     int device = 0;
     int num_cus = 0;
-    int2 *rot_dev = nullptr;           // [4096] {cos_q14, sin_q14}
+    int2 *rot_dev = nullptr;           // [4096] {cos_q14 | sin_q14 << 16, tie masks}
     uint2 *trip_off_dev = nullptr;     // [512] by slot: LDS byte offsets of the three patches
-    uint32_t *unperm_dev = nullptr;    // [128] output-bit slots per (wavefront, lane)
+    uint32_t *bit_of_dev = nullptr;    // [256] output bits of the slots per (wavefront, lane)
     uint16_t *gather_dev = nullptr;    // [kGatherClasses][kGatherClassEntries] window gather order
     uint32_t *flags_dev = nullptr;     // sticky error word
     // Weighted geometry (latch_create_geometry); window 0 runs the default kernel.
@@ -87,6 +87,34 @@ void rotation_table(int16_t *c, int16_t *s)
     }
 }
 
+// Per angle bin, the numbers k of trailing zero bits of sq (bits 0..10) for
+// which some position (u, v) with |u|, |v| <= 24 (low half of the word) or 32
+// (high half) has an unrounded offset halfway between two integers: sq (C u - S v)
+// is an odd multiple of 2^21 iff C u - S v has exactly 21 - k trailing zeros.
+// The second coordinate S u + C v takes the same values over the square, and so
+// do the bins that quarter turns and the swap of C and S relate.
+std::vector<uint32_t> tie_masks(const int16_t *c, const int16_t *s)
+{
+    std::vector<uint32_t> mask(kBins);
+    for (int a = 0; a <= 512; ++a) {
+        uint32_t m = 0;
+        for (int v = 0; v <= 32; ++v)
+            for (int u = -32; u <= 32; ++u) {
+                const int x = c[a] * u - s[a] * v;
+                if (x == 0) continue;
+                const int k = 21 - __builtin_ctz((unsigned)x);
+                if (k > 10) continue;                      // (|x| < 2^21, so k >= 1)
+                m |= 1u << (16 + k);
+                if (v <= kHalf && u >= -kHalf && u <= kHalf) m |= 1u << k;
+            }
+        for (int q = 0; q < kBins; q += 1024) {
+            mask[(a + q) % kBins] = m;
+            mask[(1024 - a + q) % kBins] = m;
+        }
+    }
+    return mask;
+}
+
 // Gather order of the extraction kernel.  Rounding half away from zero is
 // odd, so positions (u, v) and (-u, -v) sample at offsets (ox, oy) and
 // (-ox, -oy), and the unrounded offsets of (u + 1, v) are those of (u, v)
@@ -103,10 +131,9 @@ void rotation_table(int16_t *c, int16_t *s)
 // (a quarter row at unit scale), then by its column offset (ties by
 // position), so that the lanes of a load sample nearby image bytes and the
 // mirrored members form the mirrored band.  Sorted chain k goes to thread
-// k % 128, slot k / 128; the 27 slots left over repeat the centre's chain
-// (0, 0), (1, 0).  Entry: u & 0xff | (v & 0xff) << 8; slots 0..3 of thread t
-// at 4 t + slot, slot 4 at 512 + t (one 8-byte and one 2-byte load per
-// thread).
+// k % 256, slot k / 256 (0, 1, and 2 for the first 128 threads); the 27 slots
+// left over repeat the centre's chain (0, 0), (1, 0).  Entry:
+// u & 0xff | (v & 0xff) << 8, laid out as internal.h says.
 std::vector<uint16_t> gather_order()
 {
     constexpr int kThreads = 2 * 64;
@@ -136,9 +163,8 @@ std::vector<uint16_t> gather_order()
         for (int k = 0; k < kThreads * kGatherChains; ++k) {
             const int p = k < n ? idx[k] : 0;                    // units[0]: the centre's chain
             const int u = units[p].first, v = units[p].second;
-            const int t = k % kThreads, m = k / kThreads;
-            const int at = m < kGatherHeadChains ? kGatherHeadChains * t + m
-                                                 : kGatherHeadChains * kThreads + t;
+            const int t = k % 256, m = k / 256;
+            const int at = m < 2 ? 2 * t + m : 512 + t;
             table[(size_t)c * kGatherClassEntries + at] = (uint16_t)((u & 0xff) | ((v & 0xff) << 8));
         }
     }
@@ -157,10 +183,9 @@ uint32_t patch_offset(int r, int c)
     return (uint32_t)(kEdgeBase + 8 * (x - 8 * kCopyQwords) + y * kCopyRowBytes + 8 * (kCopyQwords - 1));
 }
 
-// Slot assignment of the extraction kernels.  Wavefront w evaluates
-// `per_wave` triplets (members 0 .. per_wave - 1 of toff[per_wave w ..]) in
-// rounds of 64 lanes; slot 64 r + l is lane l of round r.  On gfx950 (measured
-// with a probe over random and structured address patterns):
+// Slot assignment of the extraction kernels: n triplets in slots of 64-lane
+// rounds, slot 64 r + l being lane l of round r.  On gfx950 (measured with a
+// probe over random and structured address patterns):
 //  * a ds_read_b64 is served 32 lanes at a time over 64 dword banks, so its
 //    32-lane halves read without conflicts when their quadword addresses
 //    differ mod 32;
@@ -170,100 +195,117 @@ uint32_t patch_offset(int r, int c)
 // `group` (lanes served together) and `cols` (quadword banks) name the
 // model of the kernel's row reads.  Every patch row read of a lane is its
 // patch offset plus a uniform row offset, so the bank of all rows follows
-// from the patch offset.  A deterministic annealing search over swaps puts
-// triplets into the lane groups of a wavefront so that, per group and per
-// patch (anchor, companion 1, companion 2), the largest number of lanes
-// sharing a bank is as small as it gets.  slot_of[per_wave w + i] is the
-// slot (within its wavefront) of member i; results never depend on it, only
-// speed does.
-void search_slots(const uint2 *toff, int waves, int per_wave, int group, int cols, uint8_t *slot_of)
+// from the patch offset, and a read costs as many cycles as the largest number
+// of a group's lanes on one bank.  A deterministic annealing search over swaps
+// puts triplets into lane groups so that these maxima, per group and per patch
+// (anchor, companion 1, companion 2), sum to as little as it gets.  The table
+// itself sets a floor: a bank that holds more patches than there are groups
+// doubles up in some group.  So what helps is to gather the doubled lanes in few
+// groups: beside the maxima the objective counts the square root of a group's
+// lanes that share a bank with another.  (Sums for the default table: 82 with
+// all 512 triplets free, 88 within halves of 256, 103 within quarters of 128;
+// 96 is two cycles everywhere, and the sum of squared counts as the second
+// objective gives 95 within halves.)
+// slot[i] is the slot of triplet i; results never depend on it, only speed
+// does.
+void search_slots(const uint2 *toff, int n, int group, int cols, uint16_t *slot)
 {
-    constexpr int kIters = 3000000;
-    for (int w = 0; w < waves; ++w) {
-        std::vector<std::array<int, 3>> col(per_wave);
-        for (int i = 0; i < per_wave; ++i) {
-            const uint2 o = toff[per_wave * w + i];
-            const uint32_t off[3] = {o.x & 0xffffu, o.x >> 16, o.y};
-            for (int k = 0; k < 3; ++k) col[i][k] = (int)((off[k] >> 3) & (uint32_t)(cols - 1));
+    constexpr int kItersPerTriplet = 8000, kMaxGroup = 64;
+    constexpr float kMaximum = 100.0f, kShared = 20.0f, kTemperature = 10.0f;
+    // One group's lanes by the bank of one patch.
+    struct Banks {
+        int count[32], banks_with[kMaxGroup + 1], shared, most;
+    };
+    const int groups = n / group;
+    std::vector<std::array<int, 3>> col(n);
+    for (int i = 0; i < n; ++i) {
+        const uint32_t off[3] = {toff[i].x & 0xffffu, toff[i].x >> 16, toff[i].y};
+        for (int k = 0; k < 3; ++k) col[i][k] = (int)((off[k] >> 3) & (uint32_t)(cols - 1));
+    }
+    std::vector<std::array<Banks, 3>> state(groups);
+    auto add = [&](Banks &b, int c) {
+        const int v = b.count[c]++;
+        --b.banks_with[v];
+        ++b.banks_with[v + 1];
+        b.shared += v >= 1;
+        if (v + 1 > b.most) b.most = v + 1;
+    };
+    auto remove = [&](Banks &b, int c) {
+        const int v = b.count[c]--;
+        --b.banks_with[v];
+        ++b.banks_with[v - 1];
+        b.shared -= v >= 2;
+        while (b.banks_with[b.most] == 0) --b.most;
+    };
+    std::vector<int> group_of(n);
+    for (auto &g : state)
+        for (Banks &b : g) {
+            std::memset(&b, 0, sizeof b);
+            b.banks_with[0] = cols;
         }
-        std::vector<int> group_of(per_wave);
-        int cnt[16][3][32];
-        std::memset(cnt, 0, sizeof cnt);
-        for (int i = 0; i < per_wave; ++i) {
-            group_of[i] = i / group;
-            for (int k = 0; k < 3; ++k) ++cnt[group_of[i]][k][col[i][k]];
+    for (int i = 0; i < n; ++i) {
+        group_of[i] = i / group;
+        for (int k = 0; k < 3; ++k) add(state[group_of[i]][k], col[i][k]);
+    }
+    float root[kMaxGroup + 1];
+    for (int v = 0; v <= kMaxGroup; ++v) root[v] = kShared * std::sqrt((float)v);
+    auto cost = [&](int g) {
+        float c = 0.0f;
+        for (const Banks &b : state[g]) c += kMaximum * (float)b.most + root[b.shared];
+        return c;
+    };
+    uint32_t rs = 0x9e3779b9u;
+    auto rnd = [&]() {
+        rs ^= rs << 13;
+        rs ^= rs >> 17;
+        rs ^= rs << 5;
+        return rs;
+    };
+    auto swap_members = [&](int i, int j, int g, int h) {
+        for (int k = 0; k < 3; ++k) {
+            const int a = col[i][k], b = col[j][k];
+            if (a == b) continue;
+            remove(state[g][k], a);
+            add(state[g][k], b);
+            remove(state[h][k], b);
+            add(state[h][k], a);
         }
-        auto gmax = [&](int g, int k) {
-            int m = 0;
-            for (int c = 0; c < cols; ++c) m = cnt[g][k][c] > m ? cnt[g][k][c] : m;
-            return m;
-        };
-        uint32_t rs = 0x9e3779b9u + (uint32_t)w;
-        auto rnd = [&]() {
-            rs ^= rs << 13;
-            rs ^= rs >> 17;
-            rs ^= rs << 5;
-            return rs;
-        };
-        for (int it = 0; it < kIters; ++it) {
-            const int i = (int)(rnd() % (uint32_t)per_wave), j = (int)(rnd() % (uint32_t)per_wave);
-            const int G = group_of[i], H = group_of[j];
-            if (G == H) continue;
-            int before = 0, after = 0, sq = 0;
-            for (int k = 0; k < 3; ++k) before += gmax(G, k) + gmax(H, k);
-            for (int k = 0; k < 3; ++k) {
-                const int a = col[i][k], b = col[j][k];
-                if (a == b) continue;
-                sq += 2 * (cnt[G][k][b] - cnt[G][k][a] + 1) + 2 * (cnt[H][k][a] - cnt[H][k][b] + 1);
-                --cnt[G][k][a];
-                ++cnt[G][k][b];
-                --cnt[H][k][b];
-                ++cnt[H][k][a];
-            }
-            for (int k = 0; k < 3; ++k) after += gmax(G, k) + gmax(H, k);
-            // Objective: the summed largest bank multiplicity, then the sum of
-            // squared counts; worse moves pass with a probability that
-            // shrinks to zero over the search.
-            const int d = 64 * (after - before) + sq;
-            const double temp = 40.0 * (1.0 - (double)it / kIters);
-            const bool accept =
-                d <= 0 || (temp > 0.5 && (double)(rnd() & 0xffffu) < 65536.0 * std::exp(-d / temp));
-            if (accept) {
-                group_of[i] = H;
-                group_of[j] = G;
-            } else {
-                for (int k = 0; k < 3; ++k) {
-                    const int a = col[i][k], b = col[j][k];
-                    if (a == b) continue;
-                    ++cnt[G][k][a];
-                    --cnt[G][k][b];
-                    ++cnt[H][k][b];
-                    --cnt[H][k][a];
-                }
-            }
-        }
-        // Group g = (64 / group) r + h is lanes group h .. group (h + 1) - 1
-        // of round r.
-        const int per_round = 64 / group;
-        int fill[16] = {0};
-        for (int i = 0; i < per_wave; ++i) {
-            const int g = group_of[i];
-            slot_of[per_wave * w + i] = (uint8_t)(64 * (g / per_round) + group * (g % per_round) + fill[g]++);
-        }
+        group_of[i] = h;
+        group_of[j] = g;
+    };
+    const int iters = kItersPerTriplet * n;
+    for (int it = 0; it < iters; ++it) {
+        const int i = (int)(rnd() % (uint32_t)n), j = (int)(rnd() % (uint32_t)n);
+        const int g = group_of[i], h = group_of[j];
+        if (g == h) continue;
+        const float before = cost(g) + cost(h);
+        swap_members(i, j, g, h);
+        // Worse moves pass with a probability that shrinks to zero over the
+        // search.
+        const float d = cost(g) + cost(h) - before;
+        const float temp = kTemperature * (1.0f - (float)it / (float)iters);
+        if (d > 0.0f && !(d < 12.0f * temp && (float)(rnd() & 0xffffu) < 65536.0f * std::exp(-d / temp)))
+            swap_members(j, i, g, h);
+    }
+    // Group g = (64 / group) r + h is lanes group h .. group (h + 1) - 1 of
+    // round r.
+    const int per_round = 64 / group;
+    std::vector<int> fill(groups, 0);
+    for (int i = 0; i < n; ++i) {
+        const int g = group_of[i];
+        slot[i] = (uint16_t)(64 * (g / per_round) + group * (g % per_round) + fill[g]++);
     }
 }
 
 // search_slots takes a few hundred milliseconds; its result depends only on
 // the offsets, so it is kept per process for each offset table.
-void assign_slots(const uint2 *toff, int waves, int per_wave, int group, int cols, uint8_t *slot_of)
+void assign_slots(const uint2 *toff, int n, int group, int cols, uint16_t *slot)
 {
     static std::mutex mu;
-    static std::map<std::vector<uint32_t>, std::vector<uint8_t>> cache;
-    const int n = waves * per_wave;
+    static std::map<std::vector<uint32_t>, std::vector<uint16_t>> cache;
     std::vector<uint32_t> key;
-    key.reserve(2 * n + 4);
-    key.push_back((uint32_t)waves);
-    key.push_back((uint32_t)per_wave);
+    key.reserve(2 * n + 3);
+    key.push_back((uint32_t)n);
     key.push_back((uint32_t)group);
     key.push_back((uint32_t)cols);
     for (int i = 0; i < n; ++i) {
@@ -274,13 +316,24 @@ void assign_slots(const uint2 *toff, int waves, int per_wave, int group, int col
         std::lock_guard<std::mutex> lock(mu);
         auto it = cache.find(key);
         if (it != cache.end()) {
-            std::memcpy(slot_of, it->second.data(), (size_t)n);
+            std::copy(it->second.begin(), it->second.end(), slot);
             return;
         }
     }
-    search_slots(toff, waves, per_wave, group, cols, slot_of);
+    search_slots(toff, n, group, cols, slot);
     std::lock_guard<std::mutex> lock(mu);
-    cache.emplace(std::move(key), std::vector<uint8_t>(slot_of, slot_of + n));
+    cache.emplace(std::move(key), std::vector<uint16_t>(slot, slot + n));
+}
+
+// The same for `waves` sets of per_wave (at most 256) triplets, each in the
+// slots of its own wavefront.
+void assign_slots(const uint2 *toff, int waves, int per_wave, int group, int cols, uint8_t *slot_of)
+{
+    std::vector<uint16_t> slot(per_wave);
+    for (int w = 0; w < waves; ++w) {
+        assign_slots(toff + per_wave * w, per_wave, group, cols, slot.data());
+        for (int i = 0; i < per_wave; ++i) slot_of[per_wave * w + i] = (uint8_t)slot[i];
+    }
 }
 
 // Work calls never allocate or wait: a call whose need exceeds the handle's
@@ -543,7 +596,7 @@ ExtractArgs batch_extract_args(latch_handle h, const latch_image *images_dev, in
     a.n_dev = n_kps_dev;
     a.rot = h->rot_dev;
     a.trip_off = h->trip_off_dev;
-    a.unperm = h->unperm_dev;
+    a.bit_of = h->bit_of_dev;
     a.gather = h->gather_dev;
     a.desc = desc_dev;
     a.flags = h->flags_dev;
@@ -628,8 +681,10 @@ int create_base(latch_ctx **out)
     }
     int16_t c[kBins], s[kBins];
     rotation_table(c, s);
+    const std::vector<uint32_t> ties = tie_masks(c, s);
     int2 rot[kBins];
-    for (int a = 0; a < kBins; ++a) rot[a] = make_int2(c[a], s[a]);
+    for (int a = 0; a < kBins; ++a)
+        rot[a] = make_int2((int)((uint16_t)c[a] | (uint32_t)(uint16_t)s[a] << 16), (int)ties[a]);
     if ((e = hipMalloc((void **)&h->rot_dev, sizeof rot)) == hipSuccess &&
         (e = hipMalloc((void **)&h->flags_dev, sizeof(uint32_t))) == hipSuccess) {
         const Upload u[2] = {{h->rot_dev, rot, sizeof rot}, {h->flags_dev, nullptr, sizeof(uint32_t)}};
@@ -747,17 +802,16 @@ int latch_create(latch_handle *out, const uint8_t *triplets_host)
         toff[t].x = patch_offset(tr[0], tr[1]) | (patch_offset(tr[2], tr[3]) << 16);
         toff[t].y = patch_offset(tr[4], tr[5]);
     }
-    // Triplets by slot, and per (wavefront w, lane l) the slots of output
-    // bits 256 w + 64 k + l, k = 0..3, one byte each.
-    uint8_t slot_of[kTriplets];
-    assign_slots(toff, 2, 256, 32, 32, slot_of);   // row reads: ds_read_b64
+    // Triplets by slot, and per (wavefront w, lane l) the output bits of its
+    // slots 128 w + l and 128 w + 64 + l.
+    uint16_t slot_of[kTriplets];
+    assign_slots(toff, kTriplets, 32, 32, slot_of);   // row reads: ds_read_b64
     uint2 toff_slot[kTriplets];
-    uint32_t unperm[2 * 64] = {};
+    uint32_t bit_of[kExtractWaves * 64] = {};
     for (int t = 0; t < kTriplets; ++t) {
-        const int w = t >> 8;
-        toff_slot[256 * w + slot_of[t]] = toff[t];
-        const int k = (t >> 6) & 3, l = t & 63;
-        unperm[64 * w + l] |= (uint32_t)slot_of[t] << (8 * k);
+        const int s = slot_of[t], w = s >> 7, r = (s >> 6) & 1, l = s & 63;
+        toff_slot[s] = toff[t];
+        bit_of[64 * w + l] |= (uint32_t)t << (16 * r);
     }
     uint2 doff[kTriplets];
     for (int t = 0; t < kTriplets; ++t) {
@@ -769,12 +823,12 @@ int latch_create(latch_handle *out, const uint8_t *triplets_host)
     const size_t order_bytes = order.size() * sizeof(uint16_t);
     hipError_t e;
     if ((e = hipMalloc((void **)&h->trip_off_dev, sizeof toff_slot)) == hipSuccess &&
-        (e = hipMalloc((void **)&h->unperm_dev, sizeof unperm)) == hipSuccess &&
+        (e = hipMalloc((void **)&h->bit_of_dev, sizeof bit_of)) == hipSuccess &&
         (e = hipMalloc((void **)&h->dense_off_dev, sizeof doff)) == hipSuccess &&
         (e = hipMalloc((void **)&h->gather_dev, order_bytes)) == hipSuccess) {
         const Upload u[4] = {{h->dense_off_dev, doff, sizeof doff},
                              {h->trip_off_dev, toff_slot, sizeof toff_slot},
-                             {h->unperm_dev, unperm, sizeof unperm},
+                             {h->bit_of_dev, bit_of, sizeof bit_of},
                              {h->gather_dev, order.data(), order_bytes}};
         e = upload(u, 4);
     }
@@ -865,7 +919,7 @@ void latch_destroy(latch_handle h)
     (void)hipDeviceSynchronize();
     if (h->rot_dev) (void)hipFree(h->rot_dev);
     if (h->trip_off_dev) (void)hipFree(h->trip_off_dev);
-    if (h->unperm_dev) (void)hipFree(h->unperm_dev);
+    if (h->bit_of_dev) (void)hipFree(h->bit_of_dev);
     if (h->gather_dev) (void)hipFree(h->gather_dev);
     if (h->flags_dev) (void)hipFree(h->flags_dev);
     if (h->wtrip_dev) (void)hipFree(h->wtrip_dev);
@@ -907,7 +961,7 @@ int latch_extract(latch_handle h, const uint8_t *img_dev, int height, int width,
     a.n_dev = nullptr;
     a.rot = h->rot_dev;
     a.trip_off = h->trip_off_dev;
-    a.unperm = h->unperm_dev;
+    a.bit_of = h->bit_of_dev;
     a.gather = h->gather_dev;
     a.desc = desc_dev;
     a.flags = h->flags_dev;

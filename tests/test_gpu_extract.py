@@ -165,3 +165,32 @@ def test_bad_arguments_raise(torch_cuda, lat):
                                                   ctypes.c_void_p(kps.data_ptr()), None)
         binding._check(lat.h, rc)
     assert e.value.code == -1
+
+
+@pytest.mark.parametrize("sq", [1, 2, 3, 4, 8, 16, 32, 64, 128, 256, 307, 511, 512, 513, 768, 1024])
+def test_every_angle_bin_by_scale(torch_cuda, lat, triplets, sq):
+    """All 4,096 angle bins at scales of every number of trailing zero bits (so
+    with and without offsets halfway between two pixels) and on both sides of
+    512, from an interior centre, and every 16th bin at a corner (clamped)."""
+    g = np.random.default_rng(900 + sq)
+    img = g.integers(0, 256, (300, 333), dtype=np.uint8)
+    kps = np.zeros((4096 + 256, 4), np.float32)
+    kps[:, 0], kps[:, 1], kps[:, 3] = 166, 150, sq / 256.0
+    kps[:4096, 2] = np.arange(4096) * (360.0 / 4096.0)
+    kps[4096:, 2] = kps[:4096:16, 2]
+    kps[4096:, :2] = 5, 290
+    assert_parity(torch_cuda, lat, triplets, img, kps)
+
+
+@pytest.mark.parametrize("bad", [0.1, 0.6, 0.98])
+def test_bad_keypoints_between_good_ones(torch_cuda, lat, triplets, bad):
+    """Several keypoints per workgroup with out-of-domain ones anywhere among
+    them (first, last and in runs): zeros there, every other row complete."""
+    g = np.random.default_rng(int(1000 * bad))
+    img = synth.smoothed_noise(g, 200, 260)
+    kps = synth.random_keypoints(g, 9001, 200, 260)
+    out = g.random(len(kps)) < bad
+    out[-3000:-1] |= g.random(2999) < 0.5
+    kps[out, 3] = np.where(g.random(out.sum()) < 0.5, 0.0, np.nan)
+    kps[7, 3] = np.inf
+    assert_parity(torch_cuda, lat, triplets, img, kps, expect_flag=1)
