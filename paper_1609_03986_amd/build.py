@@ -24,6 +24,9 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
 ]
+# The MXFP4 matcher's keys are floats that are never NaN; without this every
+# maximum would quiet its operands first.
+FILE_FLAGS = {"knn.hip": ["-fno-honor-nans"]}
 _HARMLESS = "'-packed-fp32-ops' is not a recognized feature for this target"
 
 
@@ -51,8 +54,8 @@ def build(verbose=False):
     jobs = []
     for src in SOURCES:
         obj = os.path.join(CSRC, src.replace(".hip", ".o"))
-        cmd = [hipcc()] + HIPCC_FLAGS + ["-I", os.path.join(ROOT, "include"), "-c",
-                                         os.path.join(CSRC, src), "-o", obj]
+        cmd = [hipcc()] + HIPCC_FLAGS + FILE_FLAGS.get(src, []) + [
+            "-I", os.path.join(ROOT, "include"), "-c", os.path.join(CSRC, src), "-o", obj]
         jobs.append((cmd, obj))
     workers = max(1, min(len(jobs), os.cpu_count() or 1, 8))
     with concurrent.futures.ThreadPoolExecutor(workers) as pool:

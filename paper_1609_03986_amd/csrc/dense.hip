@@ -46,6 +46,7 @@ namespace latch {
 namespace {
 
 #include "fp4.h"
+#include "lanes.h"
 #include "packed16.h"
 #include "xcd_range.h"
 
@@ -344,40 +345,6 @@ __device__ __forceinline__ void insert_keys(int &k1, int &k2, int x, int y)
     const int m = imed3(k1, x, y);
     asm("v_max3_i32 %0, %0, %1, %2" : "+v"(k1) : "v"(x), "v"(y), "v"(m));
     k2 = max(k2, m);
-}
-
-// The pairs (x1 >= x2) and (y1 >= y2) of two blocks hold partial results on
-// every lane; after the exchange x holds, for one block per lane half (or row
-// parity), both partners' partials, which are merged.
-template <bool kHalves>
-__device__ __forceinline__ void exchange(int &x, int &y)
-{
-    if constexpr (kHalves) {
-        const auto v = __builtin_amdgcn_permlane32_swap(x, y, false, false);
-        x = (int)v[0];
-        y = (int)v[1];
-    } else {
-        const auto v = __builtin_amdgcn_permlane16_swap(x, y, false, false);
-        x = (int)v[0];
-        y = (int)v[1];
-    }
-}
-
-template <bool kHalves>
-__device__ __forceinline__ void exchange_top2(int &x1, int &x2, int &y1, int &y2)
-{
-    exchange<kHalves>(x1, y1);
-    exchange<kHalves>(x2, y2);
-    const int lo = min(x1, y1);
-    x1 = max(x1, y1);
-    x2 = max(lo, max(x2, y2));
-}
-
-template <bool kHalves>
-__device__ __forceinline__ void exchange_sum(int &x, int &y)
-{
-    exchange<kHalves>(x, y);
-    x += y;
 }
 
 // v, as a value the compiler does not know: what follows from it is computed

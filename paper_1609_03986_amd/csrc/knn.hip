@@ -20,12 +20,15 @@
 // ties resolve to the lowest index because the index is part of the key.  Each (query,
 // train split) writes its best two as 64-bit (distance << 32 | index) values;
 // a merge kernel reduces over splits and applies the ratio test.
+#include <type_traits>
+
 #include "internal.h"
 
 namespace latch {
 namespace {
 
 #include "fp4.h"
+#include "lanes.h"
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
@@ -132,7 +135,8 @@ __device__ __forceinline__ uint2 load_tile(const uint32_t *__restrict__ train, i
     const int row = tile * kTileRows + (tid & 31);
     const int src = max(min(row, nt - 1), 0);
     const uint2 w = reinterpret_cast<const uint2 *>(train + (size_t)src * kWords)[tid >> 5];
-    return row < nt ? w : make_uint2(0, 0);
+    const uint32_t keep = row < nt ? 0xffffffffu : 0u;
+    return make_uint2(w.x & keep, w.y & keep);
 }
 
 __device__ __forceinline__ void stage_tile(uint2 w, int tid, v4i *__restrict__ buf)
@@ -345,8 +349,8 @@ __device__ __forceinline__ void top2_pair(uint64_t &a1, uint64_t &a2, uint64_t c
 }
 
 // ---------------------------------------------------------------------------
-// MXFP4 matcher.  Same tiling as the int8 path, on the block-scaled FP4
-// matrix instruction v_mfma_scale_f32_32x32x64_f8f6f4 (K = 64 per
+// MXFP4 matcher.  Same staging as the int8 path, on the block-scaled FP4
+// matrix instruction v_mfma_scale_f32_16x16x128_f8f6f4 (K = 128 per
 // instruction, twice the int8 rate on gfx950).
 //
 // Operands.  FP4 (e2m1) holds 0 (0x0), +-0.5 (0x1 / 0x9), +-1 (0x2 / 0xa)
@@ -359,168 +363,192 @@ __device__ __forceinline__ void top2_pair(uint64_t &a1, uint64_t &a2, uint64_t c
 // Keys.  For tile row m the accumulator starts at c_m = 2^14 - 1 - m, so it
 // ends at 2^14 s + c_m; the running top-2 of a lane is kept in the frame of
 // the current tile and moved up by 32 when the next tile starts, so a key
-// from split-local row jl = 32 t + m ends as 2^14 s + 2^14 - 1 - jl + 32 T
-// after T tiles (T < 512): integers below 2^24 in magnitude, exact in f32.
+// from split-local row jl = 32 t + m ends as 2^14 s + 2^14 - 1 - jl + 32 (T - 1)
+// after T tiles (T <= 512): integers below 2^24 in magnitude, exact in f32.
 // For a fixed query the largest key is the smallest (distance, index).  Rows
-// past nt (last tile only) start at -2^25 instead, below every real key,
+// past nt (last tile only) take -2^25 instead, below every real key,
 // which also marks "no neighbour".  Top-2 selection takes the keys two at a
 // time: v_med3_f32, v_max3_f32 and v_max_f32 per two pairs.
 //
-// Fragment order.  Step s (0..7), lane l: the 32 elements of row l % 32 at
-// K = 64 s + 32 (l / 32) + 0..31 are the bits of packed word 2 s + l / 32 of
-// that row, bit 4 i + j in nibble i of dword j (16 bytes); queries use the
-// same map, so the K sum covers every bit once.  In this order a train word
-// becomes FP4 with four AND masks and one shift, no table: dword j keeps its
-// bits where they are, as nibble bit 0, 1, 2 (values 0.5, 1, 2) for
-// j = 0, 1, 2, and bit 3 (the sign) is moved down to bit 2 for j = 3, so
-// c = 0.5, 1, 2, 2 by dword.
+// Fragment order.  Step s (0..3), lane l = 16 g + n: the 32 elements of row n
+// (of a subtile of 16 train rows, of a block of 16 queries) at K = 128 s + 32 g
+// + 0..31 are the bits of packed word 4 g + s of that row, bit 4 i + j in nibble
+// i of dword j (16 bytes).  Train rows and queries use the same map, so the K
+// sum covers every bit once, and a lane's four query words are one 16-byte load.
+// In this order a train word becomes FP4 with four AND masks and one shift, no
+// table: dword j keeps its bits where they are, as nibble bit 0, 1, 2 (values
+// 0.5, 1, 2) for j = 0, 1, 2, and bit 3 (the sign) is moved down to bit 2 for
+// j = 3, so c = 0.5, 1, 2, 2 by dword.
 //
-// Tile shape.  A wavefront holds QB blocks of 32 queries (QB = 2 or 3, from
-// the tuning table), so each train fragment read from LDS feeds QB MFMAs and
-// each staged tile serves 128 QB queries of the workgroup.  Measured on 63
-// pairs of 20k x 20k random descriptors: 4.98 ms per batched launch with
-// the table-based expansion and one-key insertion, 4.70 ms with the masks
-// and two-key insertion (QB = 3, whose 256 VGPRs hold 96 of query
-// fragments; QB = 2 is about 5% slower).
+// Bound: the matrix cores, and through their power the clock.  On random bits
+// this instruction alone sustains 9.15 PFLOP/s and the 32x32x64 one, which
+// moves twice the accumulator registers per product, 7.55 PFLOP/s; the
+// matcher reaches 6.6 PFLOP/s at 8000 x 1,000,000 (matrix cores busy 70% of the
+// cycles at about 2.0 GHz), since four lane rows select from every block and
+// the selection (12 VALU instructions per 8 MFMAs) shares the issue slots.
+//
+// Tile shape.  A wavefront holds 2 QB blocks of 16 queries (QB = 2 or 3, from
+// the tuning table), so each train fragment read from LDS feeds 2 QB MFMAs and
+// each staged tile serves 128 QB queries of the workgroup; QB = 4 spills.  A
+// lane's 4 accumulators per block and subtile are rows of one query, whose
+// top two live in all four lane rows until the end of the range.  Both subtiles'
+// products come before their selection; a hand-written software pipeline that
+// selected the previous subtile between MFMAs was slower (1370 us), and so was
+// a frame of 64 rows, whose start values take the batched kernel's last
+// registers.  Measured, 32x32x64 -> 16x16x128: 8000 x 1,000,000 1370 -> 1246 us,
+// 20,000 x 20,000 83.2 -> 76.1 us, 15 pairs of 20,000 x 20,000 in one batch
+// 1309 -> 1170 us; QB = 2 is about 5% slower where it pads as little.
 // ---------------------------------------------------------------------------
-typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
-constexpr int kFp4Steps = 8;                          // K = 512 = 8 x 64
-constexpr int kFp4TileVec = kFp4Steps * 64;           // 16-byte fragments per tile (512)
+constexpr int kFp4Steps = 4;                          // K = 512 = 4 x 128
+constexpr int kFp4SubRows = 16;                       // train rows per MFMA
+constexpr int kFp4Subs = kTileRows / kFp4SubRows;     // subtiles per staged tile
+constexpr int kFp4TileVec = kFp4Subs * kFp4Steps * 64;    // 16-byte fragments per tile (512)
 constexpr int kFp4ScaleTrain = 127;                   // E8M0 2^0
 constexpr int kFp4ScaleQuery = 127 + 14;              // E8M0 2^14
 constexpr float kFp4None = -33554432.0f;              // -2^25
 
+// A wavefront's queries with QB (2 or 3): blocks of 16, and sets of four
+// blocks whose results meet one lane row each.
+template <int QB>
+struct Fp4Shape {
+    static constexpr int kBlocks = 2 * QB;
+    static constexpr int kSets = (kBlocks + 3) / 4;
+    static constexpr int kQueries = 16 * kBlocks;
+};
+
 // Two keys into a running top two (k1 >= k2), as insert_pair_u32 does for
-// integer keys: t = med3(k1, x, y), k1 = max3(k1, x, y), k2 = max(k2, t), as
-// one unit (the independent chains of the query blocks interleave; the
-// instructions are written out, since the IEEE-mode fmaxf adds NaN quieting
-// per operand; keys are never NaN).
+// integer keys: v_med3_f32, v_max3_f32 and v_max_f32.  (This file is compiled
+// without NaNs in mind: the IEEE-mode maxima would otherwise quiet every operand.
+// Keys are never NaN.)
 __device__ __forceinline__ void insert_pair(float &k1, float &k2, float x, float y)
 {
-    float t;
-    asm("v_med3_f32 %2, %0, %3, %4\n\t"
-        "v_max3_f32 %0, %0, %3, %4\n\t"
-        "v_max_f32 %1, %1, %2"
-        : "+v"(k1), "+v"(k2), "=&v"(t)
-        : "v"(x), "v"(y));
+    k2 = fmaxf(k2, __builtin_amdgcn_fmed3f(k1, x, y));
+    k1 = fmaxf(fmaxf(k1, x), y);
 }
 
 // Staging role of a thread: tile row tid % 32, packed words 2 (tid / 32) and
-// 2 (tid / 32) + 1, i.e. step tid / 32, both lane halves.
+// 2 (tid / 32) + 1.  Word w of row r is lane 16 (w / 4) + r % 16 of step w % 4 of
+// subtile r / 16.
 __device__ __forceinline__ void stage_tile_fp4(uint2 w, int tid, uint4 *__restrict__ buf)
 {
-    const int r = tid & 31;
-    const int s = tid >> 5;
-    buf[s * 64 + r] = fp4_train(w.x);
-    buf[s * 64 + 32 + r] = fp4_train(w.y);
+    const int r = tid & 31, c = tid >> 5;
+    uint4 *to = buf + ((r >> 4) * kFp4Steps + 2 * (c & 1)) * 64 + 16 * (c >> 1) + (r & 15);
+    to[0] = fp4_train(w.x);
+    to[64] = fp4_train(w.y);
 }
 
 // One (query group, train range) of the MXFP4 matcher.  Train rows
-// split * split_rows .. + split_rows - 1 (split_rows <= 2^14); each lane's
-// queries' best two (distance << 32 | index) are merged into best[qb].
+// split * split_rows .. + split_rows - 1 (split_rows <= 2^14); the best two
+// (distance << 32 | index) of query n = lane % 16 of block 4 t + lane / 16 are
+// merged into best[t].
 template <int QB>
 __device__ __forceinline__ void fp4_item(const uint32_t *__restrict__ query, int nq,
                                          const uint32_t *__restrict__ train, int nt, int qgroup,
-                                         int split, int split_rows, uint64_t (&best)[QB][2],
+                                         int split, int split_rows,
+                                         uint64_t (&best)[Fp4Shape<QB>::kSets][2],
                                          uint4 (*tbuf)[kFp4TileVec])
 {
+    constexpr int kBlocks = Fp4Shape<QB>::kBlocks, kSets = Fp4Shape<QB>::kSets;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int half = lane >> 5;
+    const int g = lane >> 4, n = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int qbase = qgroup * (kMfmaWaves * 32 * QB) + wave * (32 * QB);
+    const int qbase = (qgroup * kMfmaWaves + wave) * Fp4Shape<QB>::kQueries;
 
     const int ntiles_all = (nt + kTileRows - 1) / kTileRows;
     const int tiles_per_split = split_rows / kTileRows;
     const int t_begin = split * tiles_per_split;
     const int t_end = min(ntiles_all, t_begin + tiles_per_split);
 
-    // Tile loads two tiles ahead of staging, as in the int8 path.
+    // Tile loads two tiles ahead of staging.
     uint2 ld0 = make_uint2(0, 0), ra = ld0, rb = ld0;
     if (t_begin < t_end) ld0 = load_tile(train, nt, t_begin, tid);
     if (t_begin + 1 < t_end) ra = load_tile(train, nt, t_begin + 1, tid);
     if (t_begin + 2 < t_end) rb = load_tile(train, nt, t_begin + 2, tid);
 
-    // Resident query fragments (+-1) and query popcounts.
-    uint4 bq[QB][kFp4Steps];
-    int na[QB];
-    uint32_t qw[QB][kWords];
+    // Resident query fragments: words 4 g .. 4 g + 3 of query n of each block
+    // (of row 0 past nq: not stored), and their popcounts.
+    uint4 bq[kBlocks][kFp4Steps];
+    int na[4 * kSets] = {};
+    {
+        uint4 qw[kBlocks];
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) load_query_row(query, nq, qbase + 32 * qb + (lane & 31), qw[qb]);
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        int pc = 0;
-#pragma unroll
-        for (int s = 0; s < kFp4Steps; ++s) {
-            const uint32_t w0 = qw[qb][2 * s], w1 = qw[qb][2 * s + 1];
-            pc += __popc(w0) + __popc(w1);
-            bq[qb][s] = fp4_query(half ? w1 : w0);
+        for (int b = 0; b < kBlocks; ++b) {
+            const int qn = qbase + 16 * b + n;
+            qw[b] = make_uint4(0u, 0u, 0u, 0u);
+            if (nq > 0)
+                qw[b] = reinterpret_cast<const uint4 *>(query + (size_t)(qn < nq ? qn : 0) * kWords)[g];
         }
-        na[qb] = pc;
+#pragma unroll
+        for (int b = 0; b < kBlocks; ++b) {
+            const uint32_t w[4] = {qw[b].x, qw[b].y, qw[b].z, qw[b].w};
+#pragma unroll
+            for (int s = 0; s < kFp4Steps; ++s) {
+                bq[b][s] = fp4_query(w[s]);
+                na[b] += __popc(w[s]);
+            }
+        }
     }
 
-    float k1[QB], k2[QB];
+    float k1[4 * kSets], k2[4 * kSets];
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) k1[qb] = k2[qb] = kFp4None;
+    for (int b = 0; b < 4 * kSets; ++b) k1[b] = k2[b] = kFp4None;
 
-    // Accumulator start values c_m; register r = 4 g + e holds tile row
-    // m = 8 g + 4 half + e.
-    v16f c0;
+    // Accumulator start values c_m; register r of subtile h holds tile row
+    // m = 16 h + 4 g + r.
+    v4f c0[kFp4Subs];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) c0[r] = (float)((1 << 14) - 1 - (8 * (r >> 2) + 4 * half + (r & 3)));
+    for (int h = 0; h < kFp4Subs; ++h)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) c0[h][r] = (float)((1 << 14) - 1 - (kFp4SubRows * h + 4 * g + r));
 
     __syncthreads();       // the staging buffers may still be read for a previous range
     if (t_begin < t_end) stage_tile_fp4(ld0, tid, tbuf[0]);
     __syncthreads();
 
-    // The MFMAs of one tile over LDS buffer `buf`.
-    auto tile_mfma = [&](int buf, v16f (&acc)[QB]) {
+    // Rows past nt (in the last tile only) take a key below every real one.
+    auto mask_tail = [&](int tile, int h, v4f (&acc)[kBlocks]) {
+        const int valid_rows = nt - tile * kTileRows - kFp4SubRows * h;
+        if (valid_rows < kFp4SubRows) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (4 * g + r >= valid_rows)
+#pragma unroll
+                    for (int b = 0; b < kBlocks; ++b) acc[b][r] = kFp4None;
+        }
+    };
+    auto sub_mfma = [&](int buf, int h, v4f (&acc)[kBlocks]) {
 #pragma unroll
         for (int s = 0; s < kFp4Steps; ++s) {
-            const v8i a = fp4_operand(tbuf[buf][s * 64 + lane]);
+            const v8i a = fp4_operand(tbuf[buf][(h * kFp4Steps + s) * 64 + lane]);
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb)
-                acc[qb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                    a, fp4_operand(bq[qb][s]), s == 0 ? c0 : acc[qb], 4, 4, 0, kFp4ScaleTrain, 0,
+            for (int b = 0; b < kBlocks; ++b)
+                acc[b] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
+                    a, fp4_operand(bq[b][s]), s == 0 ? c0[h] : acc[b], 4, 4, 0, kFp4ScaleTrain, 0,
                     kFp4ScaleQuery);
         }
     };
-    // The top-2 update with one tile's keys: the running top two move into
-    // this tile's frame, then take the tile's 16 keys per query block, two
-    // at a time.
-    auto tile_top2 = [&](const v16f (&acc)[QB]) {
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-            k1[qb] += 32.0f;
-            k2[qb] += 32.0f;
-        }
-#pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) insert_pair(k1[qb], k2[qb], acc[qb][r], acc[qb][r + 1]);
-        }
-    };
-    // Rows past nt (in the last tile only) take a key below every real one.
-    auto mask_tail = [&](int tile, v16f (&acc)[QB]) {
-        const int valid_rows = nt - tile * kTileRows;
-        if (valid_rows < kTileRows) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                if (8 * (r >> 2) + 4 * half + (r & 3) >= valid_rows)
-#pragma unroll
-                    for (int qb = 0; qb < QB; ++qb) acc[qb][r] = kFp4None;
-        }
-    };
     auto tile_step = [&](int tile, int buf) {
-        v16f acc[QB];
-        tile_mfma(buf, acc);
-        mask_tail(tile, acc);
-        tile_top2(acc);
+        v4f acc0[kBlocks], acc1[kBlocks];
+        sub_mfma(buf, 0, acc0);
+        sub_mfma(buf, 1, acc1);
+#pragma unroll
+        for (int b = 0; b < kBlocks; ++b) {
+            k1[b] += 32.0f;
+            k2[b] += 32.0f;
+        }
+        mask_tail(tile, 0, acc0);
+        mask_tail(tile, 1, acc1);
+#pragma unroll
+        for (int b = 0; b < kBlocks; ++b) {
+            insert_pair(k1[b], k2[b], acc0[b][0], acc0[b][1]);
+            insert_pair(k1[b], k2[b], acc0[b][2], acc0[b][3]);
+            insert_pair(k1[b], k2[b], acc1[b][0], acc1[b][1]);
+            insert_pair(k1[b], k2[b], acc1[b][2], acc1[b][3]);
+        }
     };
-
-    // Straight-line body, as in the int8 path.  (The first update moves the
-    // empty keys up by 32 too, which keeps them below -2^24.)
     for (int tile = t_begin; tile < t_end; tile += 2) {
         tile_step(tile, 0);
         stage_tile_fp4(ra, tid, tbuf[1]);
@@ -533,51 +561,57 @@ __device__ __forceinline__ void fp4_item(const uint32_t *__restrict__ query, int
         __syncthreads();
     }
 
-    // Merge the two row halves and decode
-    // key = 2^14 (|a| - d) + 2^14 - 1 - jl + 32 (tiles - 1).
+    // Every lane row holds partial results of all blocks (its rows of every
+    // tile, its words' popcounts): lane row g ends with those of block 4 t + g.
+    // Then decode key = 2^14 (|a| - d) + 2^14 - 1 - jl + 32 (tiles - 1).
     const int shift = 32 * max(t_end - t_begin - 1, 0);
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        const float o1 = __shfl_xor(k1[qb], 32);
-        const float o2 = __shfl_xor(k2[qb], 32);
-        const float b1 = fmaxf(k1[qb], o1);
-        const float b2 = fmaxf(fminf(k1[qb], o1), fmaxf(k2[qb], o2));
+    for (int t = 0; t < kSets; ++t) {
+#pragma unroll
+        for (int b = 4 * t; b < 4 * t + 2; ++b) {
+            exchange_top2<true>(k1[b], k2[b], k1[b + 2], k2[b + 2]);
+            exchange_sum<true>(na[b], na[b + 2]);
+        }
+        exchange_top2<false>(k1[4 * t], k2[4 * t], k1[4 * t + 1], k2[4 * t + 1]);
+        exchange_sum<false>(na[4 * t], na[4 * t + 1]);
         uint64_t r[2];
-        const float kk[2] = {b1, b2};
+        const float kk[2] = {k1[4 * t], k2[4 * t]};
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             if (kk[e] < -16777216.0f) {                  // a row past nt, or none
                 r[e] = kNoNeighbour;
             } else {
                 const int key = (int)kk[e] - shift;
-                const uint32_t d = (uint32_t)(na[qb] - (key >> 14));
+                const uint32_t d = (uint32_t)(na[4 * t] - (key >> 14));
                 const uint32_t j = (uint32_t)split * (uint32_t)split_rows +
                                    (uint32_t)((1 << 14) - 1 - (key & 0x3fff));
                 r[e] = ((uint64_t)d << 32) | j;
             }
         }
-        top2_pair(best[qb][0], best[qb][1], r[0], r[1]);
+        top2_pair(best[t][0], best[t][1], r[0], r[1]);
     }
 }
 
 template <int QB>
-__device__ __forceinline__ void fp4_init_best(uint64_t (&best)[QB][2])
+__device__ __forceinline__ void fp4_init_best(uint64_t (&best)[Fp4Shape<QB>::kSets][2])
 {
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) best[qb][0] = best[qb][1] = kNoNeighbour;
+    for (int t = 0; t < Fp4Shape<QB>::kSets; ++t) best[t][0] = best[t][1] = kNoNeighbour;
 }
 
-// Lanes 0..31 of each wavefront store their queries' results.
+// Every lane stores its queries' results, one per set.
 template <int QB>
-__device__ __forceinline__ void fp4_store(const uint64_t (&best)[QB][2], int nq, int nt, int qgroup,
-                                          int split, const ItemOut &out)
+__device__ __forceinline__ void fp4_store(const uint64_t (&best)[Fp4Shape<QB>::kSets][2], int nq, int nt,
+                                          int qgroup, int split, const ItemOut &out)
 {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        const int qn = qgroup * (kMfmaWaves * 32 * QB) + wave * (32 * QB) + 32 * qb + (lane & 31);
-        if (lane < 32 && qn < nq) store_pair(best[qb][0], best[qb][1], nq, nt, split, out, qn);
+    for (int t = 0; t < Fp4Shape<QB>::kSets; ++t) {
+        const int b = 4 * t + (lane >> 4);
+        const int qn = (qgroup * kMfmaWaves + wave) * Fp4Shape<QB>::kQueries + 16 * b + (lane & 15);
+        if (b < Fp4Shape<QB>::kBlocks && qn < nq)
+            store_pair(best[t][0], best[t][1], nq, nt, split, out, qn);
     }
 }
 
@@ -694,10 +728,10 @@ knn_fp4_kernel(SplitArgs a)
     __shared__ uint4 tbuf[2][kFp4TileVec];
     const ItemOut direct{nullptr, a.idx, a.dist, a.accept, a.k, a.ratio};
     const ItemOut part{a.partial, nullptr, nullptr, nullptr, 2, 0.f};
-    uint64_t best[QB][2];
-    fp4_init_best(best);
+    uint64_t best[Fp4Shape<QB>::kSets][2];
+    fp4_init_best<QB>(best);
     fp4_item<QB>(a.query, a.nq, a.train, a.nt, blockIdx.x, blockIdx.y, a.split_rows, best, tbuf);
-    fp4_store(best, a.nq, a.nt, blockIdx.x, blockIdx.y, a.nsplit == 1 ? direct : part);
+    fp4_store<QB>(best, a.nq, a.nt, blockIdx.x, blockIdx.y, a.nsplit == 1 ? direct : part);
 }
 
 __global__ __launch_bounds__(256) void knn_popcount_kernel(SplitArgs a)
@@ -845,13 +879,13 @@ __device__ __forceinline__ void batch_loop(const uint32_t *__restrict__ query,
         if constexpr (kKind == BatchKind::kMfmaFp4) {
             // The pair's whole train range in ranges of at most 2^14 rows
             // (the MXFP4 keys' index field), merged in registers.
-            uint64_t best[QB][2];
-            fp4_init_best(best);
+            uint64_t best[Fp4Shape<QB>::kSets][2];
+            fp4_init_best<QB>(best);
             const int ranges = max(1, (nt + (int)kFp4MaxSplitRows - 1) / (int)kFp4MaxSplitRows);
             for (int r = 0; r < ranges; ++r)
                 fp4_item<QB>(q, (int)e.nq, t, nt, qgroup, r, (int)kFp4MaxSplitRows, best,
                              reinterpret_cast<uint4 (*)[kFp4TileVec]>(tbuf));
-            fp4_store(best, (int)e.nq, nt, qgroup, 0, out);
+            fp4_store<QB>(best, (int)e.nq, nt, qgroup, 0, out);
         } else {
             const int split_rows = max(kTileRows, (nt + kTileRows - 1) / kTileRows * kTileRows);
             if constexpr (kKind == BatchKind::kMfmaI8)

@@ -199,3 +199,31 @@ def test_split_counts_that_fill_the_last_round(torch_cuda, lat, nq, nt, path):
     assert np.array_equal(idx.cpu().numpy()[sel], wi)
     assert np.array_equal(dist.cpu().numpy()[sel], wd)
     assert np.array_equal(acc.cpu().numpy()[sel], wa)
+
+
+@pytest.mark.parametrize("blocks", [2, 3])
+@pytest.mark.parametrize("nq,nt", [(15, 15), (16, 16), (17, 17), (63, 31), (97, 47), (256, 48),
+                                   (257, 49), (384, 63), (385, 65), (700, 16_385)])
+def test_fp4_block_edges(torch_cuda, lat, nq, nt, blocks):
+    """Query counts around the 16-query blocks, the wavefronts and the groups, and train counts
+    around the 16-row subtiles and the last tile of a split, with distances 0 and 512 present;
+    single and batched, both query block counts."""
+    from paper_1609_03986_amd.binding import Tuning, pair_table
+    g = np.random.default_rng(nq * 7919 + nt)
+    Q, T = synth.random_descriptors(g, nq), synth.random_descriptors(g, nt)
+    Q[0], Q[-1] = 0, 0xffffffff
+    T[0], T[-1] = 0xffffffff, 0
+    T[nt // 2] = Q[nq // 2]
+    dq, dt = to_dev(torch_cuda, Q), to_dev(torch_cuda, T)
+    before = lat.get_tuning()
+    try:
+        lat.set_tuning(Tuning.from_dict(dict(before.to_dict(), fp4_query_blocks=blocks)))
+        for k in (1, 2):
+            want = oracle.knn(Q, T, k=k, ratio=0.8)
+            check(torch_cuda, lat, Q, T, k=k, paths=("fp4",))
+            got = lat.knn_batch(dq, dt, pair_table([(0, nq, 0, nt, 0)]), nq, k=k, ratio=0.8,
+                                path="fp4")
+            for a, b in zip(got, want):
+                assert np.array_equal(a.cpu().numpy(), b)
+    finally:
+        lat.set_tuning(before)
