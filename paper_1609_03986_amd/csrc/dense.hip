@@ -249,7 +249,7 @@ dense_extract_kernel(const uint8_t *__restrict__ img, int height, int width, int
 }
 
 // ---------------------------------------------------------------------------
-// Dense matching on the MXFP4 matrix cores (v_mfma_scale_f32_16x16x128_f8f6f4).
+// Dense matching on the FP4 matrix cores (v_mfma_f32_16x16x128_f8f6f4).
 //
 // A wavefront owns 4 x 16 query pixels (4 columns, 16 rows) as four blocks of
 // 4 x 4, and a workgroup of four wavefronts 16 x 16.  A block of 16 queries
@@ -265,17 +265,17 @@ dense_extract_kernel(const uint8_t *__restrict__ img, int height, int width, int
 // Operands (fp4.h).  A: train pixels, lane l = 16 g + m holds words 4 g ..
 // 4 g + 3 of tile row m (one ds_read_b128 of packed bits, expanded in
 // registers), word 4 g + s in step s.  B: queries, lane l holds the same words
-// of query n = l % 16, as +-1 / c with block scale 2^10.  The f32 sum is
-// 2^10 (|a| - d), exact.
+// of query n = l % 16, as +-1 / c.  The f32 sum is |a| - d, exact.  (No block
+// scales: the instruction without them issues in half the time.)
 //
 // Keys.  Output lane 16 g + n, register r is train row 4 g + r of the tile
-// against query n.  The accumulator starts at 2^19 + a constant - p for position
-// p of the quad, or at -2^25 where p lies outside the query's own (2 R + 1)^2
-// window, and the block's best two move up by the positions of a quad when the
-// next one starts, so a key ends as 2^19 + 2^10 (|a| - d) + 1023 - p for
+// against query n.  The accumulator starts at 512 + (a constant - p) / 1024 for
+// position p of the quad, or at -2^15 where p lies outside the query's own
+// (2 R + 1)^2 window, and the block's best two move up by the positions of a quad
+// when the next one starts, so a key ends as 512 + |a| - d + (1023 - p) / 1024 for
 // position p of the S x S region (larger is better: smaller distance, then
-// lower raster index) or below zero: integers below 2^21, exact in f32, whose
-// bit patterns order like the signed integers they are compared as.  Only a
+// lower raster index) or below zero: multiples of 1/1024 below 2^11, exact in f32,
+// whose bit patterns order like the signed integers they are compared as.  Only a
 // block's first and last quads hold rows outside a query's window, so three
 // kinds of start values, kept in registers over the workgroup's tiles, do for
 // all of them.  Train pixels outside the grid are masked after the product, in
@@ -286,19 +286,16 @@ dense_extract_kernel(const uint8_t *__restrict__ img, int height, int width, int
 // the SIMDs issue vector instructions 82% of the time; the 0.30 GB of
 // descriptors, indices and distances take 48 us by themselves (radius 0).
 // Measured (2-NN, accept flags) against XOR and popcount over the same staged
-// region: radius 2 99 -> 72 us, radius 4 256 -> 107 us, radius 8 1069 -> 200 us.
+// region: radius 2 99 -> 70 us, radius 4 256 -> 103 us, radius 8 1069 -> 187 us.
 // Not kept, no faster: the next tile's loads issued before this one's
 // arithmetic, bit 3 of a train nibble used in place as the sign (one
 // instruction less per word, with a per-query correction).
 
-typedef float v4f __attribute__((ext_vector_type(4)));
-
 constexpr int kMTile = 16;                               // queries per side of a workgroup
-constexpr int kWindowScaleBits = 10;
-constexpr int kWindowScaleQuery = 127 + kWindowScaleBits;   // E8M0 2^10
-constexpr int kWindowScaleTrain = 127;                      // E8M0 2^0
-constexpr float kWindowNone = -33554432.0f;                 // -2^25
-constexpr int kWindowBias = 1 << 19;                        // 2^10 * 512: keys are positive
+constexpr int kWindowPosBits = 10;                          // positions are a key's fraction
+constexpr float kWindowPos = 1.0f / (1 << kWindowPosBits);
+constexpr float kWindowNone = -32768.0f;
+constexpr float kWindowBias = 512.0f;                       // keys are positive
 
 template <int RP>
 struct WindowGeom {
@@ -319,7 +316,7 @@ struct WindowGeom {
     // Positions count down from kFirst within a quad, and a block's keys move
     // up by kQuadPos when its next quad starts.
     static constexpr int kQuadPos = 16 * kQuadTiles;
-    static constexpr int kFirst = (1 << kWindowScaleBits) - 1 - kQuadPos * (kQuadTiles - 1);
+    static constexpr int kFirst = (1 << kWindowPosBits) - 1 - kQuadPos * (kQuadTiles - 1);
     static_assert(kFirst >= kQuadPos, "positions below the distance");
     // Kinds of quads of a block: first, between, last.  Rows between are in
     // every query's window (RP - R <= 1), so those quads have the same masks.
@@ -383,7 +380,7 @@ dense_match_kernel(const uint32_t *__restrict__ query, const uint32_t *__restric
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 start[c][j][r] = (row_ok & (abs(col + r - qc - RP) <= radius))
-                                     ? (float)(kWindowBias + G::kFirst - p - r)
+                                     ? kWindowBias + (float)(G::kFirst - p - r) * kWindowPos
                                      : kWindowNone;
         }
     // LDS position of tile row m = n of the quad's tiles.
@@ -488,8 +485,8 @@ dense_match_kernel(const uint32_t *__restrict__ query, const uint32_t *__restric
 #pragma unroll
                 for (int b = 0; b < 4; ++b)
                     if (q > b && q < b + G::kQuadTiles) {
-                        k1[b] = __float_as_int(__int_as_float(k1[b]) + (float)G::kQuadPos);
-                        k2[b] = __float_as_int(__int_as_float(k2[b]) + (float)G::kQuadPos);
+                        k1[b] = __float_as_int(__int_as_float(k1[b]) + G::kQuadPos * kWindowPos);
+                        k2[b] = __float_as_int(__int_as_float(k2[b]) + G::kQuadPos * kWindowPos);
                     }
 #pragma unroll
                 for (int j = 0; j < G::kQuadTiles; ++j) {
@@ -509,10 +506,8 @@ dense_match_kernel(const uint32_t *__restrict__ query, const uint32_t *__restric
 #pragma unroll
                         for (int b = 0; b < 4; ++b) {
                             if (q < b || q >= b + G::kQuadTiles) continue;
-                            acc[b] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
-                                a, fp4_operand(bq[b][s]),
-                                s == 0 ? start[G::kind_of(q - b)][j] : acc[b], 4, 4, 0,
-                                kWindowScaleTrain, 0, kWindowScaleQuery);
+                            acc[b] = fp4_mfma(a, fp4_operand(bq[b][s]),
+                                              s == 0 ? start[G::kind_of(q - b)][j] : acc[b]);
                         }
                     }
                     if constexpr (decltype(at_border)::value) {
@@ -568,10 +563,10 @@ dense_match_kernel(const uint32_t *__restrict__ query, const uint32_t *__restric
                     d_out = 513;
                     return;
                 }
-                const int key = (int)__int_as_float(bits);
+                const int key = (int)(__int_as_float(bits) * (1 << kWindowPosBits));
                 const int p = 1023 - (key & 1023);              // of the S x S region
                 i_out = ((int)qy + p / G::kS - qr - RP) * gw + (int)qx + p % G::kS - qc - RP;
-                d_out = na[0] + 512 - (key >> kWindowScaleBits);
+                d_out = na[0] + 512 - (key >> kWindowPosBits);
             };
             int32_t i1, d1, i2, d2;
             decode(k1[0], i1, d1);
@@ -594,7 +589,7 @@ dense_match_kernel(const uint32_t *__restrict__ query, const uint32_t *__restric
 // Dense matching at radius 0 and 1: XOR and popcount, one query per lane.  At
 // most 9 candidates per query do not pay for expanding train and query bits
 // into matrix operands (1920 x 1080, 2-NN with accept flags: radius 0 48 us
-// against 54 us, radius 1 64 us against 72 us, radius 2 99 us against 72 us).
+// against 54 us, radius 1 64 us against 70 us, radius 2 99 us against 70 us).
 
 constexpr int kPopcountRadius = 1;
 

@@ -349,24 +349,24 @@ __device__ __forceinline__ void top2_pair(uint64_t &a1, uint64_t &a2, uint64_t c
 }
 
 // ---------------------------------------------------------------------------
-// MXFP4 matcher.  Same staging as the int8 path, on the block-scaled FP4
-// matrix instruction v_mfma_scale_f32_16x16x128_f8f6f4 (K = 128 per
-// instruction, twice the int8 rate on gfx950).
+// FP4 matcher (LATCH_PATH_MFMA_FP4).  Same staging as the int8 path, on the FP4
+// matrix instruction v_mfma_f32_16x16x128_f8f6f4 (K = 128 per instruction, twice
+// the int8 rate on gfx950).
 //
 // Operands.  FP4 (e2m1) holds 0 (0x0), +-0.5 (0x1 / 0x9), +-1 (0x2 / 0xa)
 // and +-2 (0x4 / 0xc) exactly.  A train bit enters as 0 or c (c = 0.5, 1 or
-// 2 by its place in the fragment, below) with block scale 2^0, and the query
-// bit it meets as +1 / c or -1 / c (set / clear) with block scale 2^14, so
-// each product is 0 or +-2^14 and the f32 sum over K = 512 is 2^14 s with
-// s = |a| - Hamming(a, b) as in the int8 path, exact (|2^14 s| <= 2^23).
+// 2 by its place in the fragment, below), and the query bit it meets as
+// +1 / c or -1 / c (set / clear), so each product is 0 or +-1 and the f32 sum
+// over K = 512 is s = |a| - Hamming(a, b) as in the int8 path, exact.
 //
-// Keys.  For tile row m the accumulator starts at c_m = 2^14 - 1 - m, so it
-// ends at 2^14 s + c_m; the running top-2 of a lane is kept in the frame of
-// the current tile and moved up by 32 when the next tile starts, so a key
-// from split-local row jl = 32 t + m ends as 2^14 s + 2^14 - 1 - jl + 32 (T - 1)
-// after T tiles (T <= 512): integers below 2^24 in magnitude, exact in f32.
-// For a fixed query the largest key is the smallest (distance, index).  Rows
-// past nt (last tile only) take -2^25 instead, below every real key,
+// Keys.  In units of 2^-14: for tile row m the accumulator starts at
+// c_m = 2^14 - 1 - m, so it ends at 2^14 s + c_m; the running top-2 of a lane is
+// kept in the frame of the current tile and moved up by 32 when the next tile
+// starts, so a key from split-local row jl = 32 t + m ends as
+// 2^14 s + 2^14 - 1 - jl + 32 (T - 1) after T tiles (T <= 512): integers below
+// 2^24 in magnitude, exact in f32.  For a fixed query the largest key is the
+// smallest (distance, index).  Rows past nt (last tile only) take -2048 (before
+// the scaling) instead, below every real key,
 // which also marks "no neighbour".  Top-2 selection takes the keys two at a
 // time: v_med3_f32, v_max3_f32 and v_max_f32 per two pairs.
 //
@@ -383,8 +383,7 @@ __device__ __forceinline__ void top2_pair(uint64_t &a1, uint64_t &a2, uint64_t c
 // Bound: the matrix cores, and through their power the clock.  On random bits
 // this instruction alone sustains 9.15 PFLOP/s and the 32x32x64 one, which
 // moves twice the accumulator registers per product, 7.55 PFLOP/s; the
-// matcher reaches 6.6 PFLOP/s at 8000 x 1,000,000 (matrix cores busy 70% of the
-// cycles at about 2.0 GHz), since four lane rows select from every block and
+// matcher reaches 7.0 PFLOP/s at 8000 x 1,000,000, since four lane rows select from every block and
 // the selection (12 VALU instructions per 8 MFMAs) shares the issue slots.
 //
 // Tile shape.  A wavefront holds 2 QB blocks of 16 queries (QB = 2 or 3, from
@@ -395,19 +394,16 @@ __device__ __forceinline__ void top2_pair(uint64_t &a1, uint64_t &a2, uint64_t c
 // products come before their selection; a hand-written software pipeline that
 // selected the previous subtile between MFMAs was slower (1370 us), and so was
 // a frame of 64 rows, whose start values take the batched kernel's last
-// registers.  Measured, 32x32x64 -> 16x16x128: 8000 x 1,000,000 1370 -> 1246 us,
-// 20,000 x 20,000 83.2 -> 76.1 us, 15 pairs of 20,000 x 20,000 in one batch
-// 1309 -> 1170 us; QB = 2 is about 5% slower where it pads as little.
+// registers.  Measured, 32x32x64 with block scales -> 16x16x128 with -> without:
+// 8000 x 1,000,000 1359 -> 1231 -> 1176 us, 9973 x 10007 27.4 -> 24.3 -> 23.9 us;
+// QB = 2 is about 5% slower where it pads as little.
 // ---------------------------------------------------------------------------
-typedef float v4f __attribute__((ext_vector_type(4)));
-
 constexpr int kFp4Steps = 4;                          // K = 512 = 4 x 128
 constexpr int kFp4SubRows = 16;                       // train rows per MFMA
 constexpr int kFp4Subs = kTileRows / kFp4SubRows;     // subtiles per staged tile
 constexpr int kFp4TileVec = kFp4Subs * kFp4Steps * 64;    // 16-byte fragments per tile (512)
-constexpr int kFp4ScaleTrain = 127;                   // E8M0 2^0
-constexpr int kFp4ScaleQuery = 127 + 14;              // E8M0 2^14
-constexpr float kFp4None = -33554432.0f;              // -2^25
+constexpr float kFp4Row = 1.0f / (1 << 14);           // a row's step in a key
+constexpr float kFp4None = -2048.0f;                  // below every key
 
 // A wavefront's queries with QB (2 or 3): blocks of 16, and sets of four
 // blocks whose results meet one lane row each.
@@ -502,7 +498,7 @@ __device__ __forceinline__ void fp4_item(const uint32_t *__restrict__ query, int
 #pragma unroll
     for (int h = 0; h < kFp4Subs; ++h)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) c0[h][r] = (float)((1 << 14) - 1 - (kFp4SubRows * h + 4 * g + r));
+        for (int r = 0; r < 4; ++r) c0[h][r] = (float)((1 << 14) - 1 - (kFp4SubRows * h + 4 * g + r)) * kFp4Row;
 
     __syncthreads();       // the staging buffers may still be read for a previous range
     if (t_begin < t_end) stage_tile_fp4(ld0, tid, tbuf[0]);
@@ -525,9 +521,7 @@ __device__ __forceinline__ void fp4_item(const uint32_t *__restrict__ query, int
             const v8i a = fp4_operand(tbuf[buf][(h * kFp4Steps + s) * 64 + lane]);
 #pragma unroll
             for (int b = 0; b < kBlocks; ++b)
-                acc[b] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
-                    a, fp4_operand(bq[b][s]), s == 0 ? c0[h] : acc[b], 4, 4, 0, kFp4ScaleTrain, 0,
-                    kFp4ScaleQuery);
+                acc[b] = fp4_mfma(a, fp4_operand(bq[b][s]), s == 0 ? c0[h] : acc[b]);
         }
     };
     auto tile_step = [&](int tile, int buf) {
@@ -536,8 +530,8 @@ __device__ __forceinline__ void fp4_item(const uint32_t *__restrict__ query, int
         sub_mfma(buf, 1, acc1);
 #pragma unroll
         for (int b = 0; b < kBlocks; ++b) {
-            k1[b] += 32.0f;
-            k2[b] += 32.0f;
+            k1[b] += kTileRows * kFp4Row;
+            k2[b] += kTileRows * kFp4Row;
         }
         mask_tail(tile, 0, acc0);
         mask_tail(tile, 1, acc1);
@@ -578,10 +572,10 @@ __device__ __forceinline__ void fp4_item(const uint32_t *__restrict__ query, int
         const float kk[2] = {k1[4 * t], k2[4 * t]};
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-            if (kk[e] < -16777216.0f) {                  // a row past nt, or none
+            if (kk[e] < kFp4None / 2) {                  // a row past nt, or none
                 r[e] = kNoNeighbour;
             } else {
-                const int key = (int)kk[e] - shift;
+                const int key = (int)(kk[e] * (1 << 14)) - shift;
                 const uint32_t d = (uint32_t)(na[4 * t] - (key >> 14));
                 const uint32_t j = (uint32_t)split * (uint32_t)split_rows +
                                    (uint32_t)((1 << 14) - 1 - (key & 0x3fff));
