@@ -159,8 +159,11 @@ void latch_destroy(latch_handle h);
  *     The split count depends on nq, nt, the path (LATCH_PATH_AUTO resolved
  *     by the handle's current tuning table) and the tuning's workgroup
  *     targets, so query after latch_set_tuning.
- *   hamming_knn_batch_workspace_size: the pair table's per-pair state and
- *     the work-item list of the persistent matcher.
+ *   hamming_knn_batch_workspace_size: the pair table's per-pair state, the
+ *     work-unit list of the persistent matcher, and room for up to 2048
+ *     query groups whose train rows are divided over workgroups (at most
+ *     6.1 KB each; with less, down to 16 bytes per pair and 4 per 256 output
+ *     rows and pair, the batch runs undivided).
  *   latch_detect_workspace_size: survivor masks, counts and row offsets of
  *     an image of height x width.
  *   latch_extract_batch_workspace_size: a latch_create handle orders a batch
@@ -369,8 +372,8 @@ typedef struct {
  * with nt > 2^21 - 32, is skipped and sets LATCH_FLAG_BAD_PAIR.  Pairs'
  * output ranges should not overlap (they are written concurrently).  k,
  * ratio and path as for hamming_knn.  Uses the handle's workspace
- * (hamming_knn_batch_workspace_size; LATCH_EWORKSPACE if the handle holds
- * less).
+ * (hamming_knn_batch_workspace_size; with less, the undivided batch's part of
+ * it, and LATCH_EWORKSPACE if the handle does not hold that either).
  */
 int hamming_knn_batch(latch_handle h, const uint32_t *query_dev, int64_t query_rows,
                       const uint32_t *train_dev, int64_t train_rows, const latch_pair *pairs_dev,

@@ -222,17 +222,31 @@ struct PairEntry {
 static_assert(sizeof(PairEntry) == 40, "latch_pair layout");
 
 struct PairInfo {            // per pair, computed on the device
-    int64_t item_first;
-    int32_t qgroups;
-    int32_t valid;
+    int32_t unit_first;      // its first work unit (unit = part * groups + query group)
+    int32_t groups;          // query groups, 0 for a pair that does not run
+    uint32_t parts;          // parts of its train range
+    uint32_t slot;           // more than one part: its first slot
 };
+static_assert(sizeof(PairInfo) == 16, "workspace layout");
 
 struct BatchState {          // batch header in the workspace
-    int64_t items;
-    uint32_t next_item;      // atomic work counter, reset by the setup kernel
+    int64_t units;
+    uint32_t next_unit;      // atomic work counter, reset by the setup kernel
     uint32_t pad;
 };
 
+// Query groups whose train range is divided meet in slots: two keys per query and
+// a count of finished parts.  At most kBatchMaxSlots query groups are divided, into
+// at most kBatchMaxParts parts.
+constexpr int kBatchSlotQueries = 384;           // of the largest query group
+constexpr int64_t kBatchMaxSlots = 2048;
+constexpr int kBatchMaxParts = 16;
+
+struct BatchSlots {
+    uint64_t *best;
+    uint32_t *done;
+    int count;               // 0: no pair is divided
+};
 
 struct BatchArgs {
     const uint32_t *query, *train;
@@ -242,7 +256,8 @@ struct BatchArgs {
     int64_t item_capacity;
     PairInfo *info;
     BatchState *state;
-    int32_t *item_pair;
+    int32_t *unit_pair;
+    BatchSlots slots;
     int k;
     float ratio;
     int32_t *idx, *dist;

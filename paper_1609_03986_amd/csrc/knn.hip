@@ -20,6 +20,7 @@
 // ties resolve to the lowest index because the index is part of the key.  Each (query,
 // train split) writes its best two as 64-bit (distance << 32 | index) values;
 // a merge kernel reduces over splits and applies the ratio test.
+#include <algorithm>
 #include <type_traits>
 
 #include "internal.h"
@@ -402,6 +403,7 @@ constexpr int kFp4Steps = 4;                          // K = 512 = 4 x 128
 constexpr int kFp4SubRows = 16;                       // train rows per MFMA
 constexpr int kFp4Subs = kTileRows / kFp4SubRows;     // subtiles per staged tile
 constexpr int kFp4TileVec = kFp4Subs * kFp4Steps * 64;    // 16-byte fragments per tile (512)
+constexpr int kFp4MaxTiles = (int)kFp4MaxSplitRows / kTileRows;
 constexpr float kFp4Row = 1.0f / (1 << 14);           // a row's step in a key
 constexpr float kFp4None = -2048.0f;                  // below every key
 
@@ -435,14 +437,14 @@ __device__ __forceinline__ void stage_tile_fp4(uint2 w, int tid, uint4 *__restri
     to[64] = fp4_train(w.y);
 }
 
-// One (query group, train range) of the MXFP4 matcher.  Train rows
-// split * split_rows .. + split_rows - 1 (split_rows <= 2^14); the best two
+// One (query group, train range) of the FP4 matcher.  Train tiles
+// t_begin .. t_end - 1 (at most 2^14 rows); the best two
 // (distance << 32 | index) of query n = lane % 16 of block 4 t + lane / 16 are
 // merged into best[t].
 template <int QB>
 __device__ __forceinline__ void fp4_item(const uint32_t *__restrict__ query, int nq,
                                          const uint32_t *__restrict__ train, int nt, int qgroup,
-                                         int split, int split_rows,
+                                         int t_begin, int t_end,
                                          uint64_t (&best)[Fp4Shape<QB>::kSets][2],
                                          uint4 (*tbuf)[kFp4TileVec])
 {
@@ -452,11 +454,6 @@ __device__ __forceinline__ void fp4_item(const uint32_t *__restrict__ query, int
     const int g = lane >> 4, n = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int qbase = (qgroup * kMfmaWaves + wave) * Fp4Shape<QB>::kQueries;
-
-    const int ntiles_all = (nt + kTileRows - 1) / kTileRows;
-    const int tiles_per_split = split_rows / kTileRows;
-    const int t_begin = split * tiles_per_split;
-    const int t_end = min(ntiles_all, t_begin + tiles_per_split);
 
     // Tile loads two tiles ahead of staging.
     uint2 ld0 = make_uint2(0, 0), ra = ld0, rb = ld0;
@@ -577,7 +574,7 @@ __device__ __forceinline__ void fp4_item(const uint32_t *__restrict__ query, int
             } else {
                 const int key = (int)(kk[e] * (1 << 14)) - shift;
                 const uint32_t d = (uint32_t)(na[4 * t] - (key >> 14));
-                const uint32_t j = (uint32_t)split * (uint32_t)split_rows +
+                const uint32_t j = (uint32_t)t_begin * (uint32_t)kTileRows +
                                    (uint32_t)((1 << 14) - 1 - (key & 0x3fff));
                 r[e] = ((uint64_t)d << 32) | j;
             }
@@ -724,7 +721,10 @@ knn_fp4_kernel(SplitArgs a)
     const ItemOut part{a.partial, nullptr, nullptr, nullptr, 2, 0.f};
     uint64_t best[Fp4Shape<QB>::kSets][2];
     fp4_init_best<QB>(best);
-    fp4_item<QB>(a.query, a.nq, a.train, a.nt, blockIdx.x, blockIdx.y, a.split_rows, best, tbuf);
+    const int tiles = (a.nt + kTileRows - 1) / kTileRows, per_split = a.split_rows / kTileRows;
+    const int t_begin = blockIdx.y * per_split;
+    fp4_item<QB>(a.query, a.nq, a.train, a.nt, blockIdx.x, t_begin, min(tiles, t_begin + per_split), best,
+                 tbuf);
     fp4_store<QB>(best, a.nq, a.nt, blockIdx.x, blockIdx.y, a.nsplit == 1 ? direct : part);
 }
 
@@ -738,20 +738,39 @@ __global__ __launch_bounds__(256) void knn_popcount_kernel(SplitArgs a)
 
 // ---------------------------------------------------------------------------
 // Batched matching: many (query range, train range, output range) pairs in
-// one persistent launch.  Work item = (pair, query group) over the pair's
-// whole train range, so results are final and go straight to the outputs.
-// A one-block setup kernel validates the pairs, lays their items out and
-// resets the atomic work counter (so the sequence is replayable from a HIP
-// graph without memset nodes); a fill kernel writes the item -> pair map;
-// persistent workgroups then claim items through the counter.
+// one persistent launch.  Work unit = (pair, query group, part of the pair's
+// train range); where a pair has one part, as most do, a unit's results are final
+// and go straight to the outputs.  A one-block setup kernel validates the pairs,
+// lays their units out and resets the atomic work counter (so the sequence is
+// replayable from a HIP graph without memset nodes); a fill kernel writes the
+// unit -> pair map; persistent workgroups then claim units through the counter.
 //
-// Items are laid out longest first (an item's time grows with its pair's
-// train rows): pairs go to 256 cost classes, 8 per doubling of the train
+// Units are laid out longest first (an undivided unit's time grows with its
+// pair's train rows): pairs go to 256 cost classes, 8 per doubling of the train
 // tile count, and the classes are laid out in decreasing order, so that the
-// last items claimed are the shortest and the workgroups finish together.
+// last units claimed are the shortest and the workgroups finish together.
 // The order within a class follows the atomics and does not matter: every
-// item writes its own outputs.
+// query group writes its own outputs.
+//
+// Parts (FP4 matcher).  A unit should not outlast what is left for everyone: with
+// R train tiles of work from a pair's first item on and S resident workgroups, its
+// train range is divided into parts of about R / S tiles, at least kMinPartTiles
+// (shorter ones cost more in query fragments and merging than they even out: 64, 80,
+// 96 and 128 were tried) and at most kMaxParts of them.  Long pairs among short ones and the last rounds
+// of a batch of equal pairs are divided, the rest is not.  Parts of a query group
+// meet in a slot of the workspace, two 64-bit keys per query: with k1 <= k2 the
+// part's best two, old = atomicMin(first, k1), then atomicMin(second,
+// min(k2, max(old, k1))); every k1 but the smallest is the larger of some such
+// pair once, so `second` ends as the second smallest of all.  The part that
+// arrives last writes the outputs, and no part waits for another.  Bound without
+// parts: the longest unit and the last round.  Measured, undivided -> divided, us:
+// 47 pairs of log-normal sizes around 5000 (sigma 1) 637 -> 388, 29 around 2000
+// 262 -> 110, one pair of 20,000 x 20,000 470 -> 136, 15 such pairs 1130 -> 979, 63
+// 3911 -> 3715.  Parts of R / 2 S, 3 R / 4 S and 3 R / 2 S were up to 10% slower.
 // ---------------------------------------------------------------------------
+constexpr int kMinPartTiles = 96;
+constexpr int kMaxParts = kBatchMaxParts;
+
 __device__ __forceinline__ bool pair_ok(const PairEntry &e, int64_t query_rows, int64_t train_rows,
                                         int64_t out_rows)
 {
@@ -772,72 +791,129 @@ __device__ __forceinline__ int cost_class(int64_t nt)
     return 255 - min(255, 8 * (31 - lz) + (int)frac);
 }
 
+// Inclusive scan of 256 values in LDS: within the wavefronts, then over their totals.
+__device__ __forceinline__ void scan256(unsigned long long *v, unsigned long long *totals, int tid)
+{
+    __syncthreads();
+    const int lane = tid & 63;
+    unsigned long long x = v[tid];
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned long long y = __shfl_up(x, off);
+        if (lane >= off) x += y;
+    }
+    if (lane == 63) totals[tid >> 6] = x;
+    __syncthreads();
+    for (int w = 0; w < tid >> 6; ++w) x += totals[w];
+    v[tid] = x;
+    __syncthreads();
+}
+
+// resident: workgroups that run at once; slots: query groups that may be divided.
 __global__ __launch_bounds__(256) void knn_batch_setup_kernel(
     const PairEntry *__restrict__ pairs, int n_pairs, int64_t query_rows, int64_t train_rows,
-    int64_t out_rows, int64_t item_capacity, int group, PairInfo *__restrict__ info,
-    BatchState *__restrict__ st, uint32_t *__restrict__ flags)
+    int64_t out_rows, int64_t item_capacity, int group, int resident, int slots,
+    PairInfo *__restrict__ info, BatchState *__restrict__ st, uint32_t *__restrict__ flags)
 {
-    __shared__ unsigned long long classes[256];
-    __shared__ int bad_s;
+    __shared__ unsigned long long classes[256], works[256], totals[4];
+    __shared__ int bad_s, slots_s;
     const int tid = threadIdx.x;
     classes[tid] = 0;
-    if (tid == 0) bad_s = 0;
+    works[tid] = 0;
+    if (tid == 0) bad_s = slots_s = 0;
     __syncthreads();
-    // Items per class; each pair's rank in its class goes to info[p].item_first.
+    auto groups_of = [&](const PairEntry &e) {
+        return pair_ok(e, query_rows, train_rows, out_rows) ? (e.nq + group - 1) / group : 0;
+    };
+    auto tiles_of = [](const PairEntry &e) { return (int)((e.nt + kTileRows - 1) / kTileRows); };
+    // Items (pair, query group) and their train tiles per class; each pair's rank in
+    // its class goes to info[p].unit_first.
     bool bad = false;
     for (int p = tid; p < n_pairs; p += 256) {
         const PairEntry e = pairs[p];
-        const bool ok = pair_ok(e, query_rows, train_rows, out_rows);
-        bad |= !ok;
-        const unsigned long long groups = ok ? (unsigned long long)((e.nq + group - 1) / group) : 0ull;
-        info[p].item_first = (int64_t)atomicAdd(&classes[cost_class(e.nt)], groups);
+        bad |= !pair_ok(e, query_rows, train_rows, out_rows);
+        const unsigned long long groups = (unsigned long long)groups_of(e);
+        const int c = cost_class(e.nt);
+        info[p].unit_first = (int32_t)atomicAdd(&classes[c], groups);
+        if (groups) atomicAdd(&works[c], groups * (unsigned long long)tiles_of(e));
     }
     if (bad) atomicOr(&bad_s, 1);
-    __syncthreads();
-    // Inclusive scan of the 256 class totals (Hillis-Steele); class c's
-    // items start at the exclusive prefix.
-    for (int off = 1; off < 256; off <<= 1) {
-        const unsigned long long v = tid >= off ? classes[tid - off] : 0ull;
-        __syncthreads();
-        classes[tid] += v;
-        __syncthreads();
-    }
-    const int64_t total = (int64_t)classes[255];
-    // The item map holds item_capacity entries, enough for every batch whose
-    // pairs' output ranges do not overlap; a batch that needs more is not run.
-    const bool overflow = total > item_capacity;
+    scan256(classes, totals, tid);
+    scan256(works, totals, tid);
+    // The map holds item_capacity items, enough for every batch whose pairs'
+    // output ranges do not overlap; a batch that needs more is not run.
+    const bool overflow = (int64_t)classes[255] > item_capacity;
+    // Parts and slots.
+    const unsigned long long all_work = works[255];
     for (int p = tid; p < n_pairs; p += 256) {
         const PairEntry e = pairs[p];
-        const bool ok = pair_ok(e, query_rows, train_rows, out_rows);
-        const int c = cost_class(e.nt);
-        const int64_t groups = ok && !overflow ? (e.nq + group - 1) / group : 0;
-        info[p].item_first += (int64_t)(c > 0 ? classes[c - 1] : 0ull);
-        info[p].qgroups = (int32_t)groups;
-        info[p].valid = ok && !overflow;
+        const int64_t groups = overflow ? 0 : groups_of(e);
+        uint32_t parts = 1, slot = 0;
+        if (groups > 0 && groups <= slots) {
+            const int c = cost_class(e.nt), tiles = tiles_of(e);
+            // Work from this pair on: its class's remaining items and later classes.
+            const unsigned long long in_class = classes[c] - (c > 0 ? classes[c - 1] : 0ull);
+            const unsigned long long left = all_work - works[c] +
+                                            (in_class - (uint32_t)info[p].unit_first) * tiles;
+            const int chunk = (int)max((unsigned long long)kMinPartTiles,
+                                       min(left / (uint32_t)resident, 1ull << 20));
+            parts = (uint32_t)min(kMaxParts, (tiles + chunk - 1) / chunk);
+            if (parts > 1) {
+                const int per_part = (tiles + (int)parts - 1) / (int)parts;
+                parts = (uint32_t)((tiles + per_part - 1) / per_part);
+                slot = (uint32_t)atomicAdd(&slots_s, (int)groups);
+                if ((int64_t)slot + groups > slots) parts = 1;
+            }
+            parts = max(parts, 1u);
+        }
+        info[p].groups = (int32_t)groups;
+        info[p].parts = parts;
+        info[p].slot = parts > 1 ? slot : 0u;
+    }
+    __syncthreads();
+    // Units per class and each pair's rank among them, then the classes' starts.
+    classes[tid] = 0;
+    __syncthreads();
+    for (int p = tid; p < n_pairs; p += 256)
+        info[p].unit_first = (int32_t)atomicAdd(&classes[cost_class(pairs[p].nt)],
+                                                (unsigned long long)info[p].groups * info[p].parts);
+    scan256(classes, totals, tid);
+    for (int p = tid; p < n_pairs; p += 256) {
+        const int c = cost_class(pairs[p].nt);
+        info[p].unit_first += (int32_t)(c > 0 ? classes[c - 1] : 0ull);
     }
     if ((bad_s || overflow) && tid == 0) atomicOr(flags, kFlagBadPair);
     if (tid == 255) {
-        st->items = overflow ? 0 : total;
-        st->next_item = 0;
+        st->units = (int64_t)classes[255];
+        st->next_unit = 0;
     }
 }
 
+// The unit -> pair map, and the slots of divided pairs: no neighbours, no part done.
 __global__ __launch_bounds__(256) void knn_batch_fill_kernel(const PairInfo *__restrict__ info,
                                                              int n_pairs,
-                                                             int32_t *__restrict__ item_pair)
+                                                             int32_t *__restrict__ unit_pair,
+                                                             BatchSlots slots)
 {
+    const int first = 256 * blockIdx.y + threadIdx.x, step = 256 * gridDim.y;
     for (int p = blockIdx.x; p < n_pairs; p += gridDim.x) {
         const PairInfo pi = info[p];
-        for (int i = threadIdx.x; i < pi.qgroups; i += 256) item_pair[pi.item_first + i] = p;
+        const int units = pi.groups * (int)pi.parts;
+        for (int i = first; i < units; i += step) unit_pair[pi.unit_first + i] = p;
+        if (pi.parts == 1) continue;
+        ulonglong2 *best = reinterpret_cast<ulonglong2 *>(slots.best) + (size_t)pi.slot * kBatchSlotQueries;
+        for (int i = first; i < pi.groups * kBatchSlotQueries; i += step)
+            best[i] = make_ulonglong2(kNoNeighbour, kNoNeighbour);
+        for (int i = first; i < pi.groups; i += step) slots.done[pi.slot + i] = 0u;
     }
 }
 
-// Claims the next work item for the whole workgroup; -1 when none is left.
-__device__ __forceinline__ int64_t claim_item(BatchState *__restrict__ st, int *slot)
+// Claims the next work unit for the whole workgroup; -1 when none is left.
+__device__ __forceinline__ int64_t claim_unit(BatchState *__restrict__ st, int *slot)
 {
     if (threadIdx.x == 0) {
-        const uint32_t it = atomicAdd(&st->next_item, 1u);
-        *slot = (int64_t)it < st->items ? (int)it : -1;
+        const uint32_t it = atomicAdd(&st->next_unit, 1u);
+        *slot = (int64_t)it < st->units ? (int)it : -1;
     }
     __syncthreads();
     const int it = *slot;
@@ -845,89 +921,129 @@ __device__ __forceinline__ int64_t claim_item(BatchState *__restrict__ st, int *
     return it;
 }
 
+// A part's best two of each query into the query group's slot; the part that
+// arrives last writes the group's outputs.
+template <int QB>
+__device__ __forceinline__ void fp4_merge_part(const uint64_t (&best)[Fp4Shape<QB>::kSets][2], int nq,
+                                               int nt, int qgroup, uint32_t parts, uint64_t *slot,
+                                               uint32_t *done, int *last_s, const ItemOut &out)
+{
+    static_assert(kMfmaWaves * Fp4Shape<QB>::kQueries <= kBatchSlotQueries, "a group fits its slot");
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    auto each_query = [&](auto f) {
+#pragma unroll
+        for (int t = 0; t < Fp4Shape<QB>::kSets; ++t) {
+            const int b = 4 * t + (lane >> 4);
+            const int at = wave * Fp4Shape<QB>::kQueries + 16 * b + (lane & 15);
+            const int qn = qgroup * kMfmaWaves * Fp4Shape<QB>::kQueries + at;
+            if (b < Fp4Shape<QB>::kBlocks && qn < nq) f(t, slot + 2 * at, qn);
+        }
+    };
+    each_query([&](int t, uint64_t *to, int) {
+        auto *to_u = reinterpret_cast<unsigned long long *>(to);
+        const uint64_t old = atomicMin(to_u, (unsigned long long)best[t][0]);
+        atomicMin(to_u + 1, (unsigned long long)min(best[t][1], max(old, best[t][0])));
+    });
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) *last_s = atomicAdd(done, 1u) == parts - 1;
+    __syncthreads();
+    if (!*last_s) return;
+    __threadfence();
+    each_query([&](int, uint64_t *from, int qn) {
+        store_final(__hip_atomic_load(from, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                    __hip_atomic_load(from + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), nt, out, qn);
+    });
+}
+
 enum class BatchKind { kPopcount, kMfmaI8, kMfmaFp4 };
 
+// Arguments of the persistent matchers.
+struct BatchLoopArgs {
+    const uint32_t *query, *train;
+    const PairEntry *pairs;
+    int n_pairs;
+    const PairInfo *info;
+    const int32_t *unit_pair;
+    BatchState *st;
+    BatchSlots slots;
+    int k;
+    float ratio;
+    int32_t *idx, *dist;
+    uint8_t *accept;
+};
+
 template <BatchKind kKind, int QB>
-__device__ __forceinline__ void batch_loop(const uint32_t *__restrict__ query,
-                                           const uint32_t *__restrict__ train,
-                                           const PairEntry *__restrict__ pairs,
-                                           const PairInfo *__restrict__ info,
-                                           const int32_t *__restrict__ item_pair,
-                                           BatchState *__restrict__ st, int k, float ratio,
-                                           int32_t *__restrict__ idx, int32_t *__restrict__ dist,
-                                           uint8_t *__restrict__ accept, void *tbuf,
-                                           int *slot, int n_pairs)
+__device__ __forceinline__ void batch_loop(const BatchLoopArgs &a, void *tbuf, int *slot_s)
 {
     for (;;) {
-        const int item = claim_item(st, slot);
-        if (item < 0) break;
-        const int p = item_pair[item];
-        if (p < 0 || p >= n_pairs) continue;     // cannot happen for a map written by the fill kernel
-        const PairEntry e = pairs[p];
-        const int qgroup = (int)(item - info[p].item_first);
+        const int unit = claim_unit(a.st, slot_s);
+        if (unit < 0) break;
+        const int p = a.unit_pair[unit];
+        if (p < 0 || p >= a.n_pairs) continue;   // cannot happen for a map written by the fill kernel
+        const PairEntry e = a.pairs[p];
+        const int local = unit - a.info[p].unit_first;
         const int nt = (int)e.nt;
-        const ItemOut out{nullptr, idx + e.out_first * k, dist + e.out_first * k,
-                          accept ? accept + e.out_first : nullptr, k, ratio};
-        const uint32_t *q = query + (size_t)e.query_first * kWords;
-        const uint32_t *t = train + (size_t)(nt ? e.train_first : 0) * kWords;
+        const ItemOut out{nullptr, a.idx + e.out_first * a.k, a.dist + e.out_first * a.k,
+                          a.accept ? a.accept + e.out_first : nullptr, a.k, a.ratio};
+        const uint32_t *q = a.query + (size_t)e.query_first * kWords;
+        const uint32_t *t = a.train + (size_t)(nt ? e.train_first : 0) * kWords;
         if constexpr (kKind == BatchKind::kMfmaFp4) {
-            // The pair's whole train range in ranges of at most 2^14 rows
-            // (the MXFP4 keys' index field), merged in registers.
+            // The part in ranges of at most 2^14 rows (the keys' index field),
+            // merged in registers.
+            const int groups = a.info[p].groups, parts = (int)a.info[p].parts;
+            const int part = parts > 1 ? local / groups : 0, qgroup = local - part * groups;
+            const int tiles = (nt + kTileRows - 1) / kTileRows, per_part = (tiles + parts - 1) / parts;
+            const int t_end = min(tiles, (part + 1) * per_part);
             uint64_t best[Fp4Shape<QB>::kSets][2];
             fp4_init_best<QB>(best);
-            const int ranges = max(1, (nt + (int)kFp4MaxSplitRows - 1) / (int)kFp4MaxSplitRows);
-            for (int r = 0; r < ranges; ++r)
-                fp4_item<QB>(q, (int)e.nq, t, nt, qgroup, r, (int)kFp4MaxSplitRows, best,
+            int from = part * per_part;
+            do {
+                fp4_item<QB>(q, (int)e.nq, t, nt, qgroup, from, min(t_end, from + kFp4MaxTiles), best,
                              reinterpret_cast<uint4 (*)[kFp4TileVec]>(tbuf));
-            fp4_store<QB>(best, (int)e.nq, nt, qgroup, 0, out);
+                from += kFp4MaxTiles;
+            } while (from < t_end);
+            if (parts == 1) {
+                fp4_store<QB>(best, (int)e.nq, nt, qgroup, 0, out);
+            } else {
+                const uint32_t slot = a.info[p].slot + (uint32_t)qgroup;
+                fp4_merge_part<QB>(best, (int)e.nq, nt, qgroup, (uint32_t)parts,
+                                   a.slots.best + (size_t)slot * kBatchSlotQueries * 2,
+                                   a.slots.done + slot, slot_s + 1, out);
+            }
         } else {
             const int split_rows = max(kTileRows, (nt + kTileRows - 1) / kTileRows * kTileRows);
             if constexpr (kKind == BatchKind::kMfmaI8)
-                mfma_item(q, (int)e.nq, t, nt, qgroup, 0, split_rows, out,
+                mfma_item(q, (int)e.nq, t, nt, local, 0, split_rows, out,
                           reinterpret_cast<v4i (*)[kTileVec]>(tbuf));
             else
-                popcount_item(q, (int)e.nq, t, nt, qgroup, 0, split_rows, out);
+                popcount_item(q, (int)e.nq, t, nt, local, 0, split_rows, out);
         }
     }
 }
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void
-knn_batch_mfma_kernel(const uint32_t *__restrict__ query, const uint32_t *__restrict__ train,
-                      const PairEntry *__restrict__ pairs, int n_pairs,
-                      const PairInfo *__restrict__ info,
-                      const int32_t *__restrict__ item_pair, BatchState *__restrict__ st, int k,
-                      float ratio, int32_t *__restrict__ idx, int32_t *__restrict__ dist,
-                      uint8_t *__restrict__ accept)
+knn_batch_mfma_kernel(BatchLoopArgs a)
 {
     __shared__ v4i tbuf[2][kTileVec];
-    __shared__ int slot;
-    batch_loop<BatchKind::kMfmaI8, kQueryBlocks>(query, train, pairs, info, item_pair, st, k, ratio,
-                                                 idx, dist, accept, tbuf, &slot, n_pairs);
+    __shared__ int slot[1];
+    batch_loop<BatchKind::kMfmaI8, kQueryBlocks>(a, tbuf, slot);
 }
 
 template <int QB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void
-knn_batch_fp4_kernel(const uint32_t *__restrict__ query, const uint32_t *__restrict__ train,
-                     const PairEntry *__restrict__ pairs, int n_pairs,
-                     const PairInfo *__restrict__ info, const int32_t *__restrict__ item_pair,
-                     BatchState *__restrict__ st, int k, float ratio, int32_t *__restrict__ idx,
-                     int32_t *__restrict__ dist, uint8_t *__restrict__ accept)
+knn_batch_fp4_kernel(BatchLoopArgs a)
 {
     __shared__ uint4 tbuf[2][kFp4TileVec];
-    __shared__ int slot;
-    batch_loop<BatchKind::kMfmaFp4, QB>(query, train, pairs, info, item_pair, st, k, ratio, idx,
-                                        dist, accept, tbuf, &slot, n_pairs);
+    __shared__ int slot[2];
+    batch_loop<BatchKind::kMfmaFp4, QB>(a, tbuf, slot);
 }
 
-__global__ __launch_bounds__(256) void knn_batch_popcount_kernel(
-    const uint32_t *__restrict__ query, const uint32_t *__restrict__ train,
-    const PairEntry *__restrict__ pairs, int n_pairs, const PairInfo *__restrict__ info,
-    const int32_t *__restrict__ item_pair, BatchState *__restrict__ st, int k, float ratio,
-    int32_t *__restrict__ idx, int32_t *__restrict__ dist, uint8_t *__restrict__ accept)
+__global__ __launch_bounds__(256) void knn_batch_popcount_kernel(BatchLoopArgs a)
 {
-    __shared__ int slot;
-    batch_loop<BatchKind::kPopcount, 1>(query, train, pairs, info, item_pair, st, k, ratio, idx,
-                                        dist, accept, nullptr, &slot, n_pairs);
+    __shared__ int slot[1];
+    batch_loop<BatchKind::kPopcount, 1>(a, nullptr, slot);
 }
 
 }  // namespace
@@ -967,33 +1083,30 @@ hipError_t launch_knn_merge(const KnnSplitArgs &a, hipStream_t stream)
 
 hipError_t launch_knn_batch(const BatchArgs &a, hipStream_t stream)
 {
+    const bool fp4 = a.kind == SplitKernel::kMfmaFp4;
+    // Two workgroups of the FP4 matcher fit a CU.
     hipLaunchKernelGGL(knn_batch_setup_kernel, dim3(1), dim3(256), 0, stream, a.pairs, a.n_pairs,
                        a.query_rows, a.train_rows, a.out_rows, a.item_capacity,
-                       queries_per_group(a.kind, a.shape), a.info, a.state, a.flags);
+                       queries_per_group(a.kind, a.shape), 2 * a.num_cus, fp4 ? a.slots.count : 0,
+                       a.info, a.state, a.flags);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int fill_blocks = a.n_pairs < 4096 ? a.n_pairs : 4096;
-    hipLaunchKernelGGL(knn_batch_fill_kernel, dim3(fill_blocks), dim3(256), 0, stream, a.info,
-                       a.n_pairs, a.item_pair);
+    const int fill_slices = std::max(1, std::min(16, 512 / a.n_pairs));
+    hipLaunchKernelGGL(knn_batch_fill_kernel, dim3(fill_blocks, fill_slices), dim3(256), 0, stream, a.info,
+                       a.n_pairs, a.unit_pair, a.slots);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    const int blocks =
-        a.num_cus * (a.kind == SplitKernel::kPopcount ? 8 : a.shape.batch_groups_per_cu);
+    const dim3 blocks(a.num_cus * (a.kind == SplitKernel::kPopcount ? 8 : a.shape.batch_groups_per_cu));
+    const BatchLoopArgs k{a.query, a.train, a.pairs, a.n_pairs, a.info, a.unit_pair, a.state, a.slots,
+                          a.k, a.ratio, a.idx, a.dist, a.accept};
     if (a.kind == SplitKernel::kMfmaI8)
-        hipLaunchKernelGGL(knn_batch_mfma_kernel, dim3(blocks), dim3(256), 0, stream, a.query,
-                           a.train, a.pairs, a.n_pairs, a.info, a.item_pair, a.state, a.k, a.ratio,
-                           a.idx, a.dist, a.accept);
-    else if (a.kind == SplitKernel::kMfmaFp4 && a.shape.fp4_query_blocks == 3)
-        hipLaunchKernelGGL(knn_batch_fp4_kernel<3>, dim3(blocks), dim3(256), 0, stream, a.query,
-                           a.train, a.pairs, a.n_pairs, a.info, a.item_pair, a.state, a.k, a.ratio,
-                           a.idx, a.dist, a.accept);
-    else if (a.kind == SplitKernel::kMfmaFp4)
-        hipLaunchKernelGGL(knn_batch_fp4_kernel<2>, dim3(blocks), dim3(256), 0, stream, a.query,
-                           a.train, a.pairs, a.n_pairs, a.info, a.item_pair, a.state, a.k, a.ratio,
-                           a.idx, a.dist, a.accept);
+        hipLaunchKernelGGL(knn_batch_mfma_kernel, blocks, dim3(256), 0, stream, k);
+    else if (fp4 && a.shape.fp4_query_blocks == 3)
+        hipLaunchKernelGGL(knn_batch_fp4_kernel<3>, blocks, dim3(256), 0, stream, k);
+    else if (fp4)
+        hipLaunchKernelGGL(knn_batch_fp4_kernel<2>, blocks, dim3(256), 0, stream, k);
     else
-        hipLaunchKernelGGL(knn_batch_popcount_kernel, dim3(blocks), dim3(256), 0, stream, a.query,
-                           a.train, a.pairs, a.n_pairs, a.info, a.item_pair, a.state, a.k, a.ratio,
-                           a.idx, a.dist, a.accept);
+        hipLaunchKernelGGL(knn_batch_popcount_kernel, blocks, dim3(256), 0, stream, k);
     return hipGetLastError();
 }
 

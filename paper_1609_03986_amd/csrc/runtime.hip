@@ -542,21 +542,37 @@ DetectLayout detect_layout(int height, int width)
     return l;
 }
 
-size_t batch_workspace_bytes(int n_pairs, int64_t out_rows)
+// Workspace of a batched matching: the pairs' state, the header and the unit map
+// (`base` bytes), then what dividing train ranges needs: more map entries, counts and
+// keys of the slots.
+struct BatchLayout {
+    int64_t item_capacity;
+    int64_t slots;
+    size_t info_bytes, base, map_bytes, done_bytes, total;
+};
+
+BatchLayout batch_layout(int n_pairs, int64_t out_rows)
 {
-    const int64_t item_capacity = out_rows / 256 + n_pairs + 1;
-    return align_up((size_t)n_pairs * sizeof(PairInfo), 256) + 256 +
-           align_up((size_t)item_capacity * sizeof(int32_t), 256);
+    BatchLayout l;
+    l.item_capacity = out_rows / 256 + n_pairs + 1;
+    l.slots = std::min(l.item_capacity, kBatchMaxSlots);
+    l.info_bytes = align_up((size_t)n_pairs * sizeof(PairInfo), 256);
+    l.base = l.info_bytes + 256 + align_up((size_t)l.item_capacity * sizeof(int32_t), 256);
+    l.map_bytes = align_up((size_t)(l.item_capacity + l.slots * (kBatchMaxParts - 1)) * sizeof(int32_t), 256);
+    l.done_bytes = align_up((size_t)l.slots * sizeof(uint32_t), 256);
+    l.total = l.info_bytes + 256 + l.map_bytes + l.done_bytes +
+              (size_t)l.slots * kBatchSlotQueries * 2 * sizeof(uint64_t);
+    return l;
 }
 
 // Arguments of the batched matcher with its workspace at `ws`
-// (batch_workspace_bytes bytes).
-BatchArgs batch_args(latch_handle h, uint8_t *ws, const uint32_t *query_dev, int64_t query_rows,
+// of ws_bytes.  A workspace without room for slots divides no train range.
+BatchArgs batch_args(latch_handle h, uint8_t *ws, size_t ws_bytes, const uint32_t *query_dev, int64_t query_rows,
                      const uint32_t *train_dev, int64_t train_rows, const latch_pair *pairs_dev,
                      int n_pairs, int k, float ratio, int32_t *idx_dev, int32_t *dist_dev,
                      uint8_t *accept_dev, int64_t out_rows, int path)
 {
-    const size_t info_bytes = align_up((size_t)n_pairs * sizeof(PairInfo), 256);
+    const BatchLayout l = batch_layout(n_pairs, out_rows);
     BatchArgs a;
     a.query = query_dev;
     a.train = train_dev;
@@ -565,10 +581,15 @@ BatchArgs batch_args(latch_handle h, uint8_t *ws, const uint32_t *query_dev, int
     a.out_rows = out_rows;
     a.pairs = reinterpret_cast<const PairEntry *>(pairs_dev);
     a.n_pairs = n_pairs;
-    a.item_capacity = out_rows / 256 + n_pairs + 1;
+    a.item_capacity = l.item_capacity;
     a.info = reinterpret_cast<PairInfo *>(ws);
-    a.state = reinterpret_cast<BatchState *>(ws + info_bytes);
-    a.item_pair = reinterpret_cast<int32_t *>(ws + info_bytes + 256);
+    a.state = reinterpret_cast<BatchState *>(ws + l.info_bytes);
+    uint8_t *map = ws + l.info_bytes + 256;
+    a.unit_pair = reinterpret_cast<int32_t *>(map);
+    a.slots = BatchSlots{nullptr, nullptr, 0};
+    if (ws_bytes >= l.total)
+        a.slots = BatchSlots{reinterpret_cast<uint64_t *>(map + l.map_bytes + l.done_bytes),
+                             reinterpret_cast<uint32_t *>(map + l.map_bytes), (int)l.slots};
     a.k = k;
     a.ratio = ratio;
     a.idx = idx_dev;
@@ -1132,7 +1153,7 @@ int hamming_knn_batch_workspace_size(latch_handle h, int n_pairs, int64_t out_ro
     if (!h || !bytes) return LATCH_EINVAL;
     if (n_pairs < 0 || out_rows < 0 || out_rows > LATCH_MAX_ROWS)
         return fail(h, LATCH_EINVAL, "negative or too large batch size");
-    *bytes = n_pairs == 0 ? 0 : batch_workspace_bytes(n_pairs, out_rows);
+    *bytes = n_pairs == 0 ? 0 : batch_layout(n_pairs, out_rows).total;
     return LATCH_OK;
 }
 
@@ -1263,9 +1284,9 @@ int hamming_knn_batch(latch_handle h, const uint32_t *query_dev, int64_t query_r
         return fail(h, LATCH_EINVAL, "null buffer");
     if (path == LATCH_PATH_AUTO) path = h->tuning.batch_path;
 
-    const int rc = check_workspace(h, batch_workspace_bytes(n_pairs, out_rows), "hamming_knn_batch");
+    const int rc = check_workspace(h, batch_layout(n_pairs, out_rows).base, "hamming_knn_batch");
     if (rc != LATCH_OK) return rc;
-    const BatchArgs a = batch_args(h, h->ws, query_dev, query_rows, train_dev, train_rows,
+    const BatchArgs a = batch_args(h, h->ws, h->ws_bytes, query_dev, query_rows, train_dev, train_rows,
                                    pairs_dev, n_pairs, k, ratio, idx_dev, dist_dev, accept_dev,
                                    out_rows, path);
     const char *name = a.kind == SplitKernel::kPopcount  ? "knn_batch_popcount"
@@ -1296,7 +1317,7 @@ int latch_plan_create(latch_handle h, const latch_plan_desc *d, latch_plan *out)
     latch_plan_ctx *p = new latch_plan_ctx();
     p->h = h;
     // Plan workspace: the matcher's state, then the extraction's order.
-    const size_t knn_bytes = align_up(batch_workspace_bytes(d->n_pairs, d->out_rows), 256);
+    const size_t knn_bytes = align_up(batch_layout(d->n_pairs, d->out_rows).total, 256);
     const size_t order_bytes = extract_batch_workspace(h, d->n_images, d->max_kps);
     hipError_t e = hipMalloc((void **)&p->ws, knn_bytes + order_bytes);
     if (e != hipSuccess) {
@@ -1305,7 +1326,7 @@ int latch_plan_create(latch_handle h, const latch_plan_desc *d, latch_plan *out)
     }
     const ExtractArgs ea = batch_extract_args(h, d->images, d->n_images, d->image_id, d->kps,
                                               d->max_kps, d->n_kps, d->desc);
-    const BatchArgs ba = batch_args(h, p->ws, d->desc, d->max_kps, d->desc, d->max_kps, d->pairs,
+    const BatchArgs ba = batch_args(h, p->ws, knn_bytes, d->desc, d->max_kps, d->desc, d->max_kps, d->pairs,
                                     d->n_pairs, d->k, d->ratio, d->idx, d->dist, d->accept,
                                     d->out_rows,
                                     d->path == LATCH_PATH_AUTO ? h->tuning.batch_path : d->path);

@@ -187,3 +187,71 @@ def test_many_pairs_across_cost_classes(torch_cuda, lat, path):
             assert np.array_equal(dist[of + sel], wd), (i, q, t)
             assert np.array_equal(acc[of + sel], wa), (i, q, t)
     assert lat.check_errors(clear=True) == 0
+
+
+# Train rows around the least part of a divided train range (96 tiles of 32 rows) and its
+# multiples, several 2^14-row ranges within a part, and short pairs beside long ones.
+DIVIDED = [[(300, 3072), (5, 3073)], [(385, 6145), (1, 3104)], [(768, 9_000), (384, 33), (0, 9_000)],
+           [(40, 300_000)], [(1500, 20_000), (100, 0), (100, 1), (3000, 500), (64, 40_001)]]
+
+
+@pytest.mark.parametrize("p", [0.5, 0.01])
+@pytest.mark.parametrize("blocks", [2, 3])
+@pytest.mark.parametrize("sizes", DIVIDED)
+def test_divided_train_ranges(torch_cuda, lat, triplets, sizes, blocks, p):
+    """Pairs whose train rows several workgroups share: parts merge to the oracle's results, with
+    random and heavily tied descriptors, on every call, and with a workspace that holds no room
+    for dividing."""
+    import ctypes
+    from paper_1609_03986_amd.binding import Latch, Tuning, load_library, pair_table
+    g = np.random.default_rng(sum(a * 31 + b for a, b in sizes))
+    Q = synth.random_descriptors(g, sum(a for a, _ in sizes), p)
+    T = synth.random_descriptors(g, max(b for _, b in sizes) + 7, p)
+    rows, first = [], 0
+    for i, (nq, nt) in enumerate(sizes):
+        rows.append((first, nq, i, nt, first))
+        first += nq
+    want = [oracle.knn(Q[a:a + nq], T[t:t + nt], k=2, ratio=0.8) for a, nq, t, nt, _ in rows]
+    dq, dt, table = dev(torch_cuda, Q), dev(torch_cuda, T), pair_table(rows)
+    small = Latch(triplets)
+    try:
+        # The pairs' state (16 bytes each), the header and the unit map alone.
+        up = lambda n: (n + 255) // 256 * 256
+        small.reserve(up(16 * len(rows)) + 256 + up(4 * (len(Q) // 256 + len(rows) + 1)))
+        for L in (lat, small):
+            L.set_tuning(Tuning.from_dict(dict(L.get_tuning().to_dict(), fp4_query_blocks=blocks)))
+            for k in (1, 2, 2):
+                if L is lat:
+                    got = L.knn_batch(dq, dt, table, len(Q), k=k, ratio=0.8, path="fp4")
+                else:
+                    new = lambda *s, t=torch_cuda.int32: torch_cuda.zeros(s, dtype=t, device="cuda")
+                    got = new(len(Q), k), new(len(Q), k), new(len(Q), t=torch_cuda.uint8)
+                    ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+                    assert load_library().hamming_knn_batch(
+                        L.h, ptr(dq), len(Q), ptr(dt), len(T), ptr(table), len(rows), k, 0.8,
+                        ptr(got[0]), ptr(got[1]), ptr(got[2]), len(Q), 3,
+                        ctypes.c_void_p(torch_cuda.cuda.current_stream().cuda_stream)) == 0
+                got = [a.cpu().numpy() for a in got]
+                for (a, nq, _, _, _), (wi, wd, wa) in zip(rows, want):
+                    assert np.array_equal(got[0][a:a + nq], wi[:, :k])
+                    assert np.array_equal(got[1][a:a + nq], wd[:, :k])
+                    assert np.array_equal(got[2][a:a + nq], wa)
+    finally:
+        lat.set_tuning(Tuning.from_dict(dict(lat.get_tuning().to_dict(), fp4_query_blocks=3)))
+        small.close()
+
+
+def test_more_divided_groups_than_slots(torch_cuda, lat):
+    """Pairs enough for twice the slots of divided query groups: some are divided, the others not."""
+    from paper_1609_03986_amd.binding import pair_table
+    g = np.random.default_rng(77)
+    n, nq, nt = 40, 40_000, 3200
+    D = dev(torch_cuda, synth.random_descriptors(g, n * nq // 16))
+    D = torch_cuda.cat([D ^ i for i in range(16)])
+    rows = [(i * nq, nq, i * nq, nt, i * nq) for i in range(n)]
+    idx, dist, acc = lat.knn_batch(D, D, pair_table(rows), n * nq, path="fp4")
+    for i in range(n):
+        part = slice(i * nq, (i + 1) * nq)
+        want = lat.knn(D[part], D[i * nq:i * nq + nt], path="mfma")
+        for got, w in zip((idx[part], dist[part], acc[part]), want):
+            assert bool((got == w).all()), i
