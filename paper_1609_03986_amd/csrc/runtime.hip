@@ -565,6 +565,8 @@ BatchLayout batch_layout(int n_pairs, int64_t out_rows)
     return l;
 }
 
+size_t batch_workspace_bytes(int n_pairs, int64_t out_rows) { return batch_layout(n_pairs, out_rows).total; }
+
 // Arguments of the batched matcher with its workspace at `ws`
 // of ws_bytes.  A workspace without room for slots divides no train range.
 BatchArgs batch_args(latch_handle h, uint8_t *ws, size_t ws_bytes, const uint32_t *query_dev, int64_t query_rows,
@@ -1153,7 +1155,7 @@ int hamming_knn_batch_workspace_size(latch_handle h, int n_pairs, int64_t out_ro
     if (!h || !bytes) return LATCH_EINVAL;
     if (n_pairs < 0 || out_rows < 0 || out_rows > LATCH_MAX_ROWS)
         return fail(h, LATCH_EINVAL, "negative or too large batch size");
-    *bytes = n_pairs == 0 ? 0 : batch_layout(n_pairs, out_rows).total;
+    *bytes = n_pairs == 0 ? 0 : batch_workspace_bytes(n_pairs, out_rows);
     return LATCH_OK;
 }
 
@@ -1317,7 +1319,7 @@ int latch_plan_create(latch_handle h, const latch_plan_desc *d, latch_plan *out)
     latch_plan_ctx *p = new latch_plan_ctx();
     p->h = h;
     // Plan workspace: the matcher's state, then the extraction's order.
-    const size_t knn_bytes = align_up(batch_layout(d->n_pairs, d->out_rows).total, 256);
+    const size_t knn_bytes = align_up(batch_workspace_bytes(d->n_pairs, d->out_rows), 256);
     const size_t order_bytes = extract_batch_workspace(h, d->n_images, d->max_kps);
     hipError_t e = hipMalloc((void **)&p->ws, knn_bytes + order_bytes);
     if (e != hipSuccess) {
