@@ -453,7 +453,8 @@ int latch_rotation_table(int16_t *cos_q14, int16_t *sin_q14);
  * and the split planner of hamming_knn aims at the given number of
  * workgroups per CU.  The MXFP4 matchers hold 2 or 3 blocks of 32 queries
  * per wavefront (a workgroup of 4 wavefronts takes 256 or 384 queries
- * against each staged train tile); the
+ * against each staged train tile); with 3, hamming_knn takes 2 for calls that
+ * are faster with 2.  The
  * batched MFMA matchers run the given number of persistent workgroups per
  * CU.  Defaults: MFMA_FP4 everywhere (batches too), 2 (both MFMA paths) and
  * 8 (popcount) workgroups per CU, 3 query blocks, 2 batched

@@ -181,6 +181,7 @@ struct KnnPlan {
     int64_t nq, nt;
     int64_t split_rows;       // multiple of kTileRows, <= kMaxSplitRows
     int nsplit;
+    int query_blocks;         // 32-query blocks per wavefront of the FP4 kernel
 };
 
 // Single-pair matching over train splits.  With one split the results are
@@ -192,7 +193,7 @@ enum class SplitKernel { kMfmaI8, kMfmaFp4, kPopcount };
 // Tile shapes and selection variants of the MFMA matchers (from the tuning
 // table; none changes results).
 struct KnnShape {
-    int fp4_query_blocks = 3;       // 32-query blocks per wavefront of the MXFP4 kernels: 2 or 3
+    int fp4_query_blocks = 3;       // most 32-query blocks per wavefront of the FP4 kernels: 2 or 3
     int batch_groups_per_cu = 2;    // persistent workgroups per CU of the batched MFMA matchers
 };
 
@@ -212,7 +213,7 @@ constexpr int kMfmaWaves = 4;                    // wavefronts per MFMA matcher 
 
 hipError_t launch_knn_split(const KnnSplitArgs &a, SplitKernel which, hipStream_t stream);
 // Queries per workgroup of a matcher kernel (the unit of query groups and batch items).
-int queries_per_group(SplitKernel which, const KnnShape &shape);
+int queries_per_group(SplitKernel which, int fp4_query_blocks);
 hipError_t launch_knn_merge(const KnnSplitArgs &a, hipStream_t stream);
 
 // Layout-compatible with latch_pair of the C ABI.

@@ -671,9 +671,12 @@ __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int m)
     return ((uint64_t)hi << 32) | lo;
 }
 
-// Four lanes per query: lane g of a query reads splits g, g + 4, ... (all
-// loads in flight), then two shuffle rounds combine the four top-2 pairs.
-constexpr int kMergeLanes = 4;
+// Sixteen lanes per query: lane g of a query reads splits g, g + 16, ... (four
+// loads in flight), then four shuffle rounds combine the top-2 pairs.  Bound by the
+// latency of those loads: 500 x 1,000,000 with 256 splits took 109.6 us in all with
+// 4 lanes, 101.9 with 8, 99.5 with 16 and 98.9 with 32; 2000 x 2000 7.4 us with 16
+// and 8.2 with 4.
+constexpr int kMergeLanes = 16;
 
 __global__ __launch_bounds__(256) void knn_merge_kernel(const uint64_t *__restrict__ partial, int nq,
                                                         int nsplit, int nt, int k, float ratio,
@@ -1048,21 +1051,21 @@ __global__ __launch_bounds__(256) void knn_batch_popcount_kernel(BatchLoopArgs a
 
 }  // namespace
 
-int queries_per_group(SplitKernel which, const KnnShape &shape)
+int queries_per_group(SplitKernel which, int fp4_query_blocks)
 {
-    return which == SplitKernel::kMfmaFp4 ? kMfmaWaves * 32 * shape.fp4_query_blocks : 256;
+    return which == SplitKernel::kMfmaFp4 ? kMfmaWaves * 32 * fp4_query_blocks : 256;
 }
 
 hipError_t launch_knn_split(const KnnSplitArgs &a, SplitKernel which, hipStream_t stream)
 {
     const SplitArgs k{a.query, a.train, (int)a.plan.nq, (int)a.plan.nt, (int)a.plan.split_rows,
                       a.plan.nsplit, a.partial, a.k, a.ratio, a.idx, a.dist, a.accept};
-    const int64_t group = queries_per_group(which, a.shape);
+    const int64_t group = queries_per_group(which, a.plan.query_blocks);
     const int64_t qgroups = (a.plan.nq + group - 1) / group;
     const dim3 grid((unsigned)qgroups, (unsigned)a.plan.nsplit);
     if (which == SplitKernel::kMfmaI8)
         hipLaunchKernelGGL(knn_mfma_kernel, grid, dim3(kMfmaThreads), 0, stream, k);
-    else if (which == SplitKernel::kMfmaFp4 && a.shape.fp4_query_blocks == 3)
+    else if (which == SplitKernel::kMfmaFp4 && a.plan.query_blocks == 3)
         hipLaunchKernelGGL(knn_fp4_kernel<3>, grid, dim3(kMfmaThreads), 0, stream, k);
     else if (which == SplitKernel::kMfmaFp4)
         hipLaunchKernelGGL(knn_fp4_kernel<2>, grid, dim3(kMfmaThreads), 0, stream, k);
@@ -1087,7 +1090,7 @@ hipError_t launch_knn_batch(const BatchArgs &a, hipStream_t stream)
     // Two workgroups of the FP4 matcher fit a CU.
     hipLaunchKernelGGL(knn_batch_setup_kernel, dim3(1), dim3(256), 0, stream, a.pairs, a.n_pairs,
                        a.query_rows, a.train_rows, a.out_rows, a.item_capacity,
-                       queries_per_group(a.kind, a.shape), 2 * a.num_cus, fp4 ? a.slots.count : 0,
+                       queries_per_group(a.kind, a.shape.fp4_query_blocks), 2 * a.num_cus, fp4 ? a.slots.count : 0,
                        a.info, a.state, a.flags);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -445,10 +445,13 @@ SplitKernel split_kernel(int path)
                                          : SplitKernel::kPopcount;
 }
 
-// Split plan of a single-pair call.  The base choice fills the GPU's
-// workgroup slots once (slots / query groups splits), raised to what the
-// split-local index needs and capped at 8 tiles per split.  Work items
-// (query group, split) then run in rounds of `slots`, each costing about its
+// Split plan of a single-pair call for query groups of `group`.  The base
+// choice fills the GPU's workgroup slots once (slots / query groups splits),
+// raised to what the split-local index needs and capped at 2 tiles per split (up
+// to 8 tiles, one split: the second launch takes longer than the tiles).  With caps
+// of 8 and 4 tiles a call of 2000 x 2000 took 10.0 and 8.0 us instead of 7.4,
+// 1000 x 1000 10.2 and 8.0 instead of 6.8.  Work items (query group, split) then
+// run in rounds of `slots`, each costing about its
 // split's tiles; when the base count leaves the last round partly empty (the
 // index raised it, or the query groups alone exceed the slots), a larger
 // count can spread the same tiles over fuller rounds.  Over counts up to 4x
@@ -456,35 +459,31 @@ SplitKernel split_kernel(int path)
 // smallest count whose rounds x tiles per split is within 2% of the least is
 // taken (more splits also mean more merge work and partials), unless the
 // base itself is.
-KnnPlan plan_knn(int64_t nq, int64_t nt, int path, int num_cus, const latch_tuning &tune,
-                 size_t partial_cap)
+struct SplitCount {
+    int64_t tiles_per_split, rounds;
+    int nsplit;
+};
+
+SplitCount count_splits(int64_t nq, int64_t tiles, int64_t group, int64_t slots, int64_t max_rows,
+                        size_t partial_cap)
 {
-    KnnPlan p;
-    p.nq = nq;
-    p.nt = nt;
-    const int64_t tiles = (nt + kTileRows - 1) / kTileRows;
-    if (tiles == 0) {
-        p.nsplit = 1;
-        p.split_rows = kTileRows;
-        return p;
-    }
-    const int64_t group = queries_per_group(split_kernel(path), knn_shape(tune));
     const int64_t qgroups = (nq + group - 1) / group;
-    const int64_t slots = (int64_t)num_cus * (path == LATCH_PATH_POPCOUNT ? tune.popcount_groups_per_cu
-                                                                        : tune.mfma_groups_per_cu);
     int64_t nsplit = qgroups >= slots ? 1 : slots / qgroups;
-    const int64_t max_by_size = (tiles + 7) / 8;
+    const int64_t max_by_size = tiles <= 8 ? 1 : (tiles + 1) / 2;
     if (nsplit > max_by_size) nsplit = max_by_size;
+    const int64_t max_by_cap = (int64_t)(partial_cap / ((size_t)nq * 2 * sizeof(uint64_t)));
+    if (nsplit > max_by_cap) nsplit = max_by_cap;
     if (nsplit < 1) nsplit = 1;
-    const int64_t max_rows = path == LATCH_PATH_MFMA_FP4 ? kFp4MaxSplitRows : kMaxSplitRows;
-    const int64_t min_by_index = (nt + max_rows - 1) / max_rows;
+    const int64_t max_tiles = max_rows / kTileRows;
+    const int64_t min_by_index = (tiles + max_tiles - 1) / max_tiles;
     if (nsplit < min_by_index) nsplit = min_by_index;
     if (nsplit > kMaxSplits) nsplit = kMaxSplits;
     auto tiles_per = [&](int64_t n) { return (tiles + n - 1) / n; };
-    auto cost = [&](int64_t n) {                       // rounds x tiles per split
+    auto rounds = [&](int64_t n) {
         const int64_t tps = tiles_per(n), used = (tiles + tps - 1) / tps;
-        return (qgroups * used + slots - 1) / slots * tps;
+        return (qgroups * used + slots - 1) / slots;
     };
+    auto cost = [&](int64_t n) { return rounds(n) * tiles_per(n); };
     const int64_t n_hi = std::min({(int64_t)kMaxSplits, std::max(nsplit, max_by_size), 4 * nsplit + 8,
                                    nsplit + 512});
     const int64_t base_cost = cost(nsplit);
@@ -500,9 +499,46 @@ KnnPlan plan_knn(int64_t nq, int64_t nt, int path, int num_cus, const latch_tuni
                 nsplit = n;
                 break;
             }
-    const int64_t tiles_per_split = tiles_per(nsplit);
-    p.split_rows = tiles_per_split * kTileRows;
-    p.nsplit = (int)((tiles + tiles_per_split - 1) / tiles_per_split);
+    const int64_t tps = tiles_per(nsplit);
+    return {tps, rounds(nsplit), (int)((tiles + tps - 1) / tps)};
+}
+
+// The plan: splits, and for the FP4 path the 32-query blocks per wavefront, 2 or (if
+// the tuning has 3) 3.  A tile costs a workgroup of 2 blocks 0.78 of one of 3
+// (more per query: its staging and fragment reads serve fewer), and a work item
+// starts and ends in the time of 5 and 6.5 such tiles: fewer blocks win where the
+// splits are short or where 3 pad the queries more.  With 3 and 2 blocks: 1000 x 1000
+// 7.5 and 6.8 us, 4000 x 3000 11.0 and 9.7, 500 x 1,000,000 126 and 99, 1200 x 200,000
+// 56.0 and 53.6, 9973 x 10007 24.6 and 25.6, 3000 x 10,000 13.1 and 13.1.
+KnnPlan plan_knn(int64_t nq, int64_t nt, int path, int num_cus, const latch_tuning &tune,
+                 size_t partial_cap)
+{
+    KnnPlan p;
+    p.nq = nq;
+    p.nt = nt;
+    p.query_blocks = tune.fp4_query_blocks;
+    p.nsplit = 1;
+    p.split_rows = kTileRows;
+    const int64_t tiles = (nt + kTileRows - 1) / kTileRows;
+    if (tiles == 0) return p;
+    const SplitKernel which = split_kernel(path);
+    const bool fp4 = which == SplitKernel::kMfmaFp4;
+    const int64_t slots = (int64_t)num_cus * (path == LATCH_PATH_POPCOUNT ? tune.popcount_groups_per_cu
+                                                                        : tune.mfma_groups_per_cu);
+    const int64_t max_rows = fp4 ? kFp4MaxSplitRows : kMaxSplitRows;
+    auto splits = [&](int blocks) {
+        return count_splits(nq, tiles, queries_per_group(which, blocks), slots, max_rows, partial_cap);
+    };
+    SplitCount c = splits(p.query_blocks);
+    if (fp4 && p.query_blocks == 3) {
+        const SplitCount two = splits(2);
+        if (two.rounds * (78 * two.tiles_per_split + 500) < c.rounds * (100 * c.tiles_per_split + 650)) {
+            c = two;
+            p.query_blocks = 2;
+        }
+    }
+    p.split_rows = c.tiles_per_split * kTileRows;
+    p.nsplit = c.nsplit;
     return p;
 }
 

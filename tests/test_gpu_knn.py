@@ -227,3 +227,15 @@ def test_fp4_block_edges(torch_cuda, lat, nq, nt, blocks):
                 assert np.array_equal(a.cpu().numpy(), b)
     finally:
         lat.set_tuning(before)
+
+
+@pytest.mark.parametrize("nq,nt", [(1, 256), (1, 257), (300, 288), (257, 289), (500, 2049), (100, 16_390),
+                                   (1025, 4097), (385, 40_000), (4000, 65)])
+def test_short_splits(torch_cuda, lat, nq, nt):
+    """The last size of one split and the first of two-tile splits, counts of splits around the
+    merge's lanes and loads in flight, and query counts on both sides of the block choice."""
+    g = np.random.default_rng(nq * 65_537 + nt)
+    Q, T = synth.random_descriptors(g, nq, 0.2), synth.random_descriptors(g, nt, 0.2)
+    T[-1], T[nt // 2] = T[0], Q[0]
+    for k in (1, 2):
+        check(torch_cuda, lat, Q, T, k=k)
