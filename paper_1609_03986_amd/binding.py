@@ -18,6 +18,7 @@ import ctypes
 import os
 
 import numpy as np
+import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "liblatch.so")
@@ -64,10 +65,9 @@ def load_library():
     if not os.path.exists(LIB_PATH):
         raise ImportError("liblatch.so is not built; run `python -m paper_1609_03986_amd.build`")
     # torch ships its own libamdhip64 with the same soname as the system one.
-    # Loading torch first makes the dynamic linker bind liblatch.so to that
+    # Loading torch first (above) makes the dynamic linker bind liblatch.so to that
     # runtime; loading liblatch.so first would put two HIP runtimes in the
     # process, and the second one to initialise finds no GPU.
-    import torch  # noqa: F401
     lib = ctypes.CDLL(LIB_PATH)
     P, I, I64, F = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64, ctypes.c_float
     lib.latch_create.argtypes = [ctypes.POINTER(P), P]
@@ -181,21 +181,24 @@ def latch_reserve(h, nbytes=0):
 
 
 def _stream_ptr(stream):
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    """The given stream, or the current one of the current device (its raw pointer:
+    torch.cuda.current_stream() builds a Stream object for it, 2.8 us against 0.3)."""
+    if stream is not None:
+        return stream.cuda_stream
+    if not torch.cuda.is_initialized():
+        torch.cuda.init()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dev(t, dtype, name):
-    import torch
+    """The address of a contiguous device tensor of this type."""
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError("%s must be a CUDA (HIP) tensor" % name)
     if t.dtype != dtype:
         raise TypeError("%s must have dtype %s, got %s" % (name, dtype, t.dtype))
     if not t.is_contiguous() and not (name == "img" and t.stride(1) == 1):
         raise ValueError("%s must be contiguous" % name)
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def latch_rotation_table():
@@ -248,7 +251,6 @@ def latch_extract(h, img, kps, desc=None, stream=None):
     img: uint8 [H, W] CUDA tensor; a row stride larger than W is passed as the pitch.
     kps: float32 [n, 4] CUDA tensor of (x, y, angle_deg, scale).
     """
-    import torch
     if img.dim() != 2:
         raise ValueError("img must be 2-D")
     if kps.dim() != 2 or kps.shape[1] != 4:
@@ -269,7 +271,6 @@ def latch_extract(h, img, kps, desc=None, stream=None):
 def latch_extract_dense(h, img, x0, y0, gw, gh, desc=None, stream=None):
     """Descriptors of every pixel of [x0, x0 + gw) x [y0, y0 + gh), upright at
     scale 1: int32 [gh * gw, 16] (uint32 words), raster order."""
-    import torch
     if img.dim() != 2:
         raise ValueError("img must be 2-D")
     if desc is None:
@@ -285,7 +286,6 @@ def latch_extract_dense(h, img, x0, y0, gw, gh, desc=None, stream=None):
 def hamming_knn_window(h, query, train, gw, gh, radius, k=2, ratio=0.8, stream=None):
     """Dense matching of two gh x gw descriptor grids within +/- radius:
     (idx int32 [n, k] raster indices, dist int32 [n, k], accept uint8 [n])."""
-    import torch
     n = gh * gw
     dev = query.device
     idx = torch.empty((n, k), dtype=torch.int32, device=dev)
@@ -305,7 +305,6 @@ def latch_detect(h, img, threshold, max_kps, kps=None, n_kps=None, image_id=None
     """FAST-9 keypoints with orientation, appended to kps after the n_kps[0]
     already there; returns (kps float32 [max_kps, 4], n_kps int64 [1] on the
     device: the new total, which may exceed max_kps).  A new n_kps starts at 0."""
-    import torch
     if img.dim() != 2:
         raise ValueError("img must be 2-D")
     dev = img.device
@@ -329,7 +328,6 @@ IMAGE_ENTRY_BYTES = 24
 def image_table(images):
     """Pack device images (uint8 CUDA tensors [H, W], row stride = pitch) into a
     latch_image table: a uint8 CUDA tensor of n * 24 bytes."""
-    import torch
     rows = np.zeros((len(images), 3), np.int64)
     for i, img in enumerate(images):
         if img.dim() != 2 or img.dtype != torch.uint8 or not img.is_cuda or img.stride(1) != 1:
@@ -344,7 +342,6 @@ def image_table(images):
 def latch_extract_batch(h, table, n_images, image_id, kps, desc=None, n_kps=None, stream=None):
     """Batched extraction.  table: from image_table(); image_id: int32 [n] CUDA;
     kps: float32 [n, 4] CUDA; n_kps: optional int64 [1] CUDA tensor (count to process)."""
-    import torch
     n = kps.shape[0]
     if image_id.shape[0] != n:
         raise ValueError("image_id must have one entry per keypoint")
@@ -364,7 +361,6 @@ def hamming_knn(h, query, train, k=2, ratio=0.8, path="auto", idx=None, dist=Non
     """Brute-force k-NN.  query [nq, 16], train [nt, 16] int32 (uint32 bit patterns).
 
     Returns (idx int32 [nq, k], dist int32 [nq, k], accept uint8 [nq] or None)."""
-    import torch
     nq, nt = query.shape[0], train.shape[0]
     dev = query.device
     if idx is None:
@@ -388,7 +384,6 @@ def hamming_knn_noalloc(h, query, train, idx, dist, accept=None, k=2, ratio=0.8,
     """hamming_knn with its split partials in the library's static device
     scratch: the caller passes every output (idx, dist int32 [nq, k], accept
     uint8 [nq] or None) and nothing is allocated."""
-    import torch
     nq, nt = query.shape[0], train.shape[0]
     acc_ptr = _dev(accept, torch.uint8, "accept") if accept is not None else None
     tptr = _dev(train, torch.int32, "train") if nt > 0 else None
@@ -405,7 +400,6 @@ NOALLOC_SCRATCH_BYTES = 16 << 20     # LATCH_NOALLOC_SCRATCH_BYTES
 def pair_table(pairs, device="cuda"):
     """latch_pair table from rows (query_first, nq, train_first, nt, out_first):
     an int64 CUDA tensor [n, 5]."""
-    import torch
     arr = np.asarray(pairs, np.int64).reshape(-1, 5)
     return torch.from_numpy(np.ascontiguousarray(arr)).to(device)
 
@@ -414,7 +408,6 @@ def hamming_knn_batch(h, query, train, pairs, out_rows, k=2, ratio=0.8, path="au
                       dist=None, accept=None, want_accept=True, stream=None):
     """Batched k-NN over a pair table (see pair_table).  Returns (idx, dist, accept)
     with out_rows rows; rows no pair writes are left as allocated."""
-    import torch
     dev = query.device
     if idx is None:
         idx = torch.full((out_rows, k), -2, dtype=torch.int32, device=dev)
@@ -501,22 +494,21 @@ class Plan:
 
     def __init__(self, h, table, n_images, image_id, kps, desc, pairs, idx, dist, accept=None,
                  n_kps=None, k=2, ratio=0.8, path="auto"):
-        import torch
         self._keep = (table, image_id, kps, desc, pairs, idx, dist, accept, n_kps)
         d = _PlanDesc()
-        d.images = _dev(table, torch.uint8, "table").value
+        d.images = _dev(table, torch.uint8, "table")
         d.n_images = n_images
-        d.image_id = _dev(image_id, torch.int32, "image_id").value
-        d.kps = _dev(kps, torch.float32, "kps").value
-        d.n_kps = _dev(n_kps, torch.int64, "n_kps").value if n_kps is not None else None
+        d.image_id = _dev(image_id, torch.int32, "image_id")
+        d.kps = _dev(kps, torch.float32, "kps")
+        d.n_kps = _dev(n_kps, torch.int64, "n_kps") if n_kps is not None else None
         d.max_kps = kps.shape[0]
-        d.desc = _dev(desc, torch.int32, "desc").value
-        d.pairs = _dev(pairs, torch.int64, "pairs").value
+        d.desc = _dev(desc, torch.int32, "desc")
+        d.pairs = _dev(pairs, torch.int64, "pairs")
         d.n_pairs = pairs.shape[0]
         d.k, d.ratio, d.path = k, float(ratio), PATHS[path]
-        d.idx = _dev(idx, torch.int32, "idx").value
-        d.dist = _dev(dist, torch.int32, "dist").value
-        d.accept = _dev(accept, torch.uint8, "accept").value if accept is not None else None
+        d.idx = _dev(idx, torch.int32, "idx")
+        d.dist = _dev(dist, torch.int32, "dist")
+        d.accept = _dev(accept, torch.uint8, "accept") if accept is not None else None
         d.out_rows = idx.shape[0]
         self.h = h
         self.p = ctypes.c_void_p()
