@@ -758,7 +758,7 @@ __global__ __launch_bounds__(256) void knn_popcount_kernel(SplitArgs a)
 // Parts (FP4 matcher).  A unit should not outlast what is left for everyone: with
 // R train tiles of work from a pair's first item on and S resident workgroups, its
 // train range is divided into parts of about R / S tiles, at least kMinPartTiles
-// (shorter ones cost more in query fragments and merging than they even out: 64, 80,
+// (shorter ones cost more in query fragments and merging than they even out: 48, 64,
 // 96 and 128 were tried) and at most kMaxParts of them.  Long pairs among short ones and the last rounds
 // of a batch of equal pairs are divided, the rest is not.  Parts of a query group
 // meet in a slot of the workspace, two 64-bit keys per query: with k1 <= k2 the
@@ -767,11 +767,11 @@ __global__ __launch_bounds__(256) void knn_popcount_kernel(SplitArgs a)
 // pair once, so `second` ends as the second smallest of all.  The part that
 // arrives last writes the outputs, and no part waits for another.  Bound without
 // parts: the longest unit and the last round.  Measured, undivided -> divided, us:
-// 47 pairs of log-normal sizes around 5000 (sigma 1) 637 -> 388, 29 around 2000
-// 262 -> 110, one pair of 20,000 x 20,000 470 -> 136, 15 such pairs 1130 -> 979, 63
-// 3911 -> 3715.  Parts of R / 2 S, 3 R / 4 S and 3 R / 2 S were up to 10% slower.
+// 47 pairs of log-normal sizes around 5000 (sigma 1) 637 -> 327, 29 around 2000
+// 262 -> 97, one pair of 20,000 x 20,000 470 -> 116, 15 such pairs 1130 -> 934, 63
+// 3911 -> 3697.  Parts of R / 2 S, 3 R / 4 S and 3 R / 2 S were up to 10% slower.
 // ---------------------------------------------------------------------------
-constexpr int kMinPartTiles = 96;
+constexpr int kMinPartTiles = 80;
 constexpr int kMaxParts = kBatchMaxParts;
 
 __device__ __forceinline__ bool pair_ok(const PairEntry &e, int64_t query_rows, int64_t train_rows,
@@ -924,6 +924,14 @@ __device__ __forceinline__ int64_t claim_unit(BatchState *__restrict__ st, int *
     return it;
 }
 
+// Waits until this wavefront's device-scope atomic accesses have been performed.
+// All that parts exchange goes through such accesses (the minima, the count, the loads
+// of the last part), which do not stop at an XCD's own L2, so this wait, the barrier and
+// the count order them.  A device-scope fence would also write the XCD's L2 back, in
+// every wavefront of every part: 47 pairs around 5000 rows 390 us with it, 331 without,
+// one pair of 20,000 x 20,000 139 and 120 us.
+__device__ __forceinline__ void wait_device_accesses() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // A part's best two of each query into the query group's slot; the part that
 // arrives last writes the group's outputs.
 template <int QB>
@@ -948,12 +956,11 @@ __device__ __forceinline__ void fp4_merge_part(const uint64_t (&best)[Fp4Shape<Q
         const uint64_t old = atomicMin(to_u, (unsigned long long)best[t][0]);
         atomicMin(to_u + 1, (unsigned long long)min(best[t][1], max(old, best[t][0])));
     });
-    __threadfence();
+    wait_device_accesses();
     __syncthreads();
     if (threadIdx.x == 0) *last_s = atomicAdd(done, 1u) == parts - 1;
     __syncthreads();
     if (!*last_s) return;
-    __threadfence();
     each_query([&](int, uint64_t *from, int qn) {
         store_final(__hip_atomic_load(from, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
                     __hip_atomic_load(from + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), nt, out, qn);

@@ -189,9 +189,9 @@ def test_many_pairs_across_cost_classes(torch_cuda, lat, path):
     assert lat.check_errors(clear=True) == 0
 
 
-# Train rows around the least part of a divided train range (96 tiles of 32 rows) and its
+# Train rows around the least part of a divided train range (80 tiles of 32 rows) and its
 # multiples, several 2^14-row ranges within a part, and short pairs beside long ones.
-DIVIDED = [[(300, 3072), (5, 3073)], [(385, 6145), (1, 3104)], [(768, 9_000), (384, 33), (0, 9_000)],
+DIVIDED = [[(300, 2560), (5, 2561)], [(300, 3072), (5, 3073)], [(600, 5121)], [(385, 6145), (1, 3104)], [(768, 9_000), (384, 33), (0, 9_000)],
            [(40, 300_000)], [(1500, 20_000), (100, 0), (100, 1), (3000, 500), (64, 40_001)]]
 
 
