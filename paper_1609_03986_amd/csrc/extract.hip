@@ -273,21 +273,6 @@ struct TripletSums {
     __device__ __forceinline__ uint32_t bit() const { return (((ac1 - ac2) << 1) + (q2 - q1)) >> 31; }
 };
 
-// Words 4 w .. 4 w + 3 of the descriptor whose bits are in LDS, a byte each, by
-// wavefront w: lane l packs bits 4 l .. 4 l + 3 of its 128, and groups of 8 lanes
-// add their nibbles to a word.
-__device__ __forceinline__ void store_words(const uint8_t *lds, int wave, int lane, uint32_t *row)
-{
-    const uint32_t four =
-        reinterpret_cast<const uint32_t *>(lds + kBitBase + kWaveTriplets * wave)[lane & 31];
-    int word = (int)(dot4(four, 0x08040201u, 0u) << (4 * (lane & 7)));
-    word += __builtin_amdgcn_update_dpp(0, word, 0xB1, 0xF, 0xF, false);    // quad_perm [1,0,3,2]
-    word += __builtin_amdgcn_update_dpp(0, word, 0x4E, 0xF, 0xF, false);    // quad_perm [2,3,0,1]
-    word += __builtin_amdgcn_update_dpp(0, word, 0x141, 0xF, 0xF, false);   // row_half_mirror
-    if ((lane & 39) == 0)
-        uniform_words(row + 2 * kRoundsPerWave * wave)[(uint32_t)lane >> 3] = (uint32_t)word;
-}
-
 template <bool kTable>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void extract_kernel(
     ImageSource src, const float4 *__restrict__ kps, int64_t n_host, const int64_t *__restrict__ n_dev,
@@ -347,7 +332,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
             write_chain(lds, s1);
             if (tail) write_chain(lds, s2);
             __syncthreads();   // raw window complete; the previous triplets are done
-            if (pending >= 0) store_words(lds, wave, lane, desc + pending * kWords);
+            if (pending >= 0) pack_words(lds + kBitBase, wave, lane, desc + pending * kWords);
             if (tid < kCopyUnits) copy_unit(lds, tid);
             __syncthreads();   // copies complete
         }
@@ -386,7 +371,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
         pending = q;
     }
     __syncthreads();                          // the last triplets are done
-    if (pending >= 0) store_words(lds, wave, lane, desc + pending * kWords);
+    if (pending >= 0) pack_words(lds + kBitBase, wave, lane, desc + pending * kWords);
 }
 
 }  // namespace

@@ -102,7 +102,7 @@ struct ExtractArgs {
     // Weighted geometry (window 0: the default 48 x 48, 7 x 7, unit weights).
     int window = 0;
     const uint2 *wtrip_off = nullptr;   // [512] by slot: LDS byte offsets of the patches
-    const uint32_t *wunperm = nullptr;  // [256] per (wavefront, lane): slots of its two output bits
+    const uint32_t *wbit_of = nullptr;  // [512] by slot: output bits
     WeightRows weights = {};
     // Batches: keypoint index at each position of a spatial order (default
     // kernel only), or nullptr to take the keypoints as given.

@@ -96,6 +96,19 @@ __device__ __forceinline__ uint32_t dot4(uint32_t a, uint32_t b, uint32_t acc)
     return __builtin_amdgcn_udot4(a, b, acc, false);
 }
 
+// Words 4 w .. 4 w + 3 of a descriptor from its bits, a byte each, by wavefront
+// w < 4: lane l packs bits 4 l .. 4 l + 3 of its 128, and groups of 8 lanes add
+// their nibbles to a word.
+__device__ __forceinline__ void pack_words(const uint8_t *bits, int wave, int lane, uint32_t *row)
+{
+    const uint32_t four = reinterpret_cast<const uint32_t *>(bits + 128 * wave)[lane & 31];
+    int word = (int)(dot4(four, 0x08040201u, 0u) << (4 * (lane & 7)));
+    word += __builtin_amdgcn_update_dpp(0, word, 0xB1, 0xF, 0xF, false);    // quad_perm [1,0,3,2]
+    word += __builtin_amdgcn_update_dpp(0, word, 0x4E, 0xF, 0xF, false);    // quad_perm [2,3,0,1]
+    word += __builtin_amdgcn_update_dpp(0, word, 0x141, 0xF, 0xF, false);   // row_half_mirror
+    if ((lane & 39) == 0) uniform_words(row + 4 * wave)[(uint32_t)lane >> 3] = (uint32_t)word;
+}
+
 #include "xcd_range.h"
 
 // Rule steps 1-3 for one keypoint (uniform across the workgroup), with the

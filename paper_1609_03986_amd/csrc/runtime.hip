@@ -27,7 +27,7 @@ struct latch_ctx {
     // Weighted geometry (latch_create_geometry); window 0 runs the default kernel.
     int window = 0;
     uint2 *wtrip_dev = nullptr;        // [512] by slot: weighted-kernel patch offsets
-    uint32_t *wunperm_dev = nullptr;   // [256] per (wavefront, lane): slots of its two output bits
+    uint32_t *wbit_of_dev = nullptr;   // [512] by slot: output bits of the weighted kernel
     uint2 *dense_off_dev = nullptr;    // [512] in triplet order: dense-kernel texture offsets
     WeightRows weights = {};
     uint8_t *ws = nullptr;             // grow-only workspace
@@ -326,7 +326,7 @@ void assign_slots(const uint2 *toff, int n, int group, int cols, uint16_t *slot)
 }
 
 // The same for `waves` sets of per_wave (at most 256) triplets, each in the
-// slots of its own wavefront.
+// slots of its own wavefront (the host-code tests check the search in this form).
 void assign_slots(const uint2 *toff, int waves, int per_wave, int group, int cols, uint8_t *slot_of)
 {
     std::vector<uint16_t> slot(per_wave);
@@ -662,7 +662,7 @@ ExtractArgs batch_extract_args(latch_handle h, const latch_image *images_dev, in
     a.num_cus = h->num_cus;
     a.window = h->window;
     a.wtrip_off = h->wtrip_dev;
-    a.wunperm = h->wunperm_dev;
+    a.wbit_of = h->wbit_of_dev;
     a.weights = h->weights;
     return a;
 }
@@ -939,28 +939,20 @@ int latch_create_geometry(latch_handle *out, const uint8_t *triplets_host, int w
             o[k] = weighted_patch_offset(window, tr[2 * k] - patch / 2, tr[2 * k + 1] - patch / 2);
         toff[t] = make_uint2(o[0] | (o[1] << 16), o[2]);
     }
-    // Wavefront w evaluates triplets 64 w + l and 256 + 64 w + l (members l
-    // and 64 + l) in two rounds; bank-aware slots, and per lane the slots of
-    // its two output bits.
-    const int kWWaves = 4, kWPerWave = kTriplets / kWWaves;
-    auto member = [](int w, int i) { return i < 64 ? 64 * w + i : 256 + 64 * w + (i - 64); };
-    uint2 mem[kTriplets];
-    for (int w = 0; w < kWWaves; ++w)
-        for (int i = 0; i < kWPerWave; ++i) mem[kWPerWave * w + i] = toff[member(w, i)];
-    uint8_t slot_of[kTriplets];
-    assign_slots(mem, kWWaves, kWPerWave, 32, 32, slot_of);   // row reads: ds_read_b64
+    // Bank-aware slots over all triplets (row reads: ds_read_b64).
+    uint16_t slot_of[kTriplets];
+    assign_slots(toff, kTriplets, 32, 32, slot_of);
     uint2 toff_slot[kTriplets];
-    uint32_t unperm[kWWaves * 64] = {};
-    for (int w = 0; w < kWWaves; ++w)
-        for (int i = 0; i < kWPerWave; ++i) {
-            toff_slot[kWPerWave * w + slot_of[kWPerWave * w + i]] = mem[kWPerWave * w + i];
-            unperm[64 * w + (i & 63)] |= (uint32_t)slot_of[kWPerWave * w + i] << (8 * (i >> 6));
-        }
+    uint32_t bit_of[kTriplets];
+    for (int t = 0; t < kTriplets; ++t) {
+        toff_slot[slot_of[t]] = toff[t];
+        bit_of[slot_of[t]] = (uint32_t)t;
+    }
     hipError_t e;
     if ((e = hipMalloc((void **)&h->wtrip_dev, sizeof toff_slot)) == hipSuccess &&
-        (e = hipMalloc((void **)&h->wunperm_dev, sizeof unperm)) == hipSuccess) {
+        (e = hipMalloc((void **)&h->wbit_of_dev, sizeof bit_of)) == hipSuccess) {
         const Upload u[2] = {{h->wtrip_dev, toff_slot, sizeof toff_slot},
-                             {h->wunperm_dev, unperm, sizeof unperm}};
+                             {h->wbit_of_dev, bit_of, sizeof bit_of}};
         e = upload(u, 2);
     }
     if (e != hipSuccess) {
@@ -982,7 +974,7 @@ void latch_destroy(latch_handle h)
     if (h->gather_dev) (void)hipFree(h->gather_dev);
     if (h->flags_dev) (void)hipFree(h->flags_dev);
     if (h->wtrip_dev) (void)hipFree(h->wtrip_dev);
-    if (h->wunperm_dev) (void)hipFree(h->wunperm_dev);
+    if (h->wbit_of_dev) (void)hipFree(h->wbit_of_dev);
     if (h->dense_off_dev) (void)hipFree(h->dense_off_dev);
     if (h->ws) (void)hipFree(h->ws);
     release_timed(h);
@@ -1027,7 +1019,7 @@ int latch_extract(latch_handle h, const uint8_t *img_dev, int height, int width,
     a.num_cus = h->num_cus;
     a.window = h->window;
     a.wtrip_off = h->wtrip_dev;
-    a.wunperm = h->wunperm_dev;
+    a.wbit_of = h->wbit_of_dev;
     a.weights = h->weights;
     hipError_t e = timed_launch(h, "extract", stream, [&] { return run_extract(a, stream); });
     return e == hipSuccess ? LATCH_OK : hip_fail(h, e, "extract launch");

@@ -175,3 +175,29 @@ def test_plan_with_geometry_handle(torch_cuda):
             plan.close()
     finally:
         lat.close()
+
+
+@pytest.mark.parametrize("sq", [4, 64, 256, 307, 512, 1024])
+@pytest.mark.parametrize("window", [48, 64])
+def test_every_fourth_angle_bin_by_scale(torch_cuda, window, sq):
+    """Windows sampled along image rows at every fourth angle bin (all octants, exact diagonals
+    and axes) and scales with and without offsets halfway between two pixels, from an interior
+    centre, and every 64th bin at a corner (clamped)."""
+    from paper_1609_03986_amd.binding import Latch
+    torch = torch_cuda
+    g = np.random.default_rng(window * 10_000 + sq)
+    img = g.integers(0, 256, (311, 337), dtype=np.uint8)
+    kps = np.zeros((1024 + 64, 4), np.float32)
+    kps[:, 0], kps[:, 1], kps[:, 3] = 168, 155, sq / 256.0
+    kps[:1024, 2] = np.arange(1024) * (360.0 / 1024.0)
+    kps[1024:, 2] = kps[:1024:16, 2]
+    kps[1024:, :2] = 4, 300
+    trip, w = synth.triplet_table_geom(window, 8), synth.gaussian_weights(8, 2.0, 128)
+    lat = Latch(trip, window=window, patch=8, weights=w)
+    try:
+        got = lat.extract(torch.from_numpy(img).cuda(), torch.from_numpy(kps).cuda())
+        want, f = oracle.extract_geom(img, kps, trip, window, 8, w)
+        assert f == 0 and lat.check_errors(clear=True) == 0
+        assert np.array_equal(got.cpu().numpy().view(np.uint32), want)
+    finally:
+        lat.close()
