@@ -234,3 +234,33 @@ def test_plan_with_order_and_device_count(torch_cuda, triplets):
             plan.close()
     finally:
         lat.close()
+
+
+@pytest.mark.parametrize("n_images,shuffled", [(1, False), (16, True), (17, True), (64, False), (65, False),
+                                               (200, True)])
+def test_order_over_many_buckets(torch_cuda, triplets, n_images, shuffled):
+    """Bucket counts on both sides of a chunk's span and of the scan's 4096 entries, keypoints image
+    by image and shuffled: the ordered batch equals unordered parts of it."""
+    torch = torch_cuda
+    from paper_1609_03986_amd.binding import Latch, image_table
+    g = np.random.default_rng(n_images)
+    n = ORDER_MIN + 1025
+    imgs = [torch.from_numpy(g.integers(0, 256, (2048, 64), dtype=np.uint8)).cuda() for _ in range(n_images)]
+    ids = np.sort(g.integers(0, n_images, n)).astype(np.int32)
+    if shuffled:
+        g.shuffle(ids)
+    kps = np.zeros((n, 4), np.float32)
+    kps[:, 0], kps[:, 1] = g.uniform(0, 64, n), g.uniform(-3, 2051, n)
+    kps[:, 2], kps[:, 3] = g.uniform(0, 360, n), g.uniform(0.5, 2, n)
+    idt, k = torch.from_numpy(ids).cuda(), torch.from_numpy(kps).cuda()
+    table = image_table(imgs)
+    lat = Latch(triplets)
+    try:
+        got = lat.extract_batch(table, n_images, idt, k)
+        half = n // 2
+        for part in (slice(0, half), slice(half, n)):
+            want = lat.extract_batch(table, n_images, idt[part].contiguous(), k[part].contiguous())
+            assert torch.equal(got[part], want)
+        assert lat.check_errors(clear=True) == 0
+    finally:
+        lat.close()
