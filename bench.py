@@ -575,7 +575,7 @@ def main():
         "config": {"workload": WORKLOAD, "images": 64, "descriptors_per_step": total,
                    "pairs_per_step": n_pairs, "image_pairs": 63, "match_path": args.path,
                    "parallelism": "single GPU"},
-        "arithmetic": "u8 images, exact int32 patch sums; matching on exact MXFP4 MFMA "
+        "arithmetic": "u8 images, exact int32 patch sums; matching on exact FP4 MFMA "
                       "(0 / +-1 operands, f32 sums of integers < 2^24) unless the tuning "
                       "table picks int8 MFMA or popcount",
         "pairs_per_s": n_pairs / (wall / args.steps),
@@ -738,15 +738,15 @@ def dense_component(torch, lat, timer, hd):
     de_ms, dm_ms = ke["dense_extract"]["avg_ms"], km["knn_window"]["avg_ms"]
     de_ops = npx * DENSE_OPS_PER_PIXEL / (de_ms * 1e-3) / 1e12
     cand = (2 * DENSE_RADIUS + 1) ** 2
-    dm_ops = npx * cand * POPCOUNT_OPS_PER_PAIR / (dm_ms * 1e-3) / 1e12
+    dm_ops = npx * cand * MATCH_OPS_PER_PAIR / (dm_ms * 1e-3) / 1e12
     return {"image": "%dx%d, every pixel" % (W, H), "radius": DENSE_RADIUS,
             "desc_per_s": 2 * npx / (de_wall / steps), "extract_avg_ms": de_ms,
             "match_pairs_per_s": npx * cand / (dm_wall / steps), "match_avg_ms": dm_ms,
             "extract_roofline": {"bound": "alu", "achieved": de_ops, "peak": PEAK_INT_TOPS,
                                  "unit": "TFLOP/s", "frac": de_ops / PEAK_INT_TOPS,
                                  "traffic": recorded_traffic("dense_extract", "hd")},
-            "match_roofline": {"bound": "alu", "achieved": dm_ops, "peak": PEAK_INT_TOPS,
-                               "unit": "TFLOP/s", "frac": dm_ops / PEAK_INT_TOPS}}
+            "match_roofline": {"bound": "mfma", "achieved": dm_ops, "peak": PEAK_FP4_MFMA_TOPS,
+                               "unit": "TFLOP/s", "frac": dm_ops / PEAK_FP4_MFMA_TOPS}}
 
 
 def versions(torch):

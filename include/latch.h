@@ -312,7 +312,7 @@ int latch_detect(latch_handle h, const uint8_t *img_dev, int height, int width, 
  *   accept_dev: uint8[nq] or NULL: 1 iff nt >= 2 and d1 < ratio * d2, evaluated
  *              exactly (the second neighbour is always searched, also for k = 1).
  *   path:      a latch_path value; every path returns identical results.  With more
- *              than 65,535 x 16,384 train rows the MXFP4 path (whose keys hold a
+ *              than 65,535 x 16,384 train rows the FP4 path (whose keys hold a
  *              14-bit split-local index) runs the int8 MFMA kernel instead.
  * nq == 0 is a no-op.  nq and nt must be < 2^31.  The train rows are split
  * over workgroups; with more than one split a merge kernel follows and the
@@ -451,7 +451,7 @@ int latch_rotation_table(int16_t *cos_q14, int16_t *sin_q14);
  * Tuning.  LATCH_PATH_AUTO picks the matcher path from a per-handle table
  * indexed by size buckets, bucket(n) = min(7, floor(log2(max(n, 1)) / 2)),
  * and the split planner of hamming_knn aims at the given number of
- * workgroups per CU.  The MXFP4 matchers hold 2 or 3 blocks of 32 queries
+ * workgroups per CU.  The FP4 matchers hold 2 or 3 blocks of 32 queries
  * per wavefront (a workgroup of 4 wavefronts takes 256 or 384 queries
  * against each staged train tile); with 3, hamming_knn takes 2 for calls that
  * are faster with 2.  The

@@ -1,6 +1,6 @@
 """Autotuner for the matcher: picks, per (query count, train count) size
-bucket, the fastest of the int8-MFMA, MXFP4-MFMA and popcount paths, the
-path for batched matching, the MXFP4 tile shape (2 or 3 blocks of 32
+bucket, the fastest of the int8-MFMA, FP4-MFMA and popcount paths, the
+path for batched matching, the FP4 tile shape (2 or 3 blocks of 32
 queries per wavefront), the split planner's workgroups-per-CU target and the
 persistent workgroups per CU of batched matching.  It measures the library's
 own kernels (HIP events recorded by the library on its launch stream) on
@@ -117,7 +117,7 @@ def tune(lat, buckets=None, reps=5, seed=0, log=None):
         lat.set_tuning(Tuning.from_dict(t))
         return t
 
-    # MXFP4 tile shape: the split matcher at 10,000 x 10,000 plus the batched
+    # FP4 tile shape: the split matcher at 10,000 x 10,000 plus the batched
     # matcher on a batch shaped like structure from motion (64 images of
     # 20,000 descriptors, the 63 consecutive pairs; random bits).
     q, t = pool[:10000], pool[rows - 10000:] if rows >= 20000 else pool[:10000]

@@ -24,7 +24,7 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
 ]
-# The MXFP4 matcher's keys are floats that are never NaN; without this every
+# The FP4 matcher's keys are floats that are never NaN; without this every
 # maximum would quiet its operands first.
 FILE_FLAGS = {"knn.hip": ["-fno-honor-nans"]}
 _HARMLESS = "'-packed-fp32-ops' is not a recognized feature for this target"

@@ -36,7 +36,7 @@
 // distance within +/- R rows and columns (R <= 8), ties to the lower raster
 // index, ratio test as in hamming_knn.  A workgroup owns 16 x 16 queries, stages
 // the packed train descriptors around them in LDS and forms the distances on
-// the MXFP4 matrix cores.
+// the FP4 matrix cores.
 #include <algorithm>
 #include <type_traits>
 

@@ -35,10 +35,10 @@
 //
 // The paper's CUDA kernel (Sec. 3.2) spreads one descriptor over 32 warps of
 // a 1024-thread block with float32 patches in shared memory; here four 64-lane
-// wavefronts share a 19.9 KB byte window (eight per CU, eight wavefronts per
+// wavefronts share a 20.4 KB byte window (eight per CU, eight wavefronts per
 // SIMD) and synchronise twice per descriptor.
 //
-// What bounds it: no one unit.  Per keypoint the vector ALUs issue about 850
+// What bounds it: no one unit.  Per keypoint the vector ALUs issue about 940
 // instructions, the LDS is busy some 950 cycles (patch reads 82 of 96 possible
 // bank cycles per row and group, copies, window) and the texture units 1,070 at
 // scale 1 to 1,290 over scales 1 to 3.6 (a byte load costs about 12 cycles plus

@@ -208,7 +208,7 @@ struct KnnSplitArgs {
     uint8_t *accept;
 };
 
-constexpr int64_t kFp4MaxSplitRows = 1 << 14;    // MXFP4 keys hold a 14-bit split-local index
+constexpr int64_t kFp4MaxSplitRows = 1 << 14;    // FP4 keys hold a 14-bit split-local index
 constexpr int kMfmaWaves = 4;                    // wavefronts per MFMA matcher workgroup
 
 hipError_t launch_knn_split(const KnnSplitArgs &a, SplitKernel which, hipStream_t stream);

@@ -543,7 +543,7 @@ KnnPlan plan_knn(int64_t nq, int64_t nt, int path, int num_cus, const latch_tuni
 }
 
 // The split kernel a single-pair call runs: LATCH_PATH_AUTO resolved by the
-// tuning table, and the MXFP4 path, whose keys hold a 14-bit split-local
+// tuning table, and the FP4 path, whose keys hold a 14-bit split-local
 // index, replaced by the int8 one (identical results) when the train rows
 // would need more than the 65,535 splits a grid dimension allows.
 int resolve_path(latch_handle h, int path, int64_t nq, int64_t nt)

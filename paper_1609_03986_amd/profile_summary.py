@@ -14,7 +14,7 @@
         which bench.py reads for the roofline's `traffic`.
 
 A library launch is named as the library's timing events name it: the
-order's five kernels are one "extract_order" launch, and so on.
+order's four kernels are one "extract_order" launch, and so on.
 """
 import argparse
 import collections
@@ -46,6 +46,7 @@ LAUNCHES = [
     (r"^detect_emit_kernel", "detect_emit", "detect.hip"),
     (r"^dense_extract_kernel", "dense_extract", "dense.hip"),
     (r"^dense_match_kernel", "knn_window", "dense.hip"),
+    (r"^window_popcount_kernel", "knn_window", "dense.hip"),
 ]
 
 
