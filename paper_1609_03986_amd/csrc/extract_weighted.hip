@@ -16,22 +16,24 @@
 // time (grid-stride over keypoints):
 //   1. resampling rule steps 1-3 on the keypoint (uniform);
 //   2. the W x W window gathered with the rule, issued one keypoint ahead and
-//      along image rows (Positions below), written to LDS as 16-bit pixels
-//      in four copies shifted by 0..3 columns, so that the 8 pixels of any
-//      patch row start on a quadword of one copy (two ds_read_b64);
+//      along image rows (Positions below), written to a plain byte window in
+//      LDS, from which a copy pass makes four copies of 16-bit pixels shifted by
+//      0..3 columns, so that the 8 pixels of any patch row start on a quadword
+//      of one copy (two ds_read_b64);
 //   3. one triplet per thread (W = 48: two), in (wavefront, lane) slots the host
 //      chose over all triplets so that the 32-lane halves of a ds_read_b64 hit
 //      few bank conflicts; each bit goes to its triplet's place in LDS as a byte,
 //      and after the next descriptor's first barrier 8 lanes at a time pack and
 //      store the words.
 //
-// What bounds it: LDS (63% busy: patch rows and the four copies' writes), with the
-// vector ALUs at 66%, between two barriers per descriptor.  20,000 keypoints of a
+// What bounds it: LDS (patch rows) and vector issue, about two thirds busy each,
+// between two barriers per descriptor.  20,000 keypoints of a
 // 1920 x 1080 image, W = 64: in raster order with four wavefronts, 16 at a time per
 // CU, 142 us (the texture units 67% busy: a row of the window crosses up to 64 image
 // rows); along image rows 137, reads one patch row ahead 134, eight wavefronts and
-// free slots 122.  50,000 keypoints of 3840 x 2160: 387 -> 295 us; upright 125 ->
-// 108; W = 48 104 -> 96.  Rows of 72 elements: of 68 and 76, 124.
+// free slots 122, a copy pass (64 byte writes and 64 of quadwords per descriptor
+// and wavefronts in place of 256 conflicting 16-bit ones) 110.  50,000 keypoints of
+// 3840 x 2160: 387 -> 268 us; upright 125 -> 104; W = 48 104 -> 96.
 #include "internal.h"
 
 namespace latch {
@@ -49,11 +51,14 @@ struct WGeom {
     static constexpr int kWaves = kThreads / 64;
     static constexpr int kRounds = kTriplets / kThreads;         // triplets per thread
     static constexpr int kHalfW = kW / 2;
-    static constexpr int kSpare = 8;
-    static constexpr int kRowBytes = 2 * (kW + kSpare);          // 16-bit pixels
-    static constexpr int kCopyBytes = (kW + 1) * kRowBytes;      // one spare (zero) row
-    static constexpr int kBitBase = 4 * kCopyBytes;              // the descriptor's bits, a byte each
+    static constexpr int kRowBytes = 2 * (kW + 4);               // 16-bit pixels; 4 spare spread the banks
+    static constexpr int kCopyBytes = (kW + 1) * kRowBytes;      // 7 x 7 patches reach a row past W
+    static constexpr int kRawStride = kW + 4;                    // the window as gathered, bytes
+    static constexpr int kRawBase = 4 * kCopyBytes;
+    static constexpr int kBitBase = kRawBase + kW * kRawStride + 16;   // the descriptor's bits, a byte each
     static constexpr int kLds = kBitBase + kTriplets;
+    static constexpr int kRowQuads = kW / 4;                     // patch rows start at multiples of 4 below
+    static constexpr int kUnits = kW * kRowQuads;                // W - 4 and read two quads
     static constexpr int kSamples = kW * kW / kThreads;         // per thread
     static_assert(kW * kW % kThreads == 0, "whole samples per thread");
 };
@@ -144,30 +149,45 @@ __device__ __forceinline__ void issue_samples(const Keypoint &k, const Positions
         load_samples<kW, true, false>(k, t, tid, g);
 }
 
-// Pixel (i, j) goes to element j - s of row i of copy s, s = 0..3.  For
-// j < s that is element W + kSpare + j - s of the row before (or, for i = 0, of
-// the previous copy's spare row): one of the last three spare elements of a
-// row, which no patch read reaches (a patch row reads elements up to W), so
-// the writes need no condition.
+// This thread's samples into the raw window.
 template <int kW>
 __device__ __forceinline__ void write_window(uint8_t *lds, const Positions &t, int tid,
                                              const uint32_t (&g)[WGeom<kW>::kSamples])
 {
     using G = WGeom<kW>;
-    const int step_a = t.rows ? 2 : G::kRowBytes, step_b = t.rows ? G::kRowBytes : 2;
+    const int step_a = t.rows ? 1 : G::kRawStride, step_b = t.rows ? G::kRawStride : 1;
     const int at = step_a * (tid & 63) + step_b * t.b, wrapped_at = at - 64 * step_b;
+    uint8_t *raw = lds + G::kRawBase;
 #pragma unroll
     for (int m = 0; m < G::kSamples; ++m) {
-        uint8_t *to;
-        if constexpr (kW == 64) {
-            to = lds + (t.b >= 64 - G::kWaves * m ? wrapped_at : at) + G::kWaves * m * step_b;
-        } else {
-            const int q = tid + G::kThreads * m;
-            to = lds + q / kW * G::kRowBytes + 2 * (q % kW);
-        }
-        const uint16_t v = (uint16_t)g[m];
+        const int q = tid + G::kThreads * m;
+        const int to = kW == 64 ? (t.b >= 64 - G::kWaves * m ? wrapped_at : at) + G::kWaves * m * step_b
+                                : q / kW * G::kRawStride + q % kW;
+        raw[to] = (uint8_t)g[m];
+    }
+}
+
+// Copy pass: quadword q of row i of copy s holds pixels 4 q + s .. 4 q + s + 3.
+// (Pixels past column W - 1, and the row past W - 1, meet zero weights only.)
+template <int kW>
+__device__ __forceinline__ void copy_window(uint8_t *lds, int tid)
+{
+    using G = WGeom<kW>;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) *reinterpret_cast<uint16_t *>(to + s * G::kCopyBytes - 2 * s) = v;
+    for (int e0 = 0; e0 < G::kUnits; e0 += G::kThreads) {
+        const int e = e0 + tid;
+        if (G::kUnits % G::kThreads != 0 && e >= G::kUnits) break;
+        const int i = e / G::kRowQuads, q = e % G::kRowQuads;
+        const uint32_t *src = reinterpret_cast<const uint32_t *>(lds + G::kRawBase + i * G::kRawStride + 4 * q);
+        const uint32_t d0 = src[0], d1 = src[1];
+        uint8_t *to = lds + i * G::kRowBytes + 8 * q;
+        // Bytes k, k + 1 of d1:d0 as 16-bit halves.
+        const uint32_t p[6] = {__builtin_amdgcn_perm(d1, d0, 0x0c010c00), __builtin_amdgcn_perm(d1, d0, 0x0c020c01),
+                               __builtin_amdgcn_perm(d1, d0, 0x0c030c02), __builtin_amdgcn_perm(d1, d0, 0x0c040c03),
+                               __builtin_amdgcn_perm(d1, d0, 0x0c050c04), __builtin_amdgcn_perm(d1, d0, 0x0c060c05)};
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            *reinterpret_cast<uint2 *>(to + s * G::kCopyBytes) = make_uint2(p[s], p[s + 2]);
     }
 }
 
@@ -213,10 +233,6 @@ extract_weighted_kernel(
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // The spare columns and row that patch reads reach stay zero (they meet
-    // zero weights only).
-    for (int i = tid; i < G::kBitBase / 4; i += G::kThreads) reinterpret_cast<uint32_t *>(lds)[i] = 0u;
-
     // This lane's slots (round r: 64 (kRounds wave + r) + lane) and the places of
     // their bits.
     uint2 off[G::kRounds];
@@ -245,17 +261,19 @@ extract_weighted_kernel(
     int64_t pending = -1;      // row whose bits are complete in LDS
     for (int i = 0; p < n; ++i, p += stride) {
         const bool compute = cur.ok;
-        __syncthreads();   // the previous descriptor's patch reads are done
-        if (pending >= 0 && wave < kTriplets / 128)
-            pack_words(lds + G::kBitBase, wave, lane, desc + pending * kWords);
-        pending = -1;
         if (!compute) {
             if (tid < kWords) uniform_words(desc + p * kWords)[(uint32_t)tid] = 0u;
             if (tid == 0) atomicOr(flags, bad_image ? kFlagBadImage : kFlagBadKeypoint);
         } else {
+            // The raw window was last read by the previous descriptor's copy
+            // pass, which ended before that descriptor's second barrier.
             write_window<kW>(lds, at, tid, g);
+            __syncthreads();   // raw window complete; the previous triplets are done
+            if (pending >= 0 && wave < kTriplets / 128)
+                pack_words(lds + G::kBitBase, wave, lane, desc + pending * kWords);
+            copy_window<kW>(lds, tid);
+            __syncthreads();   // copies complete
         }
-        __syncthreads();   // window complete
 
         // Next keypoint's gather, in flight during the arithmetic below.
         const int j = (i + 1) & 63;
