@@ -486,19 +486,31 @@ SplitCount count_splits(int64_t nq, int64_t tiles, int64_t group, int64_t slots,
     auto cost = [&](int64_t n) { return rounds(n) * tiles_per(n); };
     const int64_t n_hi = std::min({(int64_t)kMaxSplits, std::max(nsplit, max_by_size), 4 * nsplit + 8,
                                    nsplit + 512});
+    const int64_t top = std::min(n_hi, std::max(nsplit, max_by_cap));
+    // The cost depends on the tiles per split alone: only the smallest count of each is
+    // tried (a few dozen instead of hundreds of counts, each some divisions long).
+    auto each_count = [&](auto stop) {
+        for (int64_t n = nsplit; tiles_per(n) > 1;) {
+            const int64_t fewer = tiles_per(n) - 1;
+            n = (tiles + fewer - 1) / fewer;
+            if (n > top || stop(n)) break;
+        }
+    };
     const int64_t base_cost = cost(nsplit);
-    int64_t least = base_cost, top = nsplit;
-    for (int64_t n = nsplit + 1; n <= n_hi; ++n) {
-        if ((size_t)n * (size_t)nq * 2 * sizeof(uint64_t) > partial_cap) break;
+    int64_t least = base_cost;
+    each_count([&](int64_t n) {
         least = std::min(least, cost(n));
-        top = n;
+        return false;
+    });
+    if (base_cost * 50 > least * 51) {
+        int64_t chosen = nsplit;
+        each_count([&](int64_t n) {
+            if (cost(n) * 50 > least * 51) return false;
+            chosen = n;
+            return true;
+        });
+        nsplit = chosen;
     }
-    if (base_cost * 50 > least * 51)
-        for (int64_t n = nsplit + 1; n <= top; ++n)
-            if (cost(n) * 50 <= least * 51) {
-                nsplit = n;
-                break;
-            }
     const int64_t tps = tiles_per(nsplit);
     return {tps, rounds(nsplit), (int)((tiles + tps - 1) / tps)};
 }
