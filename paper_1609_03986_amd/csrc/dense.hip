@@ -286,7 +286,7 @@ dense_extract_kernel(const uint8_t *__restrict__ img, int height, int width, int
 // the SIMDs issue vector instructions 82% of the time; the 0.30 GB of
 // descriptors, indices and distances take 48 us by themselves (radius 0).
 // Measured (2-NN, accept flags) against XOR and popcount over the same staged
-// region: radius 2 99 -> 70 us, radius 4 256 -> 103 us, radius 8 1069 -> 187 us.
+// region: radius 2 99 -> 70 us, radius 4 256 -> 98 us, radius 8 1069 -> 182 us.
 // Not kept, no faster: the next tile's loads issued before this one's
 // arithmetic, bit 3 of a train nibble used in place as the sign (one
 // instruction less per word, with a per-query correction).
@@ -478,6 +478,9 @@ dense_match_kernel(const uint32_t *__restrict__ query, const uint32_t *__restric
         // Some staged pixel lies outside the grid (uniform).
         const bool border = x0 < RP || y0 < RP || x0 + kMTile + RP > (uint32_t)gw ||
                             y0 + kMTile + RP > (uint32_t)gh;
+        // Wavefronts in the distances issue before those that stage: radius 4 103 -> 98 us,
+        // radius 6 145 -> 137; the other way round 99 and 142.
+        __builtin_amdgcn_s_setprio(2);
         auto distances = [&](auto at_border) {
             uint4 packed = region[frag_at[0]];
 #pragma unroll
@@ -545,6 +548,7 @@ dense_match_kernel(const uint32_t *__restrict__ query, const uint32_t *__restric
         else
             distances(std::false_type{});
 
+        __builtin_amdgcn_s_setprio(0);
         // The four lane rows hold partial results of all four blocks: lane row
         // b ends with block b's.
 #pragma unroll

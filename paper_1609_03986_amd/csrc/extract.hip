@@ -25,6 +25,11 @@
 //      that the 32-lane halves of a ds_read_b64 hit few bank conflicts; each
 //      bit goes to its triplet's place in LDS as a byte, and after the next
 //      descriptor's first barrier 8 lanes at a time pack and store the words.
+// A wavefront's priority rises with the phases of a descriptor, triplets highest,
+// gather lowest: windows that are ready are finished first, and the gathers, whose
+// samples are wanted a descriptor later, fill what issue slots are left.  50,000 keypoints
+// of 1920 x 1080: 122 -> 116 us, 111 -> 100 upright; the gather above all else 120 and
+// 110, the triplets alone above the rest 117 and 104.
 //
 // Patch distances.  With A, C the 7 x 7 patches of the anchor and one
 // companion, ||A - C||^2 = sum A^2 + sum C^2 - 2 sum A C.  sum A^2 is shared by
@@ -45,8 +50,8 @@
 // 1.2 per 16-byte chunk of each 16 lanes), of 1,250 to 1,400 in all.  50,000
 // keypoints of a 1920 x 1080 image: with two wavefronts per window (four per
 // SIMD), 1,060 instructions and 95 bank cycles 135 us at mixed scales and 127 us
-// upright; now 121 and 111 us.  16 images of 3000 x 2000 with 20,000 keypoints
-// each: 894 -> 848 us, 840 -> 750 us upright.  The registers just fit: 64 per
+// upright; now 116 and 100 us.  16 images of 3000 x 2000 with 20,000 keypoints
+// each: 894 -> 795 us.  The registers just fit: 64 per
 // wavefront, and a spill of 20 bytes took back all of the gain (its accesses go
 // through the texture units).
 #include "internal.h"
@@ -326,23 +331,27 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
             if (tid < kWords) uniform_words(desc + q * kWords)[(uint32_t)tid] = 0u;
             if (tid == 0) atomicOr(flags, bad_image ? kFlagBadImage : kFlagBadKeypoint);
         } else {
+            __builtin_amdgcn_s_setprio(0);
             // The raw window was last read by the previous descriptor's copy
             // pass, which ended before that descriptor's second barrier.
             write_chain(lds, s0);
             write_chain(lds, s1);
             if (tail) write_chain(lds, s2);
             __syncthreads();   // raw window complete; the previous triplets are done
+            __builtin_amdgcn_s_setprio(1);
             if (pending >= 0) pack_words(lds + kBitBase, wave, lane, desc + pending * kWords);
             if (tid < kCopyUnits) copy_unit(lds, tid);
             __syncthreads();   // copies complete
         }
 
+        __builtin_amdgcn_s_setprio(0);
         // Start the next keypoint's gather; it completes during the arithmetic below.
         const int j = (i + 1) & 63;
         if (j == 0) batch = prepare_batch<kTable, kHalf>(kps, n, p + stride, stride, lane, rot, src);
         cur = batch_get<kTable>(batch, j, src, &bad_image);
         if (cur.ok) issue_gather(cur, gather_order, tid, tail, s0, s1, s2);
         if (!compute) continue;
+        __builtin_amdgcn_s_setprio(2);
 
         // Eq. 1 for this wavefront's 128 triplets, each bit as a byte in the
         // place of its triplet.

@@ -32,8 +32,8 @@
 // CU, 142 us (the texture units 67% busy: a row of the window crosses up to 64 image
 // rows); along image rows 137, reads one patch row ahead 134, eight wavefronts and
 // free slots 122, a copy pass (64 byte writes and 64 of quadwords per descriptor
-// and wavefronts in place of 256 conflicting 16-bit ones) 110.  50,000 keypoints of
-// 3840 x 2160: 387 -> 268 us; upright 125 -> 104; W = 48 104 -> 96.
+// and wavefronts in place of 256 conflicting 16-bit ones) 110, priorities by phase 100.
+// 50,000 keypoints of 3840 x 2160: 387 -> 246 us; upright 125 -> 94; W = 48 104 -> 96.
 #include "internal.h"
 
 namespace latch {
@@ -258,6 +258,9 @@ extract_weighted_kernel(
     Positions at = positions<kW>(cur, tid);
     if (cur.ok) issue_samples<kW>(cur, at, tid, g);
 
+    // A wavefront's priority by phase, as in the default kernel: 110 -> 100 us, 104 -> 94
+    // upright.  (W = 48, five wavefronts per SIMD, is 3% slower with it.)
+    constexpr bool kPriorities = kW == 64;
     int64_t pending = -1;      // row whose bits are complete in LDS
     for (int i = 0; p < n; ++i, p += stride) {
         const bool compute = cur.ok;
@@ -265,16 +268,19 @@ extract_weighted_kernel(
             if (tid < kWords) uniform_words(desc + p * kWords)[(uint32_t)tid] = 0u;
             if (tid == 0) atomicOr(flags, bad_image ? kFlagBadImage : kFlagBadKeypoint);
         } else {
+            if (kPriorities) __builtin_amdgcn_s_setprio(0);
             // The raw window was last read by the previous descriptor's copy
             // pass, which ended before that descriptor's second barrier.
             write_window<kW>(lds, at, tid, g);
             __syncthreads();   // raw window complete; the previous triplets are done
+            if (kPriorities) __builtin_amdgcn_s_setprio(1);
             if (pending >= 0 && wave < kTriplets / 128)
                 pack_words(lds + G::kBitBase, wave, lane, desc + pending * kWords);
             copy_window<kW>(lds, tid);
             __syncthreads();   // copies complete
         }
 
+        if (kPriorities) __builtin_amdgcn_s_setprio(0);
         // Next keypoint's gather, in flight during the arithmetic below.
         const int j = (i + 1) & 63;
         if (j == 0) batch = prepare_batch<kTable, G::kHalfW>(kps, n, p + stride, stride, lane, rot, src);
@@ -282,6 +288,7 @@ extract_weighted_kernel(
         at = positions<kW>(cur, tid);
         if (cur.ok) issue_samples<kW>(cur, at, tid, g);
         if (!compute) continue;
+        if (kPriorities) __builtin_amdgcn_s_setprio(2);
 
         constexpr int kAllRows = G::kRounds * kPatchRows;
         PatchRow rows[kRowsAhead + 1];
