@@ -264,3 +264,32 @@ def test_order_over_many_buckets(torch_cuda, triplets, n_images, shuffled):
         assert lat.check_errors(clear=True) == 0
     finally:
         lat.close()
+
+
+def test_order_in_several_launches(torch_cuda, triplets):
+    """A batch that runs in three launches, with a device count inside the last: the descriptors
+    before the count equal unordered parts, those after it stay untouched."""
+    torch = torch_cuda
+    from paper_1609_03986_amd.binding import Latch, image_table
+    g = np.random.default_rng(5)
+    n, count = 1_200_001, 1_100_003
+    imgs = [torch.from_numpy(g.integers(0, 256, (300, 200), dtype=np.uint8)).cuda() for _ in range(3)]
+    ids = torch.from_numpy(g.integers(0, 3, n).astype(np.int32)).cuda()
+    kps = np.zeros((n, 4), np.float32)
+    kps[:, 0], kps[:, 1] = g.uniform(0, 200, n), g.uniform(0, 300, n)
+    kps[:, 2], kps[:, 3] = g.uniform(0, 360, n), 1
+    k = torch.from_numpy(kps).cuda()
+    table = image_table(imgs)
+    lat = Latch(triplets)
+    try:
+        got = torch.full((n, 16), -7, dtype=torch.int32, device="cuda")
+        lat.extract_batch(table, 3, ids, k, desc=got,
+                          n_kps=torch.tensor([count], dtype=torch.int64, device="cuda"))
+        assert bool((got[count:] == -7).all())
+        for first in range(0, count, 200_000):
+            part = slice(first, min(count, first + 200_000))
+            assert torch.equal(got[part], lat.extract_batch(table, 3, ids[part].contiguous(),
+                                                            k[part].contiguous()))
+        assert lat.check_errors(clear=True) == 0
+    finally:
+        lat.close()
