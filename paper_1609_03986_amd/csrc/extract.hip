@@ -396,12 +396,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
 // 1,910,000 of uneven images 5890 -> 5450 in four, 5495 in eight.  580,000 of 1280 x 720,
 // which drift costs little, take 0.6% longer in two.
 constexpr int64_t kSegment = 400000;
+// With a count on the device the launches past it find nothing to do, about 4 us each.
+constexpr int64_t kMostCounted = 4;
 
 hipError_t launch_extract(const ExtractArgs &a, hipStream_t stream)
 {
     if (a.n <= 0) return hipSuccess;
     const int64_t resident = (int64_t)a.num_cus * (kLdsPerCu / kWinLdsBytes);
-    const int64_t launches = a.order ? std::max<int64_t>(1, a.n / kSegment) : 1;
+    int64_t launches = a.order ? std::max<int64_t>(1, a.n / kSegment) : 1;
+    if (a.n_dev) launches = std::min(launches, kMostCounted);
     const int64_t segment = (a.n + launches - 1) / launches;
     ImageSource src{a.img, a.height, a.width, a.pitch, a.table, a.image_id, a.n_images, a.order};
     for (int64_t begin = 0; begin < a.n; begin += segment) {
