@@ -215,6 +215,8 @@ hipError_t launch_knn_split(const KnnSplitArgs &a, SplitKernel which, hipStream_
 // Queries per workgroup of a matcher kernel (the unit of query groups and batch items).
 int queries_per_group(SplitKernel which, int fp4_query_blocks);
 hipError_t launch_knn_merge(const KnnSplitArgs &a, hipStream_t stream);
+// Workgroups (of 256 work items) of the merge of nq queries.
+int64_t merge_blocks(int64_t nq);
 
 // Layout-compatible with latch_pair of the C ABI.
 struct PairEntry {

@@ -677,6 +677,11 @@ __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int m)
 // 4 lanes, 101.9 with 8, 99.5 with 16 and 98.9 with 32; 2000 x 2000 7.4 us with 16
 // and 8.2 with 4.
 constexpr int kMergeLanes = 16;
+constexpr int kMergeQueries = 256 / kMergeLanes;         // per workgroup and pass
+// A launch holds fewer than 2^32 work items, which 16 lanes per query pass at 2^28
+// queries: from 2^20 on the workgroups take several passes (2^16 workgroups are 32
+// times what the GPU holds at once).
+constexpr int64_t kMergeMaxBlocks = 1 << 16;
 
 __global__ __launch_bounds__(256) void knn_merge_kernel(const uint64_t *__restrict__ partial, int nq,
                                                         int nsplit, int nt, int k, float ratio,
@@ -685,24 +690,30 @@ __global__ __launch_bounds__(256) void knn_merge_kernel(const uint64_t *__restri
                                                         uint8_t *__restrict__ accept)
 {
     const int g = threadIdx.x & (kMergeLanes - 1);
-    const int q = blockIdx.x * (256 / kMergeLanes) + threadIdx.x / kMergeLanes;
-    const bool real = q < nq;
-    uint64_t b1 = kNoNeighbour, b2 = kNoNeighbour;
-    for (int s0 = g; s0 < nsplit; s0 += 4 * kMergeLanes) {
-        ulonglong2 v[4];
+    // (nq < 2^31 and a pass takes at most kMergeMaxBlocks kMergeQueries queries: 32 bits.)
+    for (uint32_t q0 = blockIdx.x * kMergeQueries; q0 < (uint32_t)nq; q0 += gridDim.x * kMergeQueries) {
+        const uint32_t q = q0 + threadIdx.x / kMergeLanes;
+        const bool real = q < (uint32_t)nq;
+        uint64_t b1 = kNoNeighbour, b2 = kNoNeighbour;
+        for (int s0 = g; s0 < nsplit; s0 += 4 * kMergeLanes) {
+            ulonglong2 v[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int sp = s0 + kMergeLanes * i;
-            v[i] = real && sp < nsplit
-                       ? reinterpret_cast<const ulonglong2 *>(partial)[(size_t)sp * nq + q]
-                       : make_ulonglong2(kNoNeighbour, kNoNeighbour);
+            for (int i = 0; i < 4; ++i) {
+                const int sp = s0 + kMergeLanes * i;
+                v[i] = real && sp < nsplit
+                           ? reinterpret_cast<const ulonglong2 *>(partial)[(size_t)sp * nq + q]
+                           : make_ulonglong2(kNoNeighbour, kNoNeighbour);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) top2_pair(b1, b2, v[i].x, v[i].y);
         }
+        // (Every lane takes part: the loop's bounds are the workgroup's.)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) top2_pair(b1, b2, v[i].x, v[i].y);
+        for (int m = 1; m < kMergeLanes; m <<= 1)
+            top2_pair(b1, b2, shfl_xor_u64(b1, m), shfl_xor_u64(b2, m));
+        if (real && g == 0)
+            store_final(b1, b2, nt, ItemOut{nullptr, idx, dist, accept, k, ratio}, (int)q);
     }
-#pragma unroll
-    for (int m = 1; m < kMergeLanes; m <<= 1) top2_pair(b1, b2, shfl_xor_u64(b1, m), shfl_xor_u64(b2, m));
-    if (real && g == 0) store_final(b1, b2, nt, ItemOut{nullptr, idx, dist, accept, k, ratio}, q);
 }
 
 __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void
@@ -1081,11 +1092,14 @@ hipError_t launch_knn_split(const KnnSplitArgs &a, SplitKernel which, hipStream_
     return hipGetLastError();
 }
 
+int64_t merge_blocks(int64_t nq)
+{
+    return std::min((nq + kMergeQueries - 1) / kMergeQueries, kMergeMaxBlocks);
+}
+
 hipError_t launch_knn_merge(const KnnSplitArgs &a, hipStream_t stream)
 {
-    const int64_t per_block = 256 / kMergeLanes;
-    const int64_t blocks = (a.plan.nq + per_block - 1) / per_block;
-    hipLaunchKernelGGL(knn_merge_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, a.partial,
+    hipLaunchKernelGGL(knn_merge_kernel, dim3((unsigned)merge_blocks(a.plan.nq)), dim3(256), 0, stream, a.partial,
                        (int)a.plan.nq, a.plan.nsplit, (int)a.plan.nt, a.k, a.ratio, a.idx, a.dist,
                        a.accept);
     return hipGetLastError();

@@ -239,3 +239,22 @@ def test_short_splits(torch_cuda, lat, nq, nt):
     T[-1], T[nt // 2] = T[0], Q[0]
     for k in (1, 2):
         check(torch_cuda, lat, Q, T, k=k)
+
+
+def test_merge_takes_several_passes(torch_cuda, lat):
+    """2^20 queries fill one pass of the merge's workgroups; 21 more take a second one.  The train
+    rows need two splits on the FP4 path (16,384 rows each); the batched popcount matcher never
+    splits."""
+    torch = torch_cuda
+    from paper_1609_03986_amd.binding import pair_table
+    g = torch.Generator(device="cuda").manual_seed(5)
+    nq, nt = (1 << 20) + 21, 16_400
+    words = lambda n: torch.randint(-2 ** 31, 2 ** 31, (n, 16), generator=g, device="cuda").to(torch.int32)
+    q, t = words(nq), words(nt)
+    q[-30:] = t[-30:]                                    # the nearest row is in the second split
+    assert lat.knn_workspace_size(nq, nt, "fp4") >= 2 * 16 * nq
+    want = lat.knn_batch(q, t, pair_table([(0, nq, 0, nt, 0)]), nq, path="popcount")
+    got = lat.knn(q, t, path="fp4")
+    for w, x in zip(want, got):
+        assert bool((w == x).all())
+    assert bool((got[0][-30:, 0] == torch.arange(nt - 30, nt, device="cuda")).all())
