@@ -26,7 +26,8 @@
  *       latch_timing_enable, latch_timing_read: the recorded events;
  *       latch_destroy, latch_plan_destroy: the whole device.
  *   - A handle owns device copies of the rotation table and triplet table,
- *     a sticky error word and a workspace that only latch_reserve sizes.
+ *     a sticky error word, 13.6 MB for the train ranges that hamming_knn_batch
+ *     divides over workgroups and a workspace that only latch_reserve sizes.
  *     hamming_knn (with more than one train split), hamming_knn_batch,
  *     latch_detect and large batched extractions need workspace; the
  *     *_workspace_size calls give the bytes
@@ -159,11 +160,9 @@ void latch_destroy(latch_handle h);
  *     The split count depends on nq, nt, the path (LATCH_PATH_AUTO resolved
  *     by the handle's current tuning table) and the tuning's workgroup
  *     targets, so query after latch_set_tuning.
- *   hamming_knn_batch_workspace_size: the pair table's per-pair state, the
- *     work-unit list of the persistent matcher, and room for up to 2048
- *     query groups whose train rows are divided over workgroups (at most
- *     6.1 KB each; with less, down to 16 bytes per pair and 4 per 256 output
- *     rows and pair, the batch runs undivided).
+ *   hamming_knn_batch_workspace_size: the pair table's per-pair state and
+ *     the work-unit list of the persistent matcher (16 bytes per pair and 4 per
+ *     256 output rows and pair).
  *   latch_detect_workspace_size: survivor masks, counts and row offsets of
  *     an image of height x width.
  *   latch_extract_batch_workspace_size: a latch_create handle orders a batch
@@ -372,8 +371,9 @@ typedef struct {
  * with nt > 2^21 - 32, is skipped and sets LATCH_FLAG_BAD_PAIR.  Pairs'
  * output ranges should not overlap (they are written concurrently).  k,
  * ratio and path as for hamming_knn.  Uses the handle's workspace
- * (hamming_knn_batch_workspace_size; with less, the undivided batch's part of
- * it, and LATCH_EWORKSPACE if the handle does not hold that either).
+ * (hamming_knn_batch_workspace_size; LATCH_EWORKSPACE if the handle holds
+ * less) and, on the FP4 path and for up to 58,000,000 output rows, the handle's
+ * room for dividing the train ranges of long pairs over workgroups.
  */
 int hamming_knn_batch(latch_handle h, const uint32_t *query_dev, int64_t query_rows,
                       const uint32_t *train_dev, int64_t train_rows, const latch_pair *pairs_dev,

@@ -421,13 +421,8 @@ def hamming_knn_batch(h, query, train, pairs, out_rows, k=2, ratio=0.8, path="au
     args = (h, qptr, query.shape[0], tptr, train.shape[0], _dev(pairs, torch.int64, "pairs"),
             pairs.shape[0], int(k), float(ratio), _dev(idx, torch.int32, "idx"),
             _dev(dist, torch.int32, "dist"), acc_ptr, int(out_rows), PATHS[path], _stream_ptr(stream))
-    def size():
-        return hamming_knn_batch_workspace_size(h, pairs.shape[0], out_rows)
-
-    # A smaller workspace than this would do, without dividing long train ranges.
-    if not torch.cuda.is_current_stream_capturing():
-        latch_reserve(h, size())
-    _with_workspace(h, lambda: load_library().hamming_knn_batch(*args), size)
+    _with_workspace(h, lambda: load_library().hamming_knn_batch(*args),
+                    lambda: hamming_knn_batch_workspace_size(h, pairs.shape[0], out_rows))
     return idx, dist, accept
 
 

@@ -772,7 +772,7 @@ __global__ __launch_bounds__(256) void knn_popcount_kernel(SplitArgs a)
 // (shorter ones cost more in query fragments and merging than they even out: 48, 64,
 // 96 and 128 were tried) and at most kMaxParts of them.  Long pairs among short ones and the last rounds
 // of a batch of equal pairs are divided, the rest is not.  Parts of a query group
-// meet in a slot of the workspace, two 64-bit keys per query: with k1 <= k2 the
+// meet in a slot, two 64-bit keys per query: with k1 <= k2 the
 // part's best two, old = atomicMin(first, k1), then atomicMin(second,
 // min(k2, max(old, k1))); every k1 but the smallest is the larger of some such
 // pair once, so `second` ends as the second smallest of all.  The part that

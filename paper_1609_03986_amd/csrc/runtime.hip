@@ -32,6 +32,7 @@ struct latch_ctx {
     WeightRows weights = {};
     uint8_t *ws = nullptr;             // grow-only workspace
     size_t ws_bytes = 0;
+    uint8_t *parts = nullptr;          // handle_parts(): what dividing train ranges needs
     uint8_t *scratch = nullptr;        // this device's copy of the static scratch array
     latch_tuning tuning;               // LATCH_PATH_AUTO table and split targets
     std::string last_error;
@@ -590,37 +591,62 @@ DetectLayout detect_layout(int height, int width)
     return l;
 }
 
-// Workspace of a batched matching: the pairs' state, the header and the unit map
-// (`base` bytes), then what dividing train ranges needs: more map entries, counts and
-// keys of the slots.
+// Workspace of a batched matching: the pairs' state, the header and the unit map of
+// undivided pairs.
 struct BatchLayout {
     int64_t item_capacity;
-    int64_t slots;
-    size_t info_bytes, base, map_bytes, done_bytes, total;
+    size_t info_bytes, total;
 };
 
 BatchLayout batch_layout(int n_pairs, int64_t out_rows)
 {
     BatchLayout l;
     l.item_capacity = out_rows / 256 + n_pairs + 1;
-    l.slots = std::min(l.item_capacity, kBatchMaxSlots);
     l.info_bytes = align_up((size_t)n_pairs * sizeof(PairInfo), 256);
-    l.base = l.info_bytes + 256 + align_up((size_t)l.item_capacity * sizeof(int32_t), 256);
-    l.map_bytes = align_up((size_t)(l.item_capacity + l.slots * (kBatchMaxParts - 1)) * sizeof(int32_t), 256);
-    l.done_bytes = align_up((size_t)l.slots * sizeof(uint32_t), 256);
-    l.total = l.info_bytes + 256 + l.map_bytes + l.done_bytes +
-              (size_t)l.slots * kBatchSlotQueries * 2 * sizeof(uint64_t);
+    l.total = l.info_bytes + 256 + align_up((size_t)l.item_capacity * sizeof(int32_t), 256);
     return l;
 }
 
 size_t batch_workspace_bytes(int n_pairs, int64_t out_rows) { return batch_layout(n_pairs, out_rows).total; }
 
-// Arguments of the batched matcher with its workspace at `ws`
-// of ws_bytes.  A workspace without room for slots divides no train range.
-BatchArgs batch_args(latch_handle h, uint8_t *ws, size_t ws_bytes, const uint32_t *query_dev, int64_t query_rows,
-                     const uint32_t *train_dev, int64_t train_rows, const latch_pair *pairs_dev,
-                     int n_pairs, int k, float ratio, int32_t *idx_dev, int32_t *dist_dev,
-                     uint8_t *accept_dev, int64_t out_rows, int path)
+// What dividing train ranges needs beyond the workspace: the slots' keys and counts,
+// and a unit map with room for their parts.  A handle holds it for its calls from its
+// creation on and a plan its own, so that no call depends on how large a workspace
+// earlier ones left.
+struct PartMemory {
+    int64_t slots, units;
+    size_t best_bytes, done_bytes, total;
+};
+
+PartMemory part_memory(int64_t slots, int64_t units)
+{
+    PartMemory m;
+    m.slots = slots;
+    m.units = units;
+    m.best_bytes = (size_t)slots * kBatchSlotQueries * 2 * sizeof(uint64_t);
+    m.done_bytes = align_up((size_t)slots * sizeof(uint32_t), 256);
+    m.total = m.best_bytes + m.done_bytes + (size_t)units * sizeof(int32_t);
+    return m;
+}
+
+// A handle's: the units of any batch of up to 58,000,000 output rows.  (Larger ones, of
+// hundreds of rounds of units, are not divided; a plan's memory fits its batch.)
+PartMemory handle_parts() { return part_memory(kBatchMaxSlots, 1 << 18); }
+
+PartMemory plan_parts(int n_pairs, int64_t out_rows)
+{
+    const int64_t items = batch_layout(n_pairs, out_rows).item_capacity;
+    const int64_t slots = std::min(items, kBatchMaxSlots);
+    return part_memory(slots, items + slots * (kBatchMaxParts - 1));
+}
+
+// Arguments of the batched matcher with its workspace (batch_workspace_bytes bytes) at
+// `ws` and the memory of parts `m` at `parts` (nullptr: no train range is divided).
+BatchArgs batch_args(latch_handle h, uint8_t *ws, uint8_t *parts, const PartMemory &m,
+                     const uint32_t *query_dev, int64_t query_rows, const uint32_t *train_dev,
+                     int64_t train_rows, const latch_pair *pairs_dev, int n_pairs, int k, float ratio,
+                     int32_t *idx_dev, int32_t *dist_dev, uint8_t *accept_dev, int64_t out_rows,
+                     int path)
 {
     const BatchLayout l = batch_layout(n_pairs, out_rows);
     BatchArgs a;
@@ -634,12 +660,13 @@ BatchArgs batch_args(latch_handle h, uint8_t *ws, size_t ws_bytes, const uint32_
     a.item_capacity = l.item_capacity;
     a.info = reinterpret_cast<PairInfo *>(ws);
     a.state = reinterpret_cast<BatchState *>(ws + l.info_bytes);
-    uint8_t *map = ws + l.info_bytes + 256;
-    a.unit_pair = reinterpret_cast<int32_t *>(map);
+    a.unit_pair = reinterpret_cast<int32_t *>(ws + l.info_bytes + 256);
     a.slots = BatchSlots{nullptr, nullptr, 0};
-    if (ws_bytes >= l.total)
-        a.slots = BatchSlots{reinterpret_cast<uint64_t *>(map + l.map_bytes + l.done_bytes),
-                             reinterpret_cast<uint32_t *>(map + l.map_bytes), (int)l.slots};
+    if (parts && l.item_capacity + m.slots * (kBatchMaxParts - 1) <= m.units) {
+        a.slots = BatchSlots{reinterpret_cast<uint64_t *>(parts),
+                             reinterpret_cast<uint32_t *>(parts + m.best_bytes), (int)m.slots};
+        a.unit_pair = reinterpret_cast<int32_t *>(parts + m.best_bytes + m.done_bytes);
+    }
     a.k = k;
     a.ratio = ratio;
     a.idx = idx_dev;
@@ -757,6 +784,7 @@ int create_base(latch_ctx **out)
     for (int a = 0; a < kBins; ++a)
         rot[a] = make_int2((int)((uint16_t)c[a] | (uint32_t)(uint16_t)s[a] << 16), (int)ties[a]);
     if ((e = hipMalloc((void **)&h->rot_dev, sizeof rot)) == hipSuccess &&
+        (e = hipMalloc((void **)&h->parts, handle_parts().total)) == hipSuccess &&
         (e = hipMalloc((void **)&h->flags_dev, sizeof(uint32_t))) == hipSuccess) {
         const Upload u[2] = {{h->rot_dev, rot, sizeof rot}, {h->flags_dev, nullptr, sizeof(uint32_t)}};
         e = upload(u, 2);
@@ -989,6 +1017,7 @@ void latch_destroy(latch_handle h)
     if (h->wbit_of_dev) (void)hipFree(h->wbit_of_dev);
     if (h->dense_off_dev) (void)hipFree(h->dense_off_dev);
     if (h->ws) (void)hipFree(h->ws);
+    if (h->parts) (void)hipFree(h->parts);
     release_timed(h);
     for (hipEvent_t e : h->event_pool) (void)hipEventDestroy(e);
     delete h;
@@ -1326,9 +1355,9 @@ int hamming_knn_batch(latch_handle h, const uint32_t *query_dev, int64_t query_r
         return fail(h, LATCH_EINVAL, "null buffer");
     if (path == LATCH_PATH_AUTO) path = h->tuning.batch_path;
 
-    const int rc = check_workspace(h, batch_layout(n_pairs, out_rows).base, "hamming_knn_batch");
+    const int rc = check_workspace(h, batch_workspace_bytes(n_pairs, out_rows), "hamming_knn_batch");
     if (rc != LATCH_OK) return rc;
-    const BatchArgs a = batch_args(h, h->ws, h->ws_bytes, query_dev, query_rows, train_dev, train_rows,
+    const BatchArgs a = batch_args(h, h->ws, h->parts, handle_parts(), query_dev, query_rows, train_dev, train_rows,
                                    pairs_dev, n_pairs, k, ratio, idx_dev, dist_dev, accept_dev,
                                    out_rows, path);
     const char *name = a.kind == SplitKernel::kPopcount  ? "knn_batch_popcount"
@@ -1358,8 +1387,13 @@ int latch_plan_create(latch_handle h, const latch_plan_desc *d, latch_plan *out)
 
     latch_plan_ctx *p = new latch_plan_ctx();
     p->h = h;
-    // Plan workspace: the matcher's state, then the extraction's order.
-    const size_t knn_bytes = align_up(batch_workspace_bytes(d->n_pairs, d->out_rows), 256);
+    // Plan workspace: the matcher's state, on the FP4 path what its parts need, then
+    // the extraction's order.
+    const int path = d->path == LATCH_PATH_AUTO ? h->tuning.batch_path : d->path;
+    const size_t state_bytes = batch_workspace_bytes(d->n_pairs, d->out_rows);
+    const PartMemory parts = plan_parts(d->n_pairs, d->out_rows);
+    const bool divides = split_kernel(path) == SplitKernel::kMfmaFp4;
+    const size_t knn_bytes = state_bytes + (divides ? align_up(parts.total, 256) : 0);
     const size_t order_bytes = extract_batch_workspace(h, d->n_images, d->max_kps);
     hipError_t e = hipMalloc((void **)&p->ws, knn_bytes + order_bytes);
     if (e != hipSuccess) {
@@ -1368,10 +1402,9 @@ int latch_plan_create(latch_handle h, const latch_plan_desc *d, latch_plan *out)
     }
     const ExtractArgs ea = batch_extract_args(h, d->images, d->n_images, d->image_id, d->kps,
                                               d->max_kps, d->n_kps, d->desc);
-    const BatchArgs ba = batch_args(h, p->ws, knn_bytes, d->desc, d->max_kps, d->desc, d->max_kps, d->pairs,
-                                    d->n_pairs, d->k, d->ratio, d->idx, d->dist, d->accept,
-                                    d->out_rows,
-                                    d->path == LATCH_PATH_AUTO ? h->tuning.batch_path : d->path);
+    const BatchArgs ba = batch_args(h, p->ws, divides ? p->ws + state_bytes : nullptr, parts, d->desc,
+                                    d->max_kps, d->desc, d->max_kps, d->pairs, d->n_pairs, d->k, d->ratio, d->idx,
+                                    d->dist, d->accept, d->out_rows, path);
     hipStream_t s = nullptr;
     e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);

@@ -30,10 +30,52 @@ void merge_launch()
     std::puts("merge launch");
 }
 
+// Batched matching: the workspace holds what undivided pairs need; the memory of parts
+// holds its three arrays one after the other, and serves a call whose unit map it holds.
+void batch_memory()
+{
+    latch_ctx h;
+    default_tuning(&h.tuning);
+    uint8_t *ws = reinterpret_cast<uint8_t *>(1 << 20), *mem = reinterpret_cast<uint8_t *>(1 << 30);
+    auto up = [](size_t v) { return (v + 255) / 256 * 256; };
+    for (int n_pairs : {1, 3, 63, 100000, 300000})
+        for (int64_t rows : {1LL, 1280000LL, 58000000LL, 60000000LL, LATCH_MAX_ROWS}) {
+            const int64_t items = rows / 256 + n_pairs + 1;
+            check(batch_workspace_bytes(n_pairs, rows) == up(16 * (size_t)n_pairs) + 256 + up(4 * (size_t)items),
+                  "batch workspace", n_pairs, rows);
+            for (const PartMemory &m : {handle_parts(), plan_parts(n_pairs, rows)}) {
+                const BatchArgs a = batch_args(&h, ws, mem, m, nullptr, 0, nullptr, 0, nullptr, n_pairs, 2, 0.8f,
+                                               nullptr, nullptr, nullptr, rows, LATCH_PATH_MFMA_FP4);
+                const bool fits = items + m.slots * (kBatchMaxParts - 1) <= m.units;
+                check(a.item_capacity == items && a.slots.count == (fits ? m.slots : 0), "slots", n_pairs, rows);
+                const uint8_t *map = reinterpret_cast<const uint8_t *>(a.unit_pair);
+                if (!fits) {
+                    check(map >= ws && map + 4 * items <= ws + batch_workspace_bytes(n_pairs, rows),
+                          "map in the workspace", n_pairs, rows);
+                    continue;
+                }
+                const int64_t done = reinterpret_cast<uint8_t *>(a.slots.done) - mem;
+                check(reinterpret_cast<uint8_t *>(a.slots.best) == mem && done >= m.slots * kBatchSlotQueries * 16 &&
+                          done % 256 == 0 && (map - mem) % 256 == 0 && map - mem >= done + 4 * m.slots &&
+                          map - mem + 4 * (items + m.slots * (kBatchMaxParts - 1)) <= (int64_t)m.total,
+                      "memory of parts", n_pairs, rows);
+            }
+            const PartMemory own = plan_parts(n_pairs, rows);
+            check(own.units >= items + own.slots * (kBatchMaxParts - 1), "a plan's parts fit its batch", rows);
+            check(rows > 58000000 || n_pairs > 3 ||
+                      items + kBatchMaxSlots * (kBatchMaxParts - 1) <= handle_parts().units,
+                  "a handle's parts fit ordinary batches", rows);
+        }
+    check(batch_args(&h, ws, nullptr, handle_parts(), nullptr, 0, nullptr, 0, nullptr, 1, 2, 0.8f, nullptr, nullptr,
+                     nullptr, 1, LATCH_PATH_MFMA).slots.count == 0, "no memory, no slots");
+    std::puts("batch memory");
+}
+
 }  // namespace
 
 int main()
 {
     merge_launch();
+    batch_memory();
     return failures ? 1 : 0;
 }

@@ -255,3 +255,55 @@ def test_more_divided_groups_than_slots(torch_cuda, lat):
         want = lat.knn(D[part], D[i * nq:i * nq + nt], path="mfma")
         for got, w in zip((idx[part], dist[part], acc[part]), want):
             assert bool((got == w).all()), i
+
+
+def test_batch_leaves_a_sufficient_workspace_alone(torch_cuda, triplets):
+    """On a handle whose workspace holds what the call needs, a batch with a divided pair keeps that
+    workspace, so that a graph captured over it stays valid; and a call on a stream that is capturing
+    and is not the current one is captured like any other."""
+    from paper_1609_03986_amd.binding import Latch, pair_table
+    torch = torch_cuda
+    g = np.random.default_rng(11)
+    Q, T = synth.random_descriptors(g, 700, 0.3), synth.random_descriptors(g, 9000, 0.3)
+    q, t = dev(torch, Q), dev(torch, T)
+    rows = [(0, 600, 0, 9000, 0), (600, 100, 40, 33, 600)]
+    table = pair_table(rows)
+    want = [np.concatenate(x) for x in zip(*(oracle.knn(Q[a:a + n], T[f:f + m]) for a, n, f, m, _ in rows))]
+    outputs = lambda: (torch.zeros((700, 2), dtype=torch.int32, device="cuda"),
+                       torch.zeros((700, 2), dtype=torch.int32, device="cuda"),
+                       torch.zeros((700,), dtype=torch.uint8, device="cuda"))
+    lat = Latch(triplets)
+    try:
+        single = lat.knn_workspace_size(8, 9000, "fp4")
+        held = lat.reserve(max(single, lat.knn_batch_workspace_size(len(rows), 700)))
+        # Less than the batch's three query groups and the rest would take with room for dividing.
+        assert 0 < single <= held < 3 * 6144 + 2048
+        one = oracle.knn(Q[:8], T)
+        out = [x[:8] for x in outputs()]
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            lat.knn(q[:8], t, path="fp4", idx=out[0], dist=out[1], accept=out[2])
+        batch_out, side = outputs(), torch.cuda.Stream()
+        batch_graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        with torch.cuda.graph(batch_graph, stream=stream):
+            with torch.cuda.stream(side):
+                lat.knn_batch(q, t, table, 700, path="fp4", idx=batch_out[0], dist=batch_out[1],
+                              accept=batch_out[2], stream=stream)
+        for rep in range(3):
+            for path in ("fp4", "mfma", "popcount"):
+                got = lat.knn_batch(q, t, table, 700, path=path)
+                assert lat.reserve(0) == held
+                for x, w in zip(got, want):
+                    assert np.array_equal(x.cpu().numpy(), w), path
+            for replay, to, ref in ((graph, out, one), (batch_graph, batch_out, want)):
+                for x in to:
+                    x.fill_(7)
+                replay.replay()
+                torch.cuda.synchronize()
+                for x, w in zip(to, ref):
+                    assert np.array_equal(x.cpu().numpy(), w), rep
+        del graph, batch_graph
+    finally:
+        torch.cuda.synchronize()
+        lat.close()
