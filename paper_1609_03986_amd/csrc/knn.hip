@@ -23,6 +23,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "batch_parts.h"
 #include "internal.h"
 
 namespace latch {
@@ -782,9 +783,6 @@ __global__ __launch_bounds__(256) void knn_popcount_kernel(SplitArgs a)
 // 262 -> 97, one pair of 20,000 x 20,000 470 -> 116, 15 such pairs 1130 -> 934, 63
 // 3911 -> 3697.  Parts of R / 2 S, 3 R / 4 S and 3 R / 2 S were up to 10% slower.
 // ---------------------------------------------------------------------------
-constexpr int kMinPartTiles = 80;
-constexpr int kMaxParts = kBatchMaxParts;
-
 __device__ __forceinline__ bool pair_ok(const PairEntry &e, int64_t query_rows, int64_t train_rows,
                                         int64_t out_rows)
 {
@@ -792,17 +790,6 @@ __device__ __forceinline__ bool pair_ok(const PairEntry &e, int64_t query_rows, 
            e.query_first >= 0 && e.query_first + e.nq <= query_rows &&
            (e.nt == 0 || (e.train_first >= 0 && e.train_first + e.nt <= train_rows)) &&
            e.out_first >= 0 && e.out_first + e.nq <= out_rows;
-}
-
-// Cost class of a pair, 0 for the longest items: 255 - floor(8 log2(tiles + 1))
-// with the fraction taken from the three bits after the leading one.
-__device__ __forceinline__ int cost_class(int64_t nt)
-{
-    nt = max((int64_t)0, min(nt, (int64_t)kMaxSplitRows));          // invalid pairs: any class
-    const uint32_t x = (uint32_t)((nt + kTileRows - 1) / kTileRows) + 1u;   // <= 2^16
-    const int lz = __clz((int)x);
-    const uint32_t frac = ((x << lz) >> 28) & 7u;
-    return 255 - min(255, 8 * (31 - lz) + (int)frac);
 }
 
 // Inclusive scan of 256 values in LDS: within the wavefronts, then over their totals.
@@ -821,6 +808,33 @@ __device__ __forceinline__ void scan256(unsigned long long *v, unsigned long lon
     for (int w = 0; w < tid >> 6; ++w) x += totals[w];
     v[tid] = x;
     __syncthreads();
+}
+
+// First slot of this lane's `groups` query groups if it `wants` them and they are to
+// be had, else -1.  A wavefront's lanes take theirs in turn and the wavefront all of them at
+// once, so a pair that does not fit takes none from those after it.  (With one atomic
+// add per pair, undone for no one, a refused pair's slots were lost to the rest.)
+__device__ __forceinline__ int take_slots(int *used, bool wants, int groups, int slots)
+{
+    const uint64_t wanting = __ballot(wants);
+    if (wanting == 0) return -1;
+    const int lane = threadIdx.x & 63, first = __builtin_ctzll(wanting);
+    int seen = 0;
+    for (;;) {                        // (another round only if another wavefront took slots)
+        int slot = -1, at = seen;
+        for (uint64_t m = wanting; m != 0; m &= m - 1) {
+            const int l = __builtin_ctzll(m);
+            const int g = __builtin_amdgcn_readlane(groups, l);
+            if (at + g > slots) continue;
+            if (lane == l) slot = at;
+            at += g;
+        }
+        int old = 0;
+        if (lane == first) old = atomicCAS(used, seen, at);
+        old = __builtin_amdgcn_readlane(old, first);
+        if (old == seen) return slot;
+        seen = old;
+    }
 }
 
 // resident: workgroups that run at once; slots: query groups that may be divided.
@@ -869,20 +883,14 @@ __global__ __launch_bounds__(256) void knn_batch_setup_kernel(
             const unsigned long long in_class = classes[c] - (c > 0 ? classes[c - 1] : 0ull);
             const unsigned long long left = all_work - works[c] +
                                             (in_class - (uint32_t)info[p].unit_first) * tiles;
-            const int chunk = (int)max((unsigned long long)kMinPartTiles,
-                                       min(left / (uint32_t)resident, 1ull << 20));
-            parts = (uint32_t)min(kMaxParts, (tiles + chunk - 1) / chunk);
-            if (parts > 1) {
-                const int per_part = (tiles + (int)parts - 1) / (int)parts;
-                parts = (uint32_t)((tiles + per_part - 1) / per_part);
-                slot = (uint32_t)atomicAdd(&slots_s, (int)groups);
-                if ((int64_t)slot + groups > slots) parts = 1;
-            }
-            parts = max(parts, 1u);
+            parts = (uint32_t)train_parts(tiles, left, resident);
         }
+        const int got = take_slots(&slots_s, parts > 1, (int)groups, slots);
+        if (got < 0) parts = 1;
+        else slot = (uint32_t)got;
         info[p].groups = (int32_t)groups;
         info[p].parts = parts;
-        info[p].slot = parts > 1 ? slot : 0u;
+        info[p].slot = slot;
     }
     __syncthreads();
     // Units per class and each pair's rank among them, then the classes' starts.

@@ -3,6 +3,7 @@
 // with the built library for the rest.  It launches no kernel.  Prints the name of
 // each group of checks; exits non-zero on a failed one.
 #include "../../paper_1609_03986_amd/csrc/runtime.hip"
+#include "../../paper_1609_03986_amd/csrc/batch_parts.h"
 
 #include <cstdio>
 
@@ -71,10 +72,47 @@ void batch_memory()
     std::puts("batch memory");
 }
 
+// Parts of a train range: none empty, the limits kept.
+void part_rule()
+{
+    for (int tiles : {0, 1, 79, 80, 81, 159, 160, 161, 1279, 1280, 1281, 10000, 65535})
+        for (unsigned long long left : {0ull, 1ull, 512ull * 80, 512ull * 81, 512ull * 5000, 1ull << 40}) {
+            const int parts = train_parts(tiles, left, 512);
+            check(parts >= 1 && parts <= kBatchMaxParts, "part count", tiles, (long long)left, parts);
+            const int per_part = (tiles + parts - 1) / parts;
+            check(parts == 1 || ((parts - 1) * per_part < tiles && tiles >= kMinPartTiles), "no empty part", tiles,
+                  (long long)left, parts);
+        }
+    // The pairs of the GPU test of more divided query groups than slots (31 pairs of 78
+    // groups of 384 queries, train tiles from 16,384 down by a quarter octave): every
+    // pair is divided, and together they want more slots than there are.
+    const int pairs = 31, groups = 78, resident = 512;
+    unsigned long long work[256] = {}, in_class[256] = {};
+    int tiles[pairs];
+    for (int i = 0; i < pairs; ++i) {
+        tiles[i] = (int)std::lround(16384.0 * std::exp2(-i / 4.0));
+        const int c = cost_class(32LL * tiles[i]);
+        work[c] += (unsigned long long)groups * tiles[i];
+        in_class[c] += groups;
+    }
+    int wanted = 0;
+    for (int i = 0; i < pairs; ++i) {
+        const int c = cost_class(32LL * tiles[i]);
+        check(in_class[c] == (unsigned long long)groups, "one pair a class", i, c);
+        unsigned long long left = in_class[c] * tiles[i];
+        for (int later = c + 1; later < 256; ++later) left += work[later];
+        check(train_parts(tiles[i], left, resident) > 1, "divided pair", i, tiles[i]);
+        wanted += groups;
+    }
+    check(wanted > kBatchMaxSlots, "more divided groups than slots", wanted);
+    std::puts("part rule");
+}
+
 }  // namespace
 
 int main()
 {
+    part_rule();
     merge_launch();
     batch_memory();
     return failures ? 1 : 0;

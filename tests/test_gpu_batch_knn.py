@@ -307,3 +307,24 @@ def test_batch_leaves_a_sufficient_workspace_alone(torch_cuda, triplets):
     finally:
         torch.cuda.synchronize()
         lat.close()
+
+
+@pytest.mark.parametrize("p", [0.5, 0.02])
+def test_pairs_refused_a_division(torch_cuda, lat, p):
+    """31 pairs of 78 query groups with train tiles falling by a quarter octave from 16,384: every
+    pair's train range is to be divided (the host test of the rule holds the same sizes), and their
+    2,418 groups want more than the 2,048 slots, so that some pairs stay undivided."""
+    from paper_1609_03986_amd.binding import pair_table
+    g = np.random.default_rng(31)
+    groups, n = 78, 31
+    nq = groups * 384
+    tiles = [int(np.floor(16384 * 2 ** (-i / 4) + 0.5)) for i in range(n)]
+    D = dev(torch_cuda, synth.random_descriptors(g, 32 * tiles[0] // 8, p))
+    D = torch_cuda.cat([D ^ i for i in range(8)])
+    Q = dev(torch_cuda, synth.random_descriptors(g, nq, p))
+    rows = [(0, nq, 5 * i, 32 * t, i * nq) for i, t in enumerate(tiles)]
+    idx, dist, acc = lat.knn_batch(Q, D, pair_table(rows), n * nq, path="fp4")
+    for i, (_, _, first, nt, out) in enumerate(rows):
+        want = lat.knn(Q, D[first:first + nt], path="mfma")
+        for got, w in zip((idx, dist, acc), want):
+            assert bool((got[out:out + nq] == w).all()), i
