@@ -108,10 +108,107 @@ void part_rule()
     std::puts("part rule");
 }
 
+// Split plans within a cap on the partials' bytes, as the allocation-free call makes
+// them: the plan covers the train rows, and its partials fit wherever those of the
+// fewest splits that the index allows do.
+void capped_plans()
+{
+    latch_ctx probe;
+    default_tuning(&probe.tuning);
+    const size_t cap = LATCH_NOALLOC_SCRATCH_BYTES;
+    for (int per_cu : {1, 2, 8, 64})
+        for (int qb : {2, 3})
+            for (int path : {LATCH_PATH_MFMA, LATCH_PATH_POPCOUNT, LATCH_PATH_MFMA_FP4})
+                for (int64_t nq : {1LL, 385LL, 2000LL, 16000LL, 40000LL, 150000LL, 700000LL, 1100000LL, LATCH_MAX_ROWS})
+                    for (int64_t nt : {1LL, 257LL, 2000LL, 16384LL, 16385LL, 100000LL, 1000000LL, LATCH_MAX_ROWS}) {
+                        latch_tuning t = probe.tuning;
+                        t.fp4_query_blocks = (int8_t)qb;
+                        t.mfma_groups_per_cu = t.popcount_groups_per_cu = per_cu;
+                        const int run = resolve_path(&probe, path, nq, nt);
+                        const KnnPlan p = plan_knn(nq, nt, run, 256, t, cap);
+                        const int64_t most = run == LATCH_PATH_MFMA_FP4 ? kFp4MaxSplitRows : kMaxSplitRows;
+                        const int64_t fewest = (nt + most - 1) / most;
+                        check(p.split_rows % kTileRows == 0 && p.split_rows <= most && p.nsplit >= fewest &&
+                                  (int64_t)p.nsplit * p.split_rows >= nt && (p.nsplit - 1) * p.split_rows < nt,
+                              "capped plan covers the rows", nq, nt, p.nsplit);
+                        const size_t need = knn_workspace_bytes(p);
+                        if (fewest == 1 || (size_t)fewest * nq * 16 <= cap)
+                            check(need <= cap || p.nsplit == 1, "capped partials", nq, nt, p.nsplit);
+                        else
+                            check(need > cap, "more than the cap", nq, nt, p.nsplit);
+                    }
+    // The plan depends on the query count through the numbers of query groups of 256
+    // and 384 alone, so the need is largest at multiples of 128 queries.
+    for (int64_t nt : {3000LL, 20000LL, 1000000LL})
+        for (int64_t g = 1; g <= 400; g += g < 40 ? 1 : 13) {
+            const KnnPlan a = plan_knn(128 * g - 127, nt, LATCH_PATH_MFMA_FP4, 256, probe.tuning, SIZE_MAX);
+            const KnnPlan b = plan_knn(128 * g, nt, LATCH_PATH_MFMA_FP4, 256, probe.tuning, SIZE_MAX);
+            check(a.nsplit == b.nsplit && a.split_rows == b.split_rows && a.query_blocks == b.query_blocks,
+                  "plan within a group count", nt, g);
+        }
+    std::puts("capped plans");
+}
+
+// Slots of the 512 triplets as both kinds of handle place them.
+void slots_of_handles()
+{
+    uint32_t rng = 12345;
+    auto next = [&](int n) {
+        rng = rng * 1664525u + 1013904223u;
+        return (int)((rng >> 8) % (uint32_t)n);
+    };
+    for (int kind : {0, 64, 48}) {
+        uint2 toff[kTriplets];
+        for (uint2 &t : toff) {
+            uint32_t o[3];
+            for (uint32_t &x : o)
+                x = kind == 0 ? patch_offset(3 + next(42), 3 + next(42))
+                              : weighted_patch_offset(kind, next(kind - 7), next(kind - 7));
+            t = make_uint2(o[0] | (o[1] << 16), o[2]);
+            check(o[0] < 65536 && o[1] < 65536 && o[2] < 65536, "patch offsets", kind);
+        }
+        uint16_t slot[kTriplets], again[kTriplets];
+        assign_slots(toff, kTriplets, 32, 32, slot);
+        assign_slots(toff, kTriplets, 32, 32, again);
+        int used[kTriplets] = {};
+        for (int t = 0; t < kTriplets; ++t) {
+            check(slot[t] < kTriplets && slot[t] == again[t], "slot", kind, t, slot[t]);
+            if (slot[t] < kTriplets) ++used[slot[t]];
+        }
+        for (int i = 0; i < kTriplets; ++i) check(used[i] == 1, "slots are a permutation", kind, i);
+    }
+    std::puts("slots of handles");
+}
+
+// The tie masks of every angle bin, against each position's unrounded offset.
+void ties()
+{
+    std::vector<int16_t> c(kBins), s(kBins);
+    rotation_table(c.data(), s.data());
+    const std::vector<uint32_t> mask = tie_masks(c.data(), s.data());
+    for (int a = 0; a < kBins; ++a) {
+        uint32_t want = 0;
+        for (int v = -32; v <= 32; ++v)
+            for (int u = -32; u <= 32; ++u) {
+                const bool inner = std::abs(u) <= kHalf && std::abs(v) <= kHalf;
+                const int xy[2] = {c[a] * u - s[a] * v, s[a] * u + c[a] * v};
+                for (int x : xy)
+                    for (int k = 0; k <= 10 && x != 0; ++k)        // sq = 2^k, or an odd multiple
+                        if (((int64_t)x << k) % (1 << 21) == 0 && (((int64_t)x << k) >> 21) % 2 != 0)
+                            want |= (1u << (16 + k)) | (inner ? 1u << k : 0u);
+            }
+        check(mask[a] == want, "tie mask", a, mask[a], want);
+    }
+    std::puts("tie masks");
+}
+
 }  // namespace
 
 int main()
 {
+    capped_plans();
+    slots_of_handles();
+    ties();
     part_rule();
     merge_launch();
     batch_memory();
