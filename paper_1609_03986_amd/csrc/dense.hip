@@ -45,6 +45,7 @@
 namespace latch {
 namespace {
 
+#include "codegen.h"
 #include "fp4.h"
 #include "lanes.h"
 #include "packed16.h"
@@ -326,7 +327,7 @@ struct WindowGeom {
     static_assert(kPlane % 16 == 4, "planes spread over the banks");
     // Wavefronts per SIMD, and so workgroups of four per CU: what LDS and the
     // registers of start values allow.
-        static constexpr int kWaves = RP >= 4 ? 2 : 3;
+    static constexpr int kWaves = RP >= 4 ? 2 : 3;
     static_assert(kWaves * kPlane * 64 <= kLdsPerCu, "workgroups per CU fit the LDS");
 };
 
@@ -342,14 +343,6 @@ __device__ __forceinline__ void insert_keys(int &k1, int &k2, int x, int y)
     const int m = imed3(k1, x, y);
     asm("v_max3_i32 %0, %0, %1, %2" : "+v"(k1) : "v"(x), "v"(y), "v"(m));
     k2 = max(k2, m);
-}
-
-// v, as a value the compiler does not know: what follows from it is computed
-// where it is used instead of being kept in registers over a loop.
-__device__ __forceinline__ int opaque(int v)
-{
-    asm volatile("" : "+v"(v));
-    return v;
 }
 
 template <int RP>

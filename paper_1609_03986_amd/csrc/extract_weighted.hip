@@ -196,13 +196,6 @@ struct PatchRow {
     uint64_t a[2], c[2], e[2];
 };
 
-// One ds_read_b64.  (Atomic, so that the compiler does not pair quadwords into a
-// ds_read2_b64, which gfx950 serves 16 lanes and one address at a time.)
-__device__ __forceinline__ uint64_t read_quad(const uint8_t *p)
-{
-    return __atomic_load_n(reinterpret_cast<const uint64_t *>(p), __ATOMIC_RELAXED);
-}
-
 // One patch row (4 pixel pairs) of sum w d (P_1 + P_2) and sum w d A.
 __device__ __forceinline__ void weighted_row(const uint32_t *wrow, const PatchRow &r, int &sum_p, int &sum_a)
 {

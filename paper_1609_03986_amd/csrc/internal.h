@@ -123,7 +123,7 @@ struct OrderLayout {
     size_t band_base, counts, bucket, rank, order, total;   // byte offsets, total bytes
 };
 OrderLayout order_layout(int n_images, int64_t max_kps);
-// Enqueues the order's five kernels; the order lands at ws + order_layout().order.
+// Enqueues the order's four kernels; the order lands at ws + order_layout().order.
 hipError_t launch_order(const ExtractArgs &a, uint8_t *ws, hipStream_t stream);
 hipError_t launch_extract_weighted(const ExtractArgs &a, hipStream_t stream);
 // LDS byte offset of the top-left pixel (top, left) of a patch in the
@@ -199,7 +199,6 @@ struct KnnShape {
 
 struct KnnSplitArgs {
     const uint32_t *query, *train;
-    KnnShape shape;
     KnnPlan plan;
     uint64_t *partial;
     int k;

@@ -4,6 +4,8 @@
 // namespace latch { namespace { ... } } of each kernel file.
 #pragma once
 
+#include "codegen.h"
+
 typedef const __attribute__((address_space(1))) uint8_t GlobalByte;
 typedef __attribute__((address_space(1))) uint32_t GlobalWord;
 typedef __attribute__((address_space(1))) uint16_t GlobalHalf;
@@ -35,14 +37,6 @@ __device__ __forceinline__ int round_q22(int n)
     return (n + (1 << 21) + (n >> 31)) >> 22;
 }
 
-// v, as a value the compiler does not know, made where it is used: what
-// follows from it is not kept in registers over a loop.
-__device__ __forceinline__ int opaque(int v)
-{
-    asm volatile("" : "+v"(v));
-    return v;
-}
-
 // Offset of m = n + 2^21, with kTies as round_q22 has it for any n.
 template <bool kTies>
 __device__ __forceinline__ int round_half(int m)
@@ -59,13 +53,6 @@ __device__ __forceinline__ int clamp_med3(int x, int lo, int hi)
 
 // 24-bit signed multiplies, kept as such (the compiler would otherwise fold
 // them into quarter-rate 32-bit multiplies by the precomputed sq * C).
-__device__ __forceinline__ int mul_i24(int a, int b)
-{
-    int r;
-    asm("v_mul_i32_i24 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-
 __device__ __forceinline__ int mad_i24(int a, int b, int c)
 {
     int r;

@@ -410,9 +410,7 @@ void release_timed(latch_handle h)
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// Train splits: enough (query group, split) workgroups to fill every CU
-// once (by default two MFMA or eight popcount workgroups per CU),
-// at least 8 tiles (256 rows) per split, split-local indices below 2^21 - 1.
+// Bucket of a row count in the tuning's path table.
 int size_bucket(int64_t n)
 {
     int b = 0;
@@ -822,7 +820,6 @@ int knn_call(latch_handle h, const uint32_t *query_dev, int64_t nq, const uint32
     KnnSplitArgs a;
     a.query = query_dev;
     a.train = train_dev;
-    a.shape = knn_shape(h->tuning);
     a.plan = plan_knn(nq, nt, path, h->num_cus, h->tuning,
                       noalloc ? (size_t)LATCH_NOALLOC_SCRATCH_BYTES : SIZE_MAX);
     a.partial = nullptr;
