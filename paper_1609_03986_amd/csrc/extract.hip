@@ -383,10 +383,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
 // rows that its L2 has to hold: L2 misses per keypoint were 27 lines over 320,000
 // keypoints of 3000 x 2000 images and 74 over 1,280,000; each launch starts them
 // together again.  1,280,000: 3465 -> 3250 us in three, 3205 in five, 3223 in ten;
-// 1,910,000 of uneven images 5890 -> 5450 in four, 5495 in eight.  580,000 of 1280 x 720,
-// which drift costs little, take 0.6% longer in two.
+// 1,910,000 of uneven images 5890 -> 5450 in four, 5495 in eight.  At the lower end, in
+// two instead of one: 800,000 of 3000 x 2000 images 2120 -> 2030 us, 1,014,000 of uneven
+// ones 2720 -> 2600, 800,000 of 1280 x 720 1931 and 1930, 832,000 of 640 x 480 2000 and
+// 1993; 580,000 of 1280 x 720, which drift costs little, would take 0.6% longer.
 constexpr int64_t kSegment = 400000;
-// With a count on the device the launches past it find nothing to do, about 4 us each.
+// With a count on the device, launches are cut by the capacity, and those past the count
+// find nothing to do, about 3 us each.  Four instead of one at a capacity of 2,000,000:
+// 21.9 -> 31.1 us for a count of 1000, 146 -> 151 for 50,000, 1675 -> 1657 for 667,000,
+// 5650 -> 5020 for all.
 constexpr int64_t kMostCounted = 4;
 
 hipError_t launch_extract(const ExtractArgs &a, hipStream_t stream)
@@ -400,14 +405,13 @@ hipError_t launch_extract(const ExtractArgs &a, hipStream_t stream)
     for (int64_t begin = 0; begin < a.n; begin += segment) {
         const int64_t end = std::min(a.n, begin + segment);
         const unsigned blocks = (unsigned)std::min(end - begin, resident);
-        if (a.table)
-            hipLaunchKernelGGL(extract_kernel<true>, dim3(blocks), dim3(kThreads), 0, stream, src, a.kps,
-                               begin, end, a.n_dev, a.rot, a.trip_off, a.bit_of, a.gather, a.desc, a.flags);
-        else
-            hipLaunchKernelGGL(extract_kernel<false>, dim3(blocks), dim3(kThreads), 0, stream, src, a.kps,
-                               begin, end, a.n_dev, a.rot, a.trip_off, a.bit_of, a.gather, a.desc, a.flags);
+        hipLaunchKernelGGL(a.table ? extract_kernel<true> : extract_kernel<false>, dim3(blocks), dim3(kThreads), 0,
+                           stream, src, a.kps, begin, end, a.n_dev, a.rot, a.trip_off, a.bit_of, a.gather,
+                           a.desc, a.flags);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 }  // namespace latch

@@ -268,11 +268,15 @@ hipError_t launch_order(const ExtractArgs &a, uint8_t *ws, hipStream_t stream)
         (unsigned)min((l.max_buckets + kScanThreads - 1) / kScanThreads, (int64_t)a.num_cus);
     hipLaunchKernelGGL(order_bands_kernel, dim3(1 + grid_clear), dim3(kScanThreads), 0, stream, a.table,
                        a.n_images, band_base, counts, l.max_buckets);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(order_count_kernel, dim3(grid_chunks), dim3(kCountThreads), 0, stream, a.kps,
                        a.image_id, a.table, a.n_images, a.n, a.n_dev, band_base, counts, bucket,
                        rank);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(order_scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, band_base,
                        a.n_images, counts);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(order_scatter_kernel, dim3(grid_kps), dim3(kOrderThreads), 0, stream, a.n,
                        a.n_dev, counts, bucket, rank, order);
     return hipGetLastError();
