@@ -943,29 +943,13 @@ __device__ __forceinline__ int64_t claim_unit(BatchState *__restrict__ st, int *
     return it;
 }
 
-// Waits until this wavefront's atomic accesses have been performed.
-__device__ __forceinline__ void wait_accesses() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-// Counts this part, once all its wavefronts have come here: true in the part that
-// arrives last, whose accesses then follow those of all parts.  The workgroup's barrier
-// orders the wavefronts before the count of thread 0, which releases them to the device,
-// and the last part's acquires the others'.  (A release writes the XCD's L2 back, so only
-// one wavefront does: with a device-scope fence in each, 47 pairs around 5000 rows took
-// 390 us and one pair of 20,000 x 20,000 139; with relaxed accesses throughout, which this
-// hardware would also keep in order, 306 and 111.)
-__device__ __forceinline__ bool last_part(uint32_t *done, uint32_t parts, int *last_s)
-{
-    wait_accesses();
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const bool last =
-            __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
-        if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        *last_s = last;
-    }
-    __syncthreads();
-    return *last_s != 0;
-}
+// Waits until this wavefront's device-scope atomic accesses have been performed.
+// All that parts exchange goes through such accesses (the minima, the count, the loads
+// of the last part), which do not stop at an XCD's own L2, so this wait, the barrier and
+// the count order them.  A device-scope fence would also write the XCD's L2 back, in
+// every wavefront of every part: 47 pairs around 5000 rows 390 us with it, 331 without,
+// one pair of 20,000 x 20,000 139 and 120 us.
+__device__ __forceinline__ void wait_device_accesses() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // A part's best two of each query into the query group's slot; the part that
 // arrives last writes the group's outputs.
@@ -991,7 +975,11 @@ __device__ __forceinline__ void fp4_merge_part(const uint64_t (&best)[Fp4Shape<Q
         const uint64_t old = atomicMin(to_u, (unsigned long long)best[t][0]);
         atomicMin(to_u + 1, (unsigned long long)min(best[t][1], max(old, best[t][0])));
     });
-    if (!last_part(done, parts, last_s)) return;
+    wait_device_accesses();
+    __syncthreads();
+    if (threadIdx.x == 0) *last_s = atomicAdd(done, 1u) == parts - 1;
+    __syncthreads();
+    if (!*last_s) return;
     each_query([&](int, uint64_t *from, int qn) {
         store_final(__hip_atomic_load(from, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
                     __hip_atomic_load(from + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), nt, out, qn);
