@@ -244,9 +244,12 @@ constexpr int kBatchSlotQueries = 384;           // of the largest query group
 constexpr int64_t kBatchMaxSlots = 2048;
 constexpr int kBatchMaxParts = 16;
 
+class PartKeys;              // part_keys.h
+class PartCount;
+
 struct BatchSlots {
-    uint64_t *best;
-    uint32_t *done;
+    PartKeys *keys;          // kBatchSlotQueries per slot
+    PartCount *done;
     int count;               // 0: no pair is divided
 };
 

@@ -25,6 +25,7 @@
 
 #include "batch_parts.h"
 #include "internal.h"
+#include "part_keys.h"
 
 namespace latch {
 namespace {
@@ -773,10 +774,7 @@ __global__ __launch_bounds__(256) void knn_popcount_kernel(SplitArgs a)
 // (shorter ones cost more in query fragments and merging than they even out: 48, 64,
 // 96 and 128 were tried) and at most kMaxParts of them.  Long pairs among short ones and the last rounds
 // of a batch of equal pairs are divided, the rest is not.  Parts of a query group
-// meet in a slot, two 64-bit keys per query: with k1 <= k2 the
-// part's best two, old = atomicMin(first, k1), then atomicMin(second,
-// min(k2, max(old, k1))); every k1 but the smallest is the larger of some such
-// pair once, so `second` ends as the second smallest of all.  The part that
+// meet in a slot (PartKeys, part_keys.h), and the part that
 // arrives last writes the outputs, and no part waits for another.  Bound without
 // parts: the longest unit and the last round.  Measured, undivided -> divided, us:
 // 47 pairs of log-normal sizes around 5000 (sigma 1) 637 -> 327, 29 around 2000
@@ -923,10 +921,9 @@ __global__ __launch_bounds__(256) void knn_batch_fill_kernel(const PairInfo *__r
         const int units = pi.groups * (int)pi.parts;
         for (int i = first; i < units; i += step) unit_pair[pi.unit_first + i] = p;
         if (pi.parts == 1) continue;
-        ulonglong2 *best = reinterpret_cast<ulonglong2 *>(slots.best) + (size_t)pi.slot * kBatchSlotQueries;
-        for (int i = first; i < pi.groups * kBatchSlotQueries; i += step)
-            best[i] = make_ulonglong2(kNoNeighbour, kNoNeighbour);
-        for (int i = first; i < pi.groups; i += step) slots.done[pi.slot + i] = 0u;
+        PartKeys *keys = slots.keys + (size_t)pi.slot * kBatchSlotQueries;
+        for (int i = first; i < pi.groups * kBatchSlotQueries; i += step) keys[i].clear();
+        for (int i = first; i < pi.groups; i += step) slots.done[pi.slot + i].clear();
     }
 }
 
@@ -943,20 +940,12 @@ __device__ __forceinline__ int64_t claim_unit(BatchState *__restrict__ st, int *
     return it;
 }
 
-// Waits until this wavefront's device-scope atomic accesses have been performed.
-// All that parts exchange goes through such accesses (the minima, the count, the loads
-// of the last part), which do not stop at an XCD's own L2, so this wait, the barrier and
-// the count order them.  A device-scope fence would also write the XCD's L2 back, in
-// every wavefront of every part: 47 pairs around 5000 rows 390 us with it, 331 without,
-// one pair of 20,000 x 20,000 139 and 120 us.
-__device__ __forceinline__ void wait_device_accesses() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
 // A part's best two of each query into the query group's slot; the part that
 // arrives last writes the group's outputs.
 template <int QB>
 __device__ __forceinline__ void fp4_merge_part(const uint64_t (&best)[Fp4Shape<QB>::kSets][2], int nq,
-                                               int nt, int qgroup, uint32_t parts, uint64_t *slot,
-                                               uint32_t *done, int *last_s, const ItemOut &out)
+                                               int nt, int qgroup, uint32_t parts, PartKeys *slot,
+                                               PartCount *done, int *last_s, const ItemOut &out)
 {
     static_assert(kMfmaWaves * Fp4Shape<QB>::kQueries <= kBatchSlotQueries, "a group fits its slot");
     const int lane = threadIdx.x & 63;
@@ -967,23 +956,16 @@ __device__ __forceinline__ void fp4_merge_part(const uint64_t (&best)[Fp4Shape<Q
             const int b = 4 * t + (lane >> 4);
             const int at = wave * Fp4Shape<QB>::kQueries + 16 * b + (lane & 15);
             const int qn = qgroup * kMfmaWaves * Fp4Shape<QB>::kQueries + at;
-            if (b < Fp4Shape<QB>::kBlocks && qn < nq) f(t, slot + 2 * at, qn);
+            if (b < Fp4Shape<QB>::kBlocks && qn < nq) f(t, PartKeys::of(slot, at), qn);
         }
     };
-    each_query([&](int t, uint64_t *to, int) {
-        auto *to_u = reinterpret_cast<unsigned long long *>(to);
-        const uint64_t old = atomicMin(to_u, (unsigned long long)best[t][0]);
-        atomicMin(to_u + 1, (unsigned long long)min(best[t][1], max(old, best[t][0])));
-    });
+    each_query([&](int t, PartKeys *to, int) { to->merge(best[t][0], best[t][1]); });
     wait_device_accesses();
     __syncthreads();
-    if (threadIdx.x == 0) *last_s = atomicAdd(done, 1u) == parts - 1;
+    if (threadIdx.x == 0) *last_s = done->add_one() == parts - 1;
     __syncthreads();
     if (!*last_s) return;
-    each_query([&](int, uint64_t *from, int qn) {
-        store_final(__hip_atomic_load(from, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
-                    __hip_atomic_load(from + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), nt, out, qn);
-    });
+    each_query([&](int, PartKeys *from, int qn) { store_final(from->first(), from->second(), nt, out, qn); });
 }
 
 enum class BatchKind { kPopcount, kMfmaI8, kMfmaFp4 };
@@ -1038,7 +1020,7 @@ __device__ __forceinline__ void batch_loop(const BatchLoopArgs &a, void *tbuf, i
             } else {
                 const uint32_t slot = a.info[p].slot + (uint32_t)qgroup;
                 fp4_merge_part<QB>(best, (int)e.nq, nt, qgroup, (uint32_t)parts,
-                                   a.slots.best + (size_t)slot * kBatchSlotQueries * 2,
+                                   a.slots.keys + (size_t)slot * kBatchSlotQueries,
                                    a.slots.done + slot, slot_s + 1, out);
             }
         } else {

@@ -13,6 +13,7 @@
 
 #include "../../include/latch.h"
 #include "internal.h"
+#include "part_keys.h"
 
 using namespace latch;
 
@@ -613,7 +614,7 @@ size_t batch_workspace_bytes(int n_pairs, int64_t out_rows) { return batch_layou
 // earlier ones left.
 struct PartMemory {
     int64_t slots, units;
-    size_t best_bytes, done_bytes, total;
+    size_t key_bytes, done_bytes, total;
 };
 
 PartMemory part_memory(int64_t slots, int64_t units)
@@ -621,9 +622,9 @@ PartMemory part_memory(int64_t slots, int64_t units)
     PartMemory m;
     m.slots = slots;
     m.units = units;
-    m.best_bytes = (size_t)slots * kBatchSlotQueries * 2 * sizeof(uint64_t);
-    m.done_bytes = align_up((size_t)slots * sizeof(uint32_t), 256);
-    m.total = m.best_bytes + m.done_bytes + (size_t)units * sizeof(int32_t);
+    m.key_bytes = (size_t)slots * kBatchSlotQueries * sizeof(PartKeys);
+    m.done_bytes = align_up((size_t)slots * sizeof(PartCount), 256);
+    m.total = m.key_bytes + m.done_bytes + (size_t)units * sizeof(int32_t);
     return m;
 }
 
@@ -661,9 +662,9 @@ BatchArgs batch_args(latch_handle h, uint8_t *ws, uint8_t *parts, const PartMemo
     a.unit_pair = reinterpret_cast<int32_t *>(ws + l.info_bytes + 256);
     a.slots = BatchSlots{nullptr, nullptr, 0};
     if (parts && l.item_capacity + m.slots * (kBatchMaxParts - 1) <= m.units) {
-        a.slots = BatchSlots{reinterpret_cast<uint64_t *>(parts),
-                             reinterpret_cast<uint32_t *>(parts + m.best_bytes), (int)m.slots};
-        a.unit_pair = reinterpret_cast<int32_t *>(parts + m.best_bytes + m.done_bytes);
+        a.slots = BatchSlots{reinterpret_cast<PartKeys *>(parts),
+                             reinterpret_cast<PartCount *>(parts + m.key_bytes), (int)m.slots};
+        a.unit_pair = reinterpret_cast<int32_t *>(parts + m.key_bytes + m.done_bytes);
     }
     a.k = k;
     a.ratio = ratio;

@@ -56,7 +56,7 @@ void batch_memory()
                     continue;
                 }
                 const int64_t done = reinterpret_cast<uint8_t *>(a.slots.done) - mem;
-                check(reinterpret_cast<uint8_t *>(a.slots.best) == mem && done >= m.slots * kBatchSlotQueries * 16 &&
+                check(reinterpret_cast<uint8_t *>(a.slots.keys) == mem && done >= m.slots * kBatchSlotQueries * 16 &&
                           done % 256 == 0 && (map - mem) % 256 == 0 && map - mem >= done + 4 * m.slots &&
                           map - mem + 4 * (items + m.slots * (kBatchMaxParts - 1)) <= (int64_t)m.total,
                       "memory of parts", n_pairs, rows);
