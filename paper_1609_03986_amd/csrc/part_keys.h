@@ -52,7 +52,7 @@ private:
     {
         return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    uint64_t words_[2];
+    [[maybe_unused]] uint64_t words_[2];
 };
 static_assert(sizeof(PartKeys) == 16, "a slot's size");
 
@@ -63,7 +63,7 @@ public:
     __device__ __forceinline__ uint32_t add_one() { return atomicAdd(reinterpret_cast<uint32_t *>(this), 1u); }
 
 private:
-    uint32_t n_;
+    [[maybe_unused]] uint32_t n_;
 };
 
 }  // namespace latch
