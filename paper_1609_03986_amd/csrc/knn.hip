@@ -835,76 +835,108 @@ __device__ __forceinline__ int take_slots(int *used, bool wants, int groups, int
     }
 }
 
-// resident: workgroups that run at once; slots: query groups that may be divided.
+// resident: workgroups that run at once; slots: query groups that may be divided (0: no
+// pair is).  Bound by latency, so a thread keeps its first pair in registers between the
+// steps, and a batch that divides no pair has neither a scan of work nor a second count.
 __global__ __launch_bounds__(256) void knn_batch_setup_kernel(
     const PairEntry *__restrict__ pairs, int n_pairs, int64_t query_rows, int64_t train_rows,
     int64_t out_rows, int64_t item_capacity, int group, int resident, int slots,
     PairInfo *__restrict__ info, BatchState *__restrict__ st, uint32_t *__restrict__ flags)
 {
     __shared__ unsigned long long classes[256], works[256], totals[4];
-    __shared__ int bad_s, slots_s;
+    __shared__ int slots_s, longest_s[4];
     const int tid = threadIdx.x;
     classes[tid] = 0;
     works[tid] = 0;
-    if (tid == 0) bad_s = slots_s = 0;
+    if (tid == 0) slots_s = 0;
     __syncthreads();
-    auto groups_of = [&](const PairEntry &e) {
-        return pair_ok(e, query_rows, train_rows, out_rows) ? (e.nq + group - 1) / group : 0;
-    };
-    auto tiles_of = [](const PairEntry &e) { return (int)((e.nt + kTileRows - 1) / kTileRows); };
-    // Items (pair, query group) and their train tiles per class; each pair's rank in
-    // its class goes to info[p].unit_first.
+    // Items (pair, query group) and their train tiles per class.  Until a pair's units
+    // are placed, unit_first is its rank in its class, and until its parts are known,
+    // `parts` its train tiles.
+    PairInfo mine = {};
+    int mine_class = 0;
     bool bad = false;
+    int longest = 0;
     for (int p = tid; p < n_pairs; p += 256) {
         const PairEntry e = pairs[p];
-        bad |= !pair_ok(e, query_rows, train_rows, out_rows);
-        const unsigned long long groups = (unsigned long long)groups_of(e);
+        const bool ok = pair_ok(e, query_rows, train_rows, out_rows);
+        bad |= !ok;
+        const unsigned long long groups = ok ? (unsigned long long)((e.nq + group - 1) / group) : 0ull;
+        const int tiles = ok ? (int)((e.nt + kTileRows - 1) / kTileRows) : 0;
         const int c = cost_class(e.nt);
-        info[p].unit_first = (int32_t)atomicAdd(&classes[c], groups);
-        if (groups) atomicAdd(&works[c], groups * (unsigned long long)tiles_of(e));
+        const PairInfo pi{(int32_t)atomicAdd(&classes[c], groups), (int32_t)groups, (uint32_t)tiles, 0u};
+        if (slots > 0 && groups > 0) {
+            atomicAdd(&works[c], groups * (unsigned long long)tiles);
+            longest = max(longest, tiles);
+        }
+        if (p == tid) {
+            mine = pi;
+            mine_class = c;
+        } else {
+            info[p] = pi;
+        }
     }
-    if (bad) atomicOr(&bad_s, 1);
+    auto each_pair = [&](auto f) {
+        if (tid < n_pairs) f(mine, mine_class);
+        for (int p = tid + 256; p < n_pairs; p += 256) {
+            PairInfo pi = info[p];
+            f(pi, cost_class(pairs[p].nt));
+            info[p] = pi;
+        }
+    };
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) longest = max(longest, __shfl_xor(longest, off));
+    if ((tid & 63) == 0) longest_s[tid >> 6] = longest;
     scan256(classes, totals, tid);
-    scan256(works, totals, tid);
+    longest = max(max(longest_s[0], longest_s[1]), max(longest_s[2], longest_s[3]));
     // The map holds item_capacity items, enough for every batch whose pairs'
     // output ranges do not overlap; a batch that needs more is not run.
     const bool overflow = (int64_t)classes[255] > item_capacity;
-    // Parts and slots.
-    const unsigned long long all_work = works[255];
-    for (int p = tid; p < n_pairs; p += 256) {
-        const PairEntry e = pairs[p];
-        const int64_t groups = overflow ? 0 : groups_of(e);
-        uint32_t parts = 1, slot = 0;
-        if (groups > 0 && groups <= slots) {
-            const int c = cost_class(e.nt), tiles = tiles_of(e);
-            // Work from this pair on: its class's remaining items and later classes.
-            const unsigned long long in_class = classes[c] - (c > 0 ? classes[c - 1] : 0ull);
-            const unsigned long long left = all_work - works[c] +
-                                            (in_class - (uint32_t)info[p].unit_first) * tiles;
-            parts = (uint32_t)train_parts(tiles, left, resident);
+    if (bad || (overflow && tid == 0)) atomicOr(flags, kFlagBadPair);
+    bool divides = !overflow && longest > kMinPartTiles, divided = false;
+    unsigned long long all_work = 0;
+    if (divides) {
+        scan256(works, totals, tid);
+        all_work = works[255];
+        divides = may_divide(longest, classes[255], all_work, resident);
+    }
+    if (divides) {
+        // Parts and slots.
+        each_pair([&](PairInfo &pi, int c) {
+            int parts = 1;
+            if (pi.groups > 0 && pi.groups <= slots) {
+                // Work from this pair on: its class's remaining items and later classes.
+                const unsigned long long in_class = classes[c] - (c > 0 ? classes[c - 1] : 0ull);
+                const unsigned long long left =
+                    all_work - works[c] + (in_class - (uint32_t)pi.unit_first) * pi.parts;
+                parts = train_parts((int)pi.parts, left, resident);
+            }
+            const int slot = take_slots(&slots_s, parts > 1, pi.groups, slots);
+            pi.parts = slot < 0 ? 1u : (uint32_t)parts;
+            pi.slot = slot < 0 ? 0u : (uint32_t)slot;
+            divided |= slot >= 0;
+        });
+    }
+    // With parts, units per class and each pair's rank among them.
+    if (__syncthreads_or(divided)) {
+        classes[tid] = 0;
+        __syncthreads();
+        each_pair([&](PairInfo &pi, int c) {
+            pi.unit_first = (int32_t)atomicAdd(&classes[c], (unsigned long long)pi.groups * pi.parts);
+        });
+        scan256(classes, totals, tid);
+    }
+    each_pair([&](PairInfo &pi, int c) {
+        pi.unit_first += (int32_t)(c > 0 ? classes[c - 1] : 0ull);
+        if (overflow) pi.groups = 0;
+        if (!divides) {
+            pi.parts = 1u;
+            pi.slot = 0u;
         }
-        const int got = take_slots(&slots_s, parts > 1, (int)groups, slots);
-        if (got < 0) parts = 1;
-        else slot = (uint32_t)got;
-        info[p].groups = (int32_t)groups;
-        info[p].parts = parts;
-        info[p].slot = slot;
-    }
-    __syncthreads();
-    // Units per class and each pair's rank among them, then the classes' starts.
-    classes[tid] = 0;
-    __syncthreads();
-    for (int p = tid; p < n_pairs; p += 256)
-        info[p].unit_first = (int32_t)atomicAdd(&classes[cost_class(pairs[p].nt)],
-                                                (unsigned long long)info[p].groups * info[p].parts);
-    scan256(classes, totals, tid);
-    for (int p = tid; p < n_pairs; p += 256) {
-        const int c = cost_class(pairs[p].nt);
-        info[p].unit_first += (int32_t)(c > 0 ? classes[c - 1] : 0ull);
-    }
-    if ((bad_s || overflow) && tid == 0) atomicOr(flags, kFlagBadPair);
+    });
+    if (tid < n_pairs) info[tid] = mine;
     if (tid == 255) {
-        st->units = (int64_t)classes[255];
+        st->units = overflow ? 0 : (int64_t)classes[255];
         st->next_unit = 0;
     }
 }

@@ -83,6 +83,12 @@ void part_rule()
             check(parts == 1 || ((parts - 1) * per_part < tiles && tiles >= kMinPartTiles), "no empty part", tiles,
                   (long long)left, parts);
         }
+    // No division where every range is at most a least part, or where all units start at
+    // once and the longest range hardly exceeds the workgroups' share.
+    check(!may_divide(80, 5, 400, 512) && may_divide(81, 5, 405, 512), "least part");
+    check(!may_divide(87, 504, 504 * 87, 512) && !may_divide(157, 420, 420 * 157, 512), "one full round");
+    check(may_divide(157, 210, 210 * 157, 512) && may_divide(700, 504, 504 * 100, 512), "idle or uneven");
+    check(may_divide(87, 513, 513 * 87, 512), "more than a round");
     // The pairs of the GPU test of more divided query groups than slots (31 pairs of 78
     // groups of 384 queries, train tiles from 16,384 down by a quarter octave): every
     // pair is divided, and together they want more slots than there are.
@@ -95,6 +101,9 @@ void part_rule()
         work[c] += (unsigned long long)groups * tiles[i];
         in_class[c] += groups;
     }
+    unsigned long long all_work = 0;
+    for (unsigned long long w : work) all_work += w;
+    check(may_divide(tiles[0], (unsigned long long)groups * pairs, all_work, resident), "that batch divides");
     int wanted = 0;
     for (int i = 0; i < pairs; ++i) {
         const int c = cost_class(32LL * tiles[i]);
