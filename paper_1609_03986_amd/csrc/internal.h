@@ -274,5 +274,7 @@ struct BatchArgs {
 };
 
 hipError_t launch_knn_batch(const BatchArgs &a, hipStream_t stream);
+// Workgroups of the batched matcher's launch.
+int64_t batch_blocks(const BatchArgs &a);
 
 }  // namespace latch

@@ -37,6 +37,7 @@ void batch_memory()
 {
     latch_ctx h;
     default_tuning(&h.tuning);
+    h.num_cus = 256;
     uint8_t *ws = reinterpret_cast<uint8_t *>(1 << 20), *mem = reinterpret_cast<uint8_t *>(1 << 30);
     auto up = [](size_t v) { return (v + 255) / 256 * 256; };
     for (int n_pairs : {1, 3, 63, 100000, 300000})
@@ -49,6 +50,8 @@ void batch_memory()
                                                nullptr, nullptr, nullptr, rows, LATCH_PATH_MFMA_FP4);
                 const bool fits = items + m.slots * (kBatchMaxParts - 1) <= m.units;
                 check(a.item_capacity == items && a.slots.count == (fits ? m.slots : 0), "slots", n_pairs, rows);
+                const int64_t units = items + std::min<int64_t>(a.slots.count, items) * (kBatchMaxParts - 1);
+                check(batch_blocks(a) == std::min<int64_t>(units, 2 * h.num_cus), "workgroups of a batch", n_pairs, rows);
                 const uint8_t *map = reinterpret_cast<const uint8_t *>(a.unit_pair);
                 if (!fits) {
                     check(map >= ws && map + 4 * items <= ws + batch_workspace_bytes(n_pairs, rows),
