@@ -11,7 +11,8 @@
         in KiB per dispatch, each scaled by what the same counter reads for a
         plain 64 MiB device copy), as markdown; with --json, also recorded as
         "<launch>@<workload>" entries with the sha256 of the kernel's source,
-        which bench.py reads for the roofline's `traffic`.
+        which bench.py reads for the roofline's `traffic`.  --dispatches extract=3
+        says that one launch of that name is three dispatches of its kernel.
 
 A library launch is named as the library's timing events name it: the
 order's four kernels are one "extract_order" launch, and so on.
@@ -140,12 +141,14 @@ def traffic(args):
         launch, source = launch_of(k)
         if launch and k in wv:
             groups[launch][len(fv[k]["FETCH_SIZE"])].append(k)
+    several = {n: int(v) for n, v in (d.split("=") for d in getattr(args, "dispatches", None) or [])}
     per = {}
     for launch, by_count in groups.items():
         for count, ks in sorted(by_count.items(), reverse=True):
             name = launch if count == max(by_count) else "%s [%s]" % (launch, ", ".join(ks))
-            r = sum(sum(fv[k]["FETCH_SIZE"]) / count for k in ks) * 1024.0 * ff
-            w = sum(sum(wv[k]["WRITE_SIZE"]) / len(wv[k]["WRITE_SIZE"]) for k in ks) * 1024.0 * wf
+            each = several.get(launch, 1) if name == launch else 1
+            r = each * sum(sum(fv[k]["FETCH_SIZE"]) / count for k in ks) * 1024.0 * ff
+            w = each * sum(sum(wv[k]["WRITE_SIZE"]) / len(wv[k]["WRITE_SIZE"]) for k in ks) * 1024.0 * wf
             per[name] = [r, w, set(ks), launch_of(ks[0])[1]]
     lines = ["Calibration: a %d MiB device copy reads FETCH_SIZE %.1f KiB and WRITE_SIZE %.1f KiB, "
              "so bytes = FETCH_SIZE x %.4f KiB and WRITE_SIZE x %.4f KiB." % (
@@ -186,6 +189,7 @@ def main(argv=None):
     for name in ("fetch", "write", "fetch-copy", "write-copy", "workload"):
         t.add_argument("--" + name, required=True)
     t.add_argument("--json")
+    t.add_argument("--dispatches", action="append", metavar="LAUNCH=N")
     args = ap.parse_args(argv)
     if args.cmd == "stats":
         print(stats_table(args.csv))

@@ -132,3 +132,23 @@ def test_traffic_calibrates_by_the_copy_and_groups_kernels_into_launches(tmp_pat
     assert o["read_bytes_per_launch"] == pytest.approx(16.0 * 1024 * 2)
     assert o["write_bytes_per_launch"] == pytest.approx(4.0 * 1024)
     assert "| extract |" in text and "Calibration" in text
+
+
+def test_traffic_of_a_launch_of_several_dispatches(tmp_path):
+    """A launch that runs its kernel three times reads and writes three times a dispatch's bytes;
+    kernels that are not that launch, and other launches, stay as they are."""
+    copy = "__amd_rocclr_copyBuffer"
+    batch, single, scan = ["void latch::(anonymous namespace)::%s(int)" % k for k in
+                           ("extract_kernel<true>", "extract_kernel<false>", "order_scan_kernel")]
+    rows = lambda c, size: ([(copy, c, size)] + [(batch, c, 100.0)] * 6 + [(single, c, 7.0)] +
+                            [(scan, c, 4.0)] * 2)
+    Args = type("Args", (), dict(fetch=counter_csv(tmp_path / "f.csv", rows("FETCH_SIZE", 65536.0)),
+                                 write=counter_csv(tmp_path / "w.csv", rows("WRITE_SIZE", 65536.0)),
+                                 workload="toy", json=str(tmp_path / "t.json"), dispatches=["extract=3"]))
+    Args.fetch_copy, Args.write_copy = Args.fetch, Args.write
+    text = ps.traffic(Args)
+    doc = json.load(open(Args.json))["kernels"]
+    assert doc["extract@toy"]["read_bytes_per_launch"] == pytest.approx(300.0 * 1024)
+    assert doc["extract@toy"]["write_bytes_per_launch"] == pytest.approx(300.0 * 1024)
+    assert doc["extract_order@toy"]["read_bytes_per_launch"] == pytest.approx(4.0 * 1024)
+    assert "| extract [extract_kernel<false>] | extract_kernel<false> | 0.01 | 0.01 |" in text
