@@ -332,11 +332,11 @@ int hamming_knn(latch_handle h, const uint32_t *query_dev, int64_t nq,
  * that the library holds on every GPU it runs on until the process ends, not
  * in the handle's workspace: the call never allocates, frees or reserves, and
  * records no timing events.  The split plan is hamming_knn's (the one
- * hamming_knn_workspace_size prices), except that the extra splits the
- * planner may add to fill the last round of workgroups are taken only while
- * the partials fit the scratch; a call whose partials exceed the scratch even
- * without them (16 bytes per (query, train split) when the train rows are
- * split) returns LATCH_ERANGE and enqueues nothing.  Every call on one GPU shares that GPU's scratch:
+ * hamming_knn_workspace_size prices) with no more splits than whose partials
+ * (16 bytes per (query, train split) when the train rows are split) fit the
+ * scratch; a call whose partials exceed it with the fewest splits that the
+ * path's split-local index allows (16,384 rows per split on the FP4 path, 2^21 -
+ * 32 on the others) returns LATCH_ERANGE and enqueues nothing.  Every call on one GPU shares that GPU's scratch:
  * calls that overlap in time on one GPU (any handle, any stream) race, so
  * order them on one stream.  The scratch keeps the last call's contents;
  * nothing in it needs to start at zero.

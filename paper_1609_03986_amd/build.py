@@ -25,7 +25,8 @@ HIPCC_FLAGS = [
     "-Wall", "-Wno-unused-function",
 ]
 # The FP4 matcher's keys are floats that are never NaN; without this every
-# maximum would quiet its operands first.
+# maximum would quiet its operands first.  The ratio test of the same file is safe
+# with it because the host refuses a NaN ratio.
 FILE_FLAGS = {"knn.hip": ["-fno-honor-nans"]}
 _HARMLESS = "'-packed-fp32-ops' is not a recognized feature for this target"
 

@@ -38,8 +38,9 @@ __host__ __device__ inline bool may_divide(int longest, unsigned long long group
 }
 
 // Parts of a train range of `tiles` tiles with `left` tiles of work from its pair on
-// and `resident` workgroups: about left / resident tiles each, within the limits, and
-// no part empty.
+// and `resident` workgroups: as many as of left / resident tiles, or of the least part's,
+// cover it, within the limit, the range then divided evenly (a part has at least half of
+// those tiles) and no part empty.
 __host__ __device__ inline int train_parts(int tiles, unsigned long long left, int resident)
 {
     const unsigned long long share = left / (uint32_t)resident;

@@ -38,8 +38,8 @@
 // What bounds it (1920 x 1080, 55,000 keypoints at threshold 20): every
 // workgroup of a launch is resident at once, so a launch takes its few
 // microseconds of start and staging latency plus its vector work, 407
-// instructions per wavefront in the tile kernel (5 of 12 us) and 690 in the emit
-// kernel (9 of 15 us).  Scoring every pixel one per lane took 17 us, the scan
+// instructions per wavefront in the tile kernel (5 of 10.6 us) and 690 in the emit
+// kernel (9 of 13.2 us).  Scoring every pixel one per lane took 17 us, the scan
 // 4 us and an emit kernel that ran a double atan2 in every wavefront 17 us: 37.7
 // -> 25.0 us per call.  39% of that image's pixels pass the four-pixel test.
 #include "internal.h"

@@ -322,6 +322,9 @@ template <int kW>
 hipError_t launch_weighted_w(const ExtractArgs &a, hipStream_t stream)
 {
     int64_t blocks = a.n;
+    // As many workgroups as the LDS holds.  For W = 48 that is six per CU where five
+    // wavefronts per SIMD let five run at once; with five, 2,000 keypoints take 15.0 ->
+    // 14.0 us, 20,000 92.6 -> 92.2 and 50,000 223.2 -> 224.1.
     const int64_t resident = (int64_t)a.num_cus * (kLdsPerCu / WGeom<kW>::kLds);
     if (blocks > resident) blocks = resident;
     ImageSource src{a.img, a.height, a.width, a.pitch, a.table, a.image_id, a.n_images, nullptr};

@@ -386,7 +386,7 @@ __device__ __forceinline__ void top2_pair(uint64_t &a1, uint64_t &a2, uint64_t c
 // Bound: the matrix cores, and through their power the clock.  On random bits
 // this instruction alone sustains 9.15 PFLOP/s and the 32x32x64 one, which
 // moves twice the accumulator registers per product, 7.55 PFLOP/s; the
-// matcher reaches 7.0 PFLOP/s at 8000 x 1,000,000, since four lane rows select from every block and
+// matcher reaches 6.7 to 7.1 PFLOP/s by machine at 8000 x 1,000,000, since four lane rows select from every block and
 // the selection (12 VALU instructions per 8 MFMAs) shares the issue slots.
 //
 // Tile shape.  A wavefront holds 2 QB blocks of 16 queries (QB = 2 or 3, from
@@ -421,7 +421,7 @@ struct Fp4Shape {
 // Two keys into a running top two (k1 >= k2), as insert_pair_u32 does for
 // integer keys: v_med3_f32, v_max3_f32 and v_max_f32.  (This file is compiled
 // without NaNs in mind: the IEEE-mode maxima would otherwise quiet every operand.
-// Keys are never NaN.)
+// Keys are never NaN, nor is the ratio of the test at the end, which the host checks.)
 __device__ __forceinline__ void insert_pair(float &k1, float &k2, float x, float y)
 {
     k2 = fmaxf(k2, __builtin_amdgcn_fmed3f(k1, x, y));
@@ -770,16 +770,17 @@ __global__ __launch_bounds__(256) void knn_popcount_kernel(SplitArgs a)
 //
 // Parts (FP4 matcher).  A unit should not outlast what is left for everyone: with
 // R train tiles of work from a pair's first item on and S resident workgroups, its
-// train range is divided into parts of about R / S tiles, at least kMinPartTiles
-// (shorter ones cost more in query fragments and merging than they even out: 48, 64,
-// 96 and 128 were tried) and at most kMaxParts of them.  Long pairs among short ones and the last rounds
-// of a batch of equal pairs are divided, the rest is not.  Parts of a query group
-// meet in a slot (PartKeys, part_keys.h), and the part that
-// arrives last writes the outputs, and no part waits for another.  Bound without
-// parts: the longest unit and the last round.  Measured, undivided -> divided, us:
-// 47 pairs of log-normal sizes around 5000 (sigma 1) 637 -> 327, 29 around 2000
-// 262 -> 97, one pair of 20,000 x 20,000 470 -> 116, 15 such pairs 1130 -> 934, 63
-// 3911 -> 3697.  Parts of R / 2 S, 3 R / 4 S and 3 R / 2 S were up to 10% slower.
+// train range is divided into as many parts as hold about R / S tiles each, counted
+// with at least kMinPartTiles (shorter ones cost more in query fragments and merging than
+// they even out: 48, 64, 96 and 128 were tried), and at most kMaxParts (batch_parts.h,
+// which also has the batches that are not divided at all).  Long pairs among short ones
+// and the last rounds of a batch of equal pairs are divided, the rest is not.  Parts of a
+// query group meet in a slot (part_keys.h), the one that arrives last writes the outputs,
+// and none waits for another.  Bound without parts: the longest unit and the last round.
+// Measured, undivided -> divided, us: 47 pairs of log-normal sizes around 5000 (sigma 1)
+// 627 -> 315, 29 around 2000 256 -> 97, one pair of 20,000 x 20,000 476 -> 115, 15 such
+// pairs 1097 -> 908, 63 3794 -> 3602.  Parts of R / 2 S, 3 R / 4 S and 3 R / 2 S were up to
+// 10% slower.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ bool pair_ok(const PairEntry &e, int64_t query_rows, int64_t train_rows,
                                         int64_t out_rows)
