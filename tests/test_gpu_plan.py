@@ -117,3 +117,39 @@ def test_plan_replays_equal_eager_and_oracle(torch_cuda, lat, triplets):
     finally:
         plan.close()
         del keep
+
+
+@pytest.mark.parametrize("path", ["fp4", "mfma", "popcount"])
+def test_plan_of_every_path_with_a_long_pair(torch_cuda, lat, path):
+    """A plan holds the memory for dividing train ranges on the FP4 path and none on the others; a
+    pair long enough to be divided, with short ones, gives what the eager calls give, replay after
+    replay, while an eager batch on the handle divides ranges of its own in between."""
+    from paper_1609_03986_amd.binding import image_table, pair_table
+    torch = torch_cuda
+    g = np.random.default_rng(17)
+    counts = [500, 9000, 40, 700]
+    imgs = [torch.from_numpy(synth.smoothed_noise(g, 200, 260)).cuda() for _ in counts]
+    kps = torch.from_numpy(np.concatenate([synth.random_keypoints(g, c, 200, 260) for c in counts])
+                           .astype(np.float32)).cuda()
+    ids = torch.from_numpy(np.repeat(np.arange(4, dtype=np.int32), counts)).cuda()
+    first = np.concatenate([[0], np.cumsum(counts)[:-1]])
+    pairs = pair_table([(first[i], counts[i], first[i + 1], counts[i + 1], first[i]) for i in range(3)])
+    total, table = sum(counts), image_table(imgs)
+    desc = lat.extract_batch(table, 4, ids, kps)
+    want = (desc,) + lat.knn_batch(desc, desc, pairs, total, path=path)
+    out = [torch.zeros_like(x) for x in want]
+    plan = lat.plan(table, 4, ids, kps, out[0], pairs, out[1], out[2], out[3], path=path)
+    try:
+        for _ in range(3):
+            out[0].zero_()
+            for x, w in zip(out[1:], want[1:]):
+                x.copy_(w)                                   # rows that no pair writes
+                x[:total - counts[3]] = 5
+            plan.run()
+            torch.cuda.synchronize()
+            for x, w in zip(out, want):
+                assert bool((x == w).all())
+            again = lat.knn_batch(desc, desc, pairs, total, path="fp4")
+            assert all(bool((a == w).all()) for a, w in zip(again, want[1:]))
+    finally:
+        plan.close()
