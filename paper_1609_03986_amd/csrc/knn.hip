@@ -1142,16 +1142,17 @@ hipError_t launch_knn_merge(const KnnSplitArgs &a, hipStream_t stream)
     return hipGetLastError();
 }
 
-// Workgroups of a batch: the tuned number per CU, and no more than there can be units.  A
+// Workgroups of a batch: the tuned number per CU, and no more than there can be units (parts
+// only where a train range can exceed a least part).  A
 // workgroup that finds no unit still takes its turn at the counter, some 40 ns, which was
 // most of a small batch's time: 4 pairs of 200 rows 34.0 -> 15.8 us on the FP4 path (31.3
-// with a setup that divided nothing), 36.3 -> 18.2 on int8, 161 -> 30 on popcount.
+// with a setup that divided nothing), 36.3 -> 18.2 on int8, 161 -> 30 on popcount; 63 of 20
+// rows 31.1 -> 13.4 (28.6).
 int64_t batch_blocks(const BatchArgs &a)
 {
     const int64_t resident = (int64_t)a.num_cus * (a.kind == SplitKernel::kPopcount ? 8 : a.shape.batch_groups_per_cu);
-    const int64_t parts = a.kind == SplitKernel::kMfmaFp4
-                              ? std::min<int64_t>(a.slots.count, a.item_capacity) * (kBatchMaxParts - 1)
-                              : 0;
+    const bool divides = a.kind == SplitKernel::kMfmaFp4 && a.train_rows > kMinPartTiles * kTileRows;
+    const int64_t parts = divides ? std::min<int64_t>(a.slots.count, a.item_capacity) * (kBatchMaxParts - 1) : 0;
     return std::min(resident, a.item_capacity + parts);
 }
 

@@ -46,12 +46,14 @@ void batch_memory()
             check(batch_workspace_bytes(n_pairs, rows) == up(16 * (size_t)n_pairs) + 256 + up(4 * (size_t)items),
                   "batch workspace", n_pairs, rows);
             for (const PartMemory &m : {handle_parts(), plan_parts(n_pairs, rows)}) {
-                const BatchArgs a = batch_args(&h, ws, mem, m, nullptr, 0, nullptr, 0, nullptr, n_pairs, 2, 0.8f,
-                                               nullptr, nullptr, nullptr, rows, LATCH_PATH_MFMA_FP4);
+                BatchArgs a = batch_args(&h, ws, mem, m, nullptr, 0, nullptr, LATCH_MAX_ROWS, nullptr, n_pairs, 2,
+                                         0.8f, nullptr, nullptr, nullptr, rows, LATCH_PATH_MFMA_FP4);
                 const bool fits = items + m.slots * (kBatchMaxParts - 1) <= m.units;
                 check(a.item_capacity == items && a.slots.count == (fits ? m.slots : 0), "slots", n_pairs, rows);
                 const int64_t units = items + std::min<int64_t>(a.slots.count, items) * (kBatchMaxParts - 1);
                 check(batch_blocks(a) == std::min<int64_t>(units, 2 * h.num_cus), "workgroups of a batch", n_pairs, rows);
+                a.train_rows = kMinPartTiles * kTileRows;         // no range to divide
+                check(batch_blocks(a) == std::min<int64_t>(items, 2 * h.num_cus), "undivided batch", n_pairs, rows);
                 const uint8_t *map = reinterpret_cast<const uint8_t *>(a.unit_pair);
                 if (!fits) {
                     check(map >= ws && map + 4 * items <= ws + batch_workspace_bytes(n_pairs, rows),
