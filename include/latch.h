@@ -26,7 +26,7 @@
  *       latch_timing_enable, latch_timing_read: the recorded events;
  *       latch_destroy, latch_plan_destroy: the whole device.
  *   - A handle owns device copies of the rotation table and triplet table,
- *     a sticky error word, 13.6 MB for the train ranges that hamming_knn_batch
+ *     a sticky error word, 16.8 MB for the train ranges that hamming_knn_batch
  *     divides over workgroups and a workspace that only latch_reserve sizes.
  *     hamming_knn (with more than one train split), hamming_knn_batch,
  *     latch_detect and large batched extractions need workspace; the
@@ -372,8 +372,8 @@ typedef struct {
  * output ranges should not overlap (they are written concurrently).  k,
  * ratio and path as for hamming_knn.  Uses the handle's workspace
  * (hamming_knn_batch_workspace_size; LATCH_EWORKSPACE if the handle holds
- * less) and, on the FP4 path and for up to 58,000,000 output rows, the handle's
- * room for dividing the train ranges of long pairs over workgroups.
+ * less) and, on the FP4 path while out_rows / 256 + n_pairs < 1,017,000, the
+ * handle's room for dividing the train ranges of long pairs over workgroups.
  */
 int hamming_knn_batch(latch_handle h, const uint32_t *query_dev, int64_t query_rows,
                       const uint32_t *train_dev, int64_t train_rows, const latch_pair *pairs_dev,

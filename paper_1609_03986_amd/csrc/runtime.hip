@@ -628,9 +628,10 @@ PartMemory part_memory(int64_t slots, int64_t units)
     return m;
 }
 
-// A handle's: the units of any batch of up to 58,000,000 output rows.  (Larger ones, of
-// hundreds of rounds of units, are not divided; a plan's memory fits its batch.)
-PartMemory handle_parts() { return part_memory(kBatchMaxSlots, 1 << 18); }
+// A handle's: 2^20 units, so batches of which out_rows / 256 + n_pairs is below 1,017,000.
+// (Larger ones, of a thousand rounds of units, are not divided; a plan's memory fits its
+// batch.)
+PartMemory handle_parts() { return part_memory(kBatchMaxSlots, 1 << 20); }
 
 PartMemory plan_parts(int n_pairs, int64_t out_rows)
 {

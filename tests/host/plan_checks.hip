@@ -41,7 +41,7 @@ void batch_memory()
     uint8_t *ws = reinterpret_cast<uint8_t *>(1 << 20), *mem = reinterpret_cast<uint8_t *>(1 << 30);
     auto up = [](size_t v) { return (v + 255) / 256 * 256; };
     for (int n_pairs : {1, 3, 63, 100000, 300000})
-        for (int64_t rows : {1LL, 1280000LL, 58000000LL, 60000000LL, LATCH_MAX_ROWS}) {
+        for (int64_t rows : {1LL, 1280000LL, 183000000LL, 262000000LL, LATCH_MAX_ROWS}) {
             const int64_t items = rows / 256 + n_pairs + 1;
             check(batch_workspace_bytes(n_pairs, rows) == up(16 * (size_t)n_pairs) + 256 + up(4 * (size_t)items),
                   "batch workspace", n_pairs, rows);
@@ -68,9 +68,9 @@ void batch_memory()
             }
             const PartMemory own = plan_parts(n_pairs, rows);
             check(own.units >= items + own.slots * (kBatchMaxParts - 1), "a plan's parts fit its batch", rows);
-            check(rows > 58000000 || n_pairs > 3 ||
-                      items + kBatchMaxSlots * (kBatchMaxParts - 1) <= handle_parts().units,
-                  "a handle's parts fit ordinary batches", rows);
+            check((rows / 256 + n_pairs < 1017000) ==
+                      (items + kBatchMaxSlots * (kBatchMaxParts - 1) <= handle_parts().units),
+                  "a handle's parts fit ordinary batches", n_pairs, rows);
         }
     check(batch_args(&h, ws, nullptr, handle_parts(), nullptr, 0, nullptr, 0, nullptr, 1, 2, 0.8f, nullptr, nullptr,
                      nullptr, 1, LATCH_PATH_MFMA).slots.count == 0, "no memory, no slots");
