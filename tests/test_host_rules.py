@@ -18,11 +18,13 @@ HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="ROCm compilers not available")
 def test_host_rules(tmp_path):
+    if not os.path.exists(build.LIB):
+        build.build()
     obj, exe = str(tmp_path / "plan_checks.o"), str(tmp_path / "plan_checks")
     compile_it = [HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-Xclang", "-target-feature",
                   "-Xclang", "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-c",
                   os.path.join(HERE, "host", "plan_checks.hip"), "-o", obj]
-    link_it = [HIPCC, "--offload-arch=gfx950", obj, os.path.join(PACKAGE, "liblatch.so"),
+    link_it = [HIPCC, "--offload-arch=gfx950", obj, build.LIB,
                "-Wl,-rpath," + PACKAGE, "-o", exe]
     for cmd in (compile_it, link_it):
         made = subprocess.run(cmd, capture_output=True, text=True)
